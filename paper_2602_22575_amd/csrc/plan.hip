@@ -1,44 +1,34 @@
 // S2O ranking stage for gfx950 (paper Sec. 3.1, Alg. 1, Eqs. (1)-(2)).
 //
-//   kguide_kernel        k_guide = mean of the first key segment (k_mean[0]).
+//   kguide_kernel        partial sums of the first key segment (k_guide = k_mean[0]).
 //   pool_sq_sort_kernel  one workgroup per (z, h, segment): a single pass over the
 //                        segment's Q rows gives q_mean and s_Q; the S scores are then
-//                        Argsort-ed in LDS (bitonic network on 64-bit keys) -> Q_perm.
+//                        Argsort-ed in LDS (block_sort) -> Q_perm.
 //   score_kernel         s_K[n, t] = <q_mean[n], K[t]> as an MFMA contraction per KV head:
 //                        columns = (query head of the group, segment), rows = key tokens
 //                        staged through LDS.  q_mean is split exactly into three bf16 terms
 //                        so that bf16 MFMA reproduces the fp32 x bf16 products exactly (fp32
 //                        accumulation).  The scores are stored (in the caller's s_K array or
-//                        in scratch) together with one sampled score per 64 tokens.
-//                        The Argsort of a prefix row (up to L - S scores) is a sample sort:
-//                        buckets are delimited by splitters taken from a sorted sample of
-//                        the row, so their populations are balanced for any distribution.
-//   splitter_kernel      per prefix row: sorts the sample in LDS and keeps every
-//                        (sample size / buckets)-th value as a splitter.
-//   scatter_kernel       per (row, cell of up to 1024 tokens): (key, token) pairs to their
-//                        bucket.  Every bucket of a row owns a region of twice the average
-//                        population; the cell counts its buckets in LDS, claims a run in each
-//                        region with one atomic add on the row's cursor, and writes its pairs
-//                        staged in LDS sorted by bucket, so that the global stores are runs,
-//                        not scatters.  No counting pass over the scores, no offset scan.
-//   span_kernel          per prefix row: the final cursors are the bucket populations; cuts
-//                        them into spans (runs of consecutive buckets that fit the LDS sort).
-//   count_kernel, scan_exact_kernel, scatter_exact_kernel
-//                        the exact path for rows in which a bucket outgrew its region (many
-//                        equal scores): bucket counts per cell, run offsets (bucket-major,
-//                        cell-minor), scatter to a compact layout.  They loop over a list of
-//                        such rows, which is normally empty.
-//   span_sort_kernel     sorts each span in LDS and writes the token indices at their
-//                        final ranks -> KV_perm.  Linear-time: a second, fine bucketing on
-//                        the score value leaves a few keys per sub-bucket, which are ranked by
-//                        direct comparison; a span whose keys pile up in one sub-bucket
-//                        (many equal scores) falls back to a bitonic network.
-//   big_sort_kernel      fallback for a bucket that alone exceeds the LDS sort (e.g. all
-//                        scores equal): a stable LSD radix sort by one workgroup.
+//                        in scratch) together with one sampled score per 32 tokens.
+//   threshold_kernel     only if some row is longer than one LDS sort: cuts every such row into
+//                        score ranges of about equal population, from the sample.
+//   row_sort_kernel      a row, or one score range of it, is collected in LDS by streaming over
+//                        the row's scores, sorted there (block_sort), and the token indices are
+//                        written at their final ranks -> KV_perm.  The number of keys above the
+//                        range, counted on the way, is its first rank: nothing is exchanged
+//                        between workgroups.
+//   split_sort_kernel    many long rows: a workgroup takes whole rows, deals the keys of a row out
+//                        to its ranges first and sorts range after range.
 //
-// Argsort semantics: descending score, ties by ascending index, -0 == +0.  Every sort works
-// on the 64-bit key (~ordered(score)) << 32 | index, whose ascending order is exactly
-// that order, so no stability property is needed anywhere.
+// Measured against the form this replaces, which scattered (key, token) pairs of all rows to
+// buckets in memory, packed the buckets into spans and sorted those (eight launches of its own,
+// Llama head shape, us): 4K tokens in 512-token segments 76 -> 34 for the whole ranking, 8K 109 ->
+// 52, 32K 285 -> 181, 64K in 1024-token segments 1015 -> 754, 128K 1830 -> 1440, and 3700 -> 1440
+// where far-off scores had sent the old spans to their bitonic network.
+//
+// Argsort semantics: descending score, ties by ascending index, -0 == +0.
+#include <type_traits>
+
 #include "s2o_internal.h"
 
 namespace s2o {
@@ -49,48 +39,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kD = 128;
-constexpr int kNBMax = 64;         // buckets per prefix row (upper bound)
-constexpr int kBucketAvg = 2048;   // target average bucket population
-constexpr int kSampleStride = 64;  // one sampled score per this many tokens
-constexpr int kSpanCap = 4096;     // elements one span_sort workgroup sorts in LDS
-constexpr int kSubBuckets = 2048;  // fine buckets of the in-LDS sort
-constexpr int kSubMax = 64;        // a fuller sub-bucket sends the span to the bitonic fallback
+constexpr int kSampleStride = 32;  // one sampled score per this many tokens
 constexpr int kChunkMax = 1024;    // key tokens per score workgroup (halved while the grid is too small)
-constexpr int kCellMax = 1024;     // key tokens per (row, cell) of the scatter: four per thread (512 tokens and
-                                   // 128 threads: 489 against 476 us at 128K)
-constexpr int kScatterThreads = kCellMax / 4;
 constexpr int kSub = 128;          // key tokens per LDS tile of the score kernel
 constexpr int kScoreWaves = 4;     // wavefronts (row blocks of 32) of a score workgroup.  8 would let all 4 x 64 rows
                                    // of a KV head at 128K share one pass over its K rows (295 against 307 us alone),
                                    // but an 8-wavefront workgroup of 200 registers needs a whole CU at once and
                                    // starves beside the own-segment pass on the second stream (up to 3 ms)
 constexpr int kKStride = 136;      // bf16 elements per K row in LDS (272 B)
-constexpr int kBigGrid = 64;       // workgroups of the fallback sort
-constexpr int kRedoGrid = 2048;    // workgroups of the exact path's kernels (they loop over the redo list)
-
-__host__ __device__ inline int row_buckets(int64_t len) {
-  const int64_t nb = len / kBucketAvg;
-  return nb < 1 ? 1 : (nb > kNBMax ? kNBMax : (int)nb);
-}
-
-// Layout of the (key, token) pairs between the scatter and the sorts.  Every bucket of a row owns
-// a region of bucket_cap(len) slots, twice the average population, and the workgroups of the
-// scatter claim runs inside it from a cursor, so no counting pass over the scores is needed to
-// find a run's place.  (The splitters are every 32nd value of a sorted 1-in-64 sample, so a
-// bucket's population scatters like a Gamma(32) variable around the mean, sigma = 18 %: twice
-// the mean is 5.7 sigma away; one and a half times would send one row in five to the exact
-// path.)  A row in which some bucket does outgrow its region -- many equal scores -- is laid out
-// again by the exact path (count, offsets, scatter), compactly, from the start of its regions.
-// region_base(n): first slot of row n inside its head, a closed-form upper bound of the sum of
-// the earlier rows' regions (nb * cap < 2 * len + 16 * nb; regions start on 128-byte
-// boundaries).
-__host__ __device__ inline uint32_t bucket_cap(int64_t len) {
-  const int64_t avg = len / row_buckets(len);
-  return (uint32_t)((2 * avg + 15) & ~(int64_t)15);
-}
-__host__ __device__ inline int64_t region_base(int64_t n, int64_t S, int64_t L, int nc) {
-  return nc ? n * (2 * L + 16 * kNBMax) : 2 * kv_row_offset(n, S) + n * 16 * kNBMax;
-}
+constexpr int kGuideParts = 8;     // workgroups per KV head summing the first key segment
 
 // float -> uint32 whose unsigned order is the float order (-0 canonicalised to +0)
 __device__ inline uint32_t ordered_u32(float f) {
@@ -101,36 +58,64 @@ __device__ inline uint32_t ordered_u32(float f) {
 __device__ inline float ordered_to_float(uint32_t o) {
   return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
 }
-__device__ inline uint64_t sort_key(float score, uint32_t idx) {
-  return ((uint64_t)(~ordered_u32(score)) << 32) | idx;
-}
 
 __device__ inline float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ inline float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
 // ---------------------------------------------------------------------------------------
+constexpr int kMapBins = 256;      // linear pieces of the map
+// Shapes of the LDS sort: threads and keys per thread; 36 fine buckets per thread.
+template <int kT, int kPer>
+struct SortShape {
+  static constexpr int kThreads = kT, kPerThread = kPer, kCap = kT * kPer;
+  static constexpr int kWords = 12 * kT;                         // bucket words, three buckets each
+  static constexpr size_t pow2(size_t v) { size_t p = 1; while (p < v) p <<= 1; return p; }
+  // byte offsets: bucket words, (score, token) pairs (+ 64 behind them), misc
+  static constexpr size_t kListAt = 4 * (size_t)kWords, kTailAt = kListAt + 8 * ((size_t)kCap + 64);
+  static constexpr size_t kFallback = 8 * pow2(kCap);            // the bitonic network uses everything below misc
+  static constexpr size_t kMiscAt = kTailAt > kFallback ? kTailAt : kFallback;
+  static constexpr size_t kLds = kMiscAt + 256;
+};
+using SmallSort = SortShape<256, 8>;     // 2048 keys, 29 KB: five workgroups per CU
+using MidSort = SortShape<512, 13>;      // 6656 keys, 77 KB: two per CU
+using LargeSort = SortShape<1024, 13>;   // 13312 keys, 153 KB: one per CU
+
+// Rows longer than the sort's capacity are cut into ranges of this many keys on average.  The
+// cuts come from a 1-in-32 sample, so the population of a range of the medium shape scatters by
+// about 8 % of the mean: the capacity is 4.3 sigma away, and a range in 100000 does not fit (with
+// a 1-in-64 sample and ranges of 0.8 of the capacity it was one in 100, and collecting those
+// again cost 140 us at 128K).  A range that does not fit is cut again (row_sort_kernel).
+__host__ __device__ inline int range_target(int cap) { return cap - 7 * (cap / 25); }
+__host__ __device__ inline int row_ranges(int64_t len, int cap) {
+  return len <= cap ? (len > 0 ? 1 : 0) : (int)((len + range_target(cap) - 1) / range_target(cap));
+}
+
+// Split rows: a long row is taken by one workgroup, which first deals its keys out to one region
+// per range (cap pairs each, in its own part of the scratch) and then sorts range after range;
+// the longest rows first.  Alternatively every (row, range) is a piece of its own whose workgroup
+// scans the whole row for its keys: no pairs in memory, and enough pieces when there are few
+// rows, but a row of 128K tokens is scanned 27 times.  Measured (us, splitting / scanning, for the
+// whole ranking): 2016 rows at 128K 1440 / 1900, at 64K 754 / 845; 480 rows at 32K (6 ranges)
+// 215 / 170, at 16K 111 / 91.
+constexpr int kSplitGroups = 512;  // workgroups of the medium shape that fit the chip at once
+constexpr int kSplitRows = 1024;   // split from this many long rows and this many ranges on: below that the longest
+constexpr int kSplitRanges = 6;    // row alone takes too long, or the scans cost less than the dealing out
+constexpr int kMaxSplit = 256;      // ranges of a split row at most (L <= 1M tokens: 219)
+constexpr size_t kSplitLds = 8 * kMaxSplit;   // a row's range counts and lower ends, behind the sort's LDS
+
 struct Scratch {
   float* kguide;      // [Z*Hkv][kGuideParts][128] partial column sums of the first key segment
-  float* qmean;       // [Z*H*N*128]
   uint16_t* qsplit;   // [Z*H*N][3][128] bf16
-  float* samples;     // [Z*H*N][L/64] one score per 64 tokens of the row's prefix
-  float* splitters;   // [Z*H*N][kNBMax] descending; entries past the row's buckets are -inf
-  uint16_t* chist;    // [Z*H*N][maxch][kNBMax] bucket counts per cell of `cell` tokens
-  uint32_t* coffs;    // same shape: offset of the cell inside its row
-  uint32_t* counters; // [0]=#spans [1]=#big spans [2]=error flag [3]=#rows redone by the exact path
-  uint32_t* cursor;   // [Z*H*N][kNBMax] pairs claimed so far in each bucket's region (= its population at the end)
-  uint32_t* rowflag;  // [Z*H*N] != 0: a bucket of the row outgrew its region
-  uint32_t* bst;      // [Z*H*N][kNBMax+1] rank at which each bucket of the row starts
-  int32_t* redo;      // [Z*H*N] rows whose buckets are laid out again by the exact (counting) path
-  int4* spans;        // [max_spans][2]  (row, first rank, end rank, w), (starts of the span's first four buckets)
-  int4* bigspans;     // [max_spans]
+  float* samples;     // [Z*H*N][L/32] one score per 32 tokens of the row's prefix
+  float* thr;         // [Z*H*N][max_ranges + 2] descending; entry r = lower end of range r; then the sample's
+                      // highest and lowest score (from entry [ranges of the row] on)
   float* sk;          // [Z*H*P] s_K, used when the caller does not ask for the scores
-  uint64_t* pairs;    // [Z*H][region_base(N)]: per row one region per bucket (see bucket_cap)
-  int64_t pairs_per_head;
-  uint64_t* alt;      // [kBigGrid * L]
-  int64_t max_spans;
-  int maxch;          // cells per row
-  int cell;           // key tokens per (row, cell) of the bucket counts
+  uint32_t* ticket;   // next row to take, and number of ranges left over (split rows)
+  int2* left_over;    // [rows][max_ranges] (row_id, range) whose keys did not fit their region (split rows)
+  uint64_t* pairs;    // [kSplitGroups][max_ranges][cap] (score, token) pairs by range (split rows)
+  int cap;            // keys of one LDS sort
+  int max_ranges;     // ranges of the longest row
+  bool split;         // long rows are split by one workgroup each, not scanned once per range
   int chunk;          // key tokens per score workgroup: kChunkMax, less for short sequences
   size_t total;
 };
@@ -142,40 +127,31 @@ static Scratch carve(void* base, int Z, int H, int Hkv, int L, int S, int non_ca
   const int64_t rows = (int64_t)Z * H * N;
   const int64_t P = kv_rows_total(N, S, L, non_causal);
   Scratch s;
-  s.max_spans = (int64_t)Z * H * (3 * P / kSpanCap + 2 * N) + 8;
   // one workgroup per (KV head, 128 rows, chunk): keep at least ~1024 of them in the grid
   {
     const int64_t rbg = ((int64_t)(H / Hkv) * N + 32 * kScoreWaves - 1) / (32 * kScoreWaves);
     s.chunk = kChunkMax;
     while (s.chunk > kSub && (int64_t)Z * Hkv * rbg * ((L + s.chunk - 1) / s.chunk) < 1024) s.chunk /= 2;
   }
-  // bucket counts are kept per (row, cell of tokens); one workgroup of the counting and scatter
-  // passes handles one cell: as large as the staging area allows unless the grid gets too small
-  s.cell = kCellMax;
-  while (s.cell > 256 && rows * (((non_causal ? L : L / 2) + s.cell - 1) / s.cell) < 2048) s.cell /= 2;
-  s.maxch = (L + s.cell - 1) / s.cell;
+  const int64_t longest = non_causal ? L : (int64_t)L - S;
+  s.cap = longest <= SmallSort::kCap ? SmallSort::kCap
+          : longest > MidSort::kCap && longest <= LargeSort::kCap ? LargeSort::kCap : MidSort::kCap;
+  s.max_ranges = row_ranges(longest, s.cap);
+  const int64_t long_rows = (int64_t)Z * H * (non_causal ? N : N - 1);
+  s.split = s.max_ranges >= kSplitRanges && long_rows >= kSplitRows;
   size_t off = 0;
   // (integer arithmetic: the size query carves from a null base)
   auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return (char*)((uintptr_t)base + o); };
-  s.kguide = (float*)take((size_t)Z * Hkv * 8 * kD * 4);
-  s.qmean = (float*)take((size_t)rows * kD * 4);
+  s.kguide = (float*)take((size_t)Z * Hkv * kGuideParts * kD * 4);
   s.qsplit = (uint16_t*)take((size_t)rows * 3 * kD * 2);
   s.samples = (float*)take((size_t)rows * (L / kSampleStride) * 4);
-  s.splitters = (float*)take((size_t)rows * kNBMax * 4);
-  s.chist = (uint16_t*)take((size_t)rows * s.maxch * kNBMax * 2);
-  s.coffs = (uint32_t*)take((size_t)rows * s.maxch * kNBMax * 4);
-  s.counters = (uint32_t*)take(64);
-  s.cursor = (uint32_t*)take((size_t)rows * kNBMax * 4);
-  s.rowflag = (uint32_t*)take((size_t)rows * 4);
-  s.bst = (uint32_t*)take((size_t)rows * (kNBMax + 1) * 4);
-  s.redo = (int32_t*)take((size_t)rows * 4);
-  s.spans = (int4*)take((size_t)s.max_spans * 32);
-  s.bigspans = (int4*)take((size_t)s.max_spans * 16);
+  s.thr = (float*)take((size_t)rows * (s.max_ranges + 2) * 4);
+  s.ticket = (uint32_t*)take(64);
+  s.left_over = (int2*)take(s.split ? (size_t)rows * s.max_ranges * 8 : 0);
   s.sk = (float*)take((size_t)Z * H * P * 4);
-  s.pairs_per_head = region_base(N, S, L, non_causal);
-  s.pairs = (uint64_t*)take((size_t)Z * H * s.pairs_per_head * 8);
-  s.alt = (uint64_t*)take((size_t)kBigGrid * L * 8);
-  s.total = off;
+  s.pairs = (uint64_t*)take(s.split ? (size_t)kSplitGroups * s.max_ranges * s.cap * 8 : 0);
+  // the size reported to callers stays at no less than 8 bytes per ranked key
+  s.total = off > (size_t)Z * H * P * 8 ? off : align256((size_t)Z * H * P * 8);
   return s;
 }
 
@@ -211,37 +187,42 @@ hipError_t static_plan_scratch(void** ptr) {
 }
 
 // ---------------------------------------------------------------------------------------
-__global__ void init_kernel(Scratch s, int64_t rows, int32_t* status) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < 16) s.counters[i] = 0;
-  if (i == 0 && status) *status = 0;
-}
-
-// A broken invariant (see the S2O_PLAN_* bits) is recorded in the scratch counters and, if the
-// caller gave one, in the status word; nothing is ever dropped silently.
-__device__ inline void raise(const PlanArgs& a, const Scratch& sc, uint32_t bit) {
-  atomicOr(&sc.counters[2], bit);
+// A broken invariant (see the S2O_PLAN_* bits) is recorded in the caller's status word, which
+// the first kernel of the call clears.
+__device__ inline void raise(const PlanArgs& a, uint32_t bit) {
   if (a.status) atomicOr(reinterpret_cast<unsigned int*>(a.status), bit);
 }
-
-// k_guide[z,g,:] = mean_{s<S} K[z,g,s,:]
-constexpr int kGuideParts = 8;     // workgroups per KV head summing the first key segment
 
 // Partial column sums of the first key segment: workgroup (z, g, part) adds the rows of its
 // eighth of the segment; the consumers add the eight partial sums in a fixed order, so k_guide
 // is reproducible bit for bit without a serial pass over the segment by one workgroup.
 __global__ __launch_bounds__(256) void kguide_kernel(PlanArgs a, Scratch sc) {
   __shared__ float red[16][kD];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (a.status) *a.status = 0;
+    sc.ticket[0] = 0u;
+    sc.ticket[1] = 0u;
+  }
   const int unit = blockIdx.x / kGuideParts, part = blockIdx.x % kGuideParts;
   const int z = unit / a.Hkv, g = unit % a.Hkv;
   const int c = threadIdx.x & 15, r = threadIdx.x >> 4;
   const uint16_t* Kh = a.K + z * a.ks[0] + g * a.ks[1];
   const int rows = a.S / kGuideParts;            // S is a multiple of 64
+  const int end = (part + 1) * rows;
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int row = part * rows + r; row < (part + 1) * rows; row += 16) {
-    const u32x4 v = *reinterpret_cast<const u32x4*>(Kh + (int64_t)row * a.ks[2] + 8 * c);
+  for (int row0 = part * rows + r; row0 < end; row0 += 16 * 4) {   // four loads in flight
+    u32x4 v4[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) { acc[2 * q] += bf16_lo(v[q]); acc[2 * q + 1] += bf16_hi(v[q]); }
+    for (int u = 0; u < 4; ++u)
+      v4[u] = *reinterpret_cast<const u32x4*>(Kh + (int64_t)min(row0 + 16 * u, end - 1) * a.ks[2] + 8 * c);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (row0 + 16 * u < end) {
+        const u32x4 v = v4[u];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { acc[2 * q] += bf16_lo(v[q]); acc[2 * q + 1] += bf16_hi(v[q]); }
+      }
+    }
   }
 #pragma unroll
   for (int j = 0; j < 8; ++j) red[r][8 * c + j] = acc[j];
@@ -252,6 +233,27 @@ __global__ __launch_bounds__(256) void kguide_kernel(PlanArgs a, Scratch sc) {
     for (int i = 0; i < 16; ++i) s += red[i][threadIdx.x];
     sc.kguide[(int64_t)blockIdx.x * kD + threadIdx.x] = s;
   }
+}
+
+// ---------------------------------------------------------------------------------------
+// Sum over the lanes up to and including this one (data-parallel-primitive moves, no LDS).
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);    // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);    // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);    // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);    // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 -> rows 1, 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 -> rows 2, 3
+  return x;
+}
+
+// A value that is the same in every lane, as the scalar it is.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+// The same value, but unknown to the optimiser from here on: what is computed from it is not
+// kept in registers across phases (or hoisted out of a loop that normally runs once).
+__device__ __forceinline__ int fresh(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
 // In-LDS bitonic sort of n2 (power of two) 64-bit keys, ascending.
@@ -270,14 +272,267 @@ __device__ inline void bitonic_sort_lds(uint64_t* keys, int n2, int tid, int nth
   }
 }
 
-__device__ inline int next_pow2(int v) { int p = 1; while (p < v) p <<= 1; return p; }
+// LDS of one sort.
+template <class Shape>
+struct SortLds {
+  uint32_t* word;     // [kWords] three 6-bit bucket counters, later the words' first place above them;
+                      // then the list of keys that share a bucket
+  uint64_t* list;     // [kCap + 64] (score, token) pairs: as collected, then in bucket order, then (tokens) in final order
+  uint64_t* all;      // everything below misc, for the bitonic network
+  uint32_t* misc;     // 64 words
+  uint64_t* map;      // [kMapBins] (the list's area, free while the keys are in registers) first bucket word
+                      // and bucket words of a linear piece, as floats
+  __device__ explicit SortLds(unsigned char* smem) {
+    word = reinterpret_cast<uint32_t*>(smem);
+    list = reinterpret_cast<uint64_t*>(smem + Shape::kListAt);
+    all = reinterpret_cast<uint64_t*>(smem);
+    misc = reinterpret_cast<uint32_t*>(smem + Shape::kMiscAt);
+    map = list;
+  }
+};
 
+// What the sort takes for a score: NaN (an input error) counts as -inf.
+__device__ __forceinline__ float sort_score(float s) { return s == s ? s : -INFINITY; }
+__device__ __forceinline__ uint64_t pair_of(float s, uint32_t tok) { return ((uint64_t)tok << 32) | __float_as_uint(s); }
+__device__ __forceinline__ float pair_score(uint64_t p) { return __uint_as_float((uint32_t)p); }
+__device__ __forceinline__ uint32_t pair_token(uint64_t p) { return (uint32_t)(p >> 32); }
+// 1 if pair p comes before the key (s, tok), else 0; no branches
+__device__ __forceinline__ uint32_t ahead_of(uint64_t p, float s, uint32_t tok) {
+  return (uint32_t)(pair_score(p) > s) | ((uint32_t)(pair_score(p) == s) & (uint32_t)(pair_token(p) < tok));
+}
+
+// Sorts n keys (1 <= n <= kCap) by (score descending, token ascending) and writes the tokens to
+// out[0..n).  Key t + e * kThreads is (f[e], tok[e]) of thread t.  Every thread of the workgroup
+// calls it after a barrier behind which the LDS is free; a caller that uses the LDS again puts a
+// barrier in front.  bounded: all scores are known to lie in [flo, fhi]; otherwise the range is
+// found first.
+//
+// Linear time: a monotone map of the score to 36 x kThreads fine buckets (about three per key) by
+// one counting atomic, which also ranks the key inside its bucket, a scan of the counters, and
+// every key is put at its bucket's place.  What is left is the order inside a bucket: keys that
+// share one, about a quarter, are listed, and a full set of lanes works on the list: each is
+// compared with its bucket's pairs and its token put at its final place.  (Comparing from where
+// the keys are, three lanes in four idle, took 37 instead of 17 vector instructions per 64 keys.)
+// A bucket of over 60 keys (many equal scores, or an outlier that stretches the range) sends the
+// whole set to a bitonic network instead.
+//
+// What bounds it is LDS and vector instructions alike: per 64 keys one atomic, one random 4-byte
+// read and one random 8-byte write, 9 to 12 clocks each, the list about the same again; and about
+// 60 vector instructions.  Three 6-bit counters and the 14-bit place share a word so that one
+// read gives all of them.  Wavefronts without keys in a row of kThreads skip it.
+template <class Shape>
+__device__ __forceinline__ void block_sort(const SortLds<Shape>& m, int n, float (&f)[Shape::kPerThread],
+                                           uint32_t (&tok)[Shape::kPerThread], bool bounded, float flo, float fhi,
+                                           int32_t* out) {
+  constexpr int T = Shape::kThreads, kPer = Shape::kPerThread, kWaves = T / 64;
+  constexpr int kW = Shape::kWords / T;             // bucket words of a thread
+  static_assert(Shape::kCap <= 16384 && kW % 4 == 0, "packing of the bucket words");
+  const int tid = fresh(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int left = n - tid;                               // key e exists iff e * T < left
+  uint32_t* const wlo = m.misc;                     // [16]
+  uint32_t* const whi = m.misc + 16;                // [16]
+  uint32_t* const wsum = m.misc + 32;               // [16]
+  uint32_t* const crowded = m.misc + 48;
+  uint32_t* const nlist = m.misc + 49;
+  u32x4* const w4 = reinterpret_cast<u32x4*>(m.word);
+  {
+    const u32x4 z = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int k = 0; k < kW / 4; ++k) w4[tid + k * T] = z;
+  }
+  if (tid == 0) { *crowded = 0u; *nlist = 0u; }
+  // scale: bucket words per unit of the score for a bounded set, map pieces per unit otherwise;
+  // 0 (everything in the first) for an empty or infinite range
+  float scale;
+  if (bounded) {
+    const float range = fhi - flo;
+    scale = range > 0.f ? ((float)Shape::kWords - 0.5f) / range : 0.f;   // below kWords for every score of the range
+    __syncthreads();
+  } else {
+    float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      const bool mine = tid + e * T < n;
+      lo = fminf(lo, mine ? f[e] : INFINITY);
+      hi = fmaxf(hi, mine ? f[e] : -INFINITY);
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) { lo = fminf(lo, __shfl_xor(lo, d)); hi = fmaxf(hi, __shfl_xor(hi, d)); }
+    if (lane == 0) { wlo[wave] = __float_as_uint(lo); whi[wave] = __float_as_uint(hi); }
+    uint32_t* const hist = reinterpret_cast<uint32_t*>(m.map) + kMapBins;   // (the upper half of the map's area)
+    for (int i = tid; i < kMapBins; i += T) hist[i] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      lo = fminf(lo, __uint_as_float(wlo[w]));
+      hi = fmaxf(hi, __uint_as_float(whi[w]));
+    }
+    flo = lo; fhi = hi;
+    const float range = fhi - flo;
+    scale = range > 0.f ? ((float)kMapBins - 0.5f) / range : 0.f;
+    // The first and the last range of a row, and whole rows, are far from evenly filled (tails, a
+    // few far-off keys).  Half of the buckets are spread over the score range evenly, the other
+    // half follows a sample, the first key of every thread.
+    if (tid < n) atomicAdd(&hist[min((uint32_t)((fhi - f[0]) * scale), (uint32_t)(kMapBins - 1))], 1u);
+    __syncthreads();
+    if (tid < 64) {                                 // one wavefront, four pieces per lane; 1/16 bucket words, exact in fp32
+      const u32x4 c = reinterpret_cast<const u32x4*>(hist)[tid];
+      const uint32_t per_bin = 8u * Shape::kWords / kMapBins, per_key = (8u * Shape::kWords - 16u) / (uint32_t)min(n, T);
+      uint32_t at = wave_inclusive_sum(c[0] + c[1] + c[2] + c[3]) - (c[0] + c[1] + c[2] + c[3]);
+      at = at * per_key + 4u * tid * per_bin;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t len = per_bin + c[k] * per_key;
+        // (the wavefront has read every count of the upper half before the first is overwritten)
+        m.map[4 * tid + k] = ((uint64_t)__float_as_uint((float)len * 0.0625f) << 32) | __float_as_uint((float)at * 0.0625f);
+        at += len;
+      }
+    }
+    __syncthreads();
+  }
+  left = fresh(left);
+  // ---- count: pk = word | shift of the counter << 14 | rank << 19
+  uint32_t pk[kPer], old[kPer];
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    if (e * T < left) {
+      float y = (fhi - f[e]) * scale;
+      if (!bounded) {                               // monotone: a piece ends where the next one begins
+        const uint32_t b = min((uint32_t)y, (uint32_t)(kMapBins - 1));
+        const uint64_t piece = m.map[b];
+        y = fmaf(__uint_as_float((uint32_t)(piece >> 32)), fminf(y - (float)b, 1.0f), __uint_as_float((uint32_t)piece));
+      }
+      const uint32_t w = min((uint32_t)y, (uint32_t)(Shape::kWords - 1));
+      const uint32_t sh = __umul24((uint32_t)(3.0f * __builtin_amdgcn_fractf(y)), 6u);   // (three fractions are below 3)
+      // (24-bit: a 32-bit multiply takes four times as long)
+      old[e] = atomicAdd(&m.word[w], 1u << (sh & 31u));
+      pk[e] = (fresh(sh) << 14) | w;              // (not folded into a multiply)
+    }
+  }
+  uint32_t most = 0;
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    if (e * T < left) {
+      const uint32_t r = __builtin_amdgcn_ubfe(old[e], pk[e] >> 14, 6u);
+      most = max(most, r);
+      pk[e] |= r << 19;
+    }
+  }
+  if (most >= 60u) *crowded = 1u;
+  __syncthreads();
+  // ---- first place of every word's first bucket, into the word
+  {
+    u32x4 x[kW / 4];
+    uint32_t s[kW], run = 0;
+#pragma unroll
+    for (int k = 0; k < kW / 4; ++k) x[k] = w4[kW / 4 * tid + k];
+#pragma unroll
+    for (int k = 0; k < kW; ++k) {
+      const uint32_t w = x[k / 4][k % 4];
+      s[k] = run;
+      run += (w & 63u) + __builtin_amdgcn_ubfe(w, 6u, 6u) + __builtin_amdgcn_ubfe(w, 12u, 6u);
+    }
+    const uint32_t incl = wave_inclusive_sum(run);
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t base = incl - run;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) base += w < wave ? wsum[w] : 0u;
+#pragma unroll
+    for (int k = 0; k < kW; ++k) x[k / 4][k % 4] |= (base + s[k]) << 18;
+#pragma unroll
+    for (int k = 0; k < kW / 4; ++k) w4[kW / 4 * tid + k] = x[k];
+  }
+  const bool fallback = __builtin_amdgcn_readfirstlane((int)*crowded) != 0;
+  __syncthreads();
+  if (!fallback) {
+    left = fresh(left);
+    // ---- place.  A key alone in its bucket is where it belongs; the others go to a list:
+    // first place of the bucket | population << 14 | rank << 20
+#pragma unroll
+    for (int e = 0; e < kPer; ++e)
+      if (e * T < left) old[e] = m.word[pk[e] & 0x3fffu];
+    uint32_t shared = 0;                            // bit e: key e shares its bucket
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      if (e * T < left) {
+        const uint32_t sh = __builtin_amdgcn_ubfe(pk[e], 14u, 5u), r = pk[e] >> 19;
+        const uint32_t below = old[e] & ((1u << sh) - 1u);
+        const uint32_t p0 = (old[e] >> 18) + (below & 63u) + (below >> 6), c = __builtin_amdgcn_ubfe(old[e], sh, 6u);
+        m.list[p0 + r] = pair_of(f[e], tok[e]);
+        pk[e] = p0 | (c << 14) | (r << 20);
+        shared |= c > 1u ? 1u << e : 0u;
+      }
+    }
+    __syncthreads();                                // the bucket words are free now: the list goes there
+    {
+      const uint32_t cnt = (uint32_t)__builtin_popcount(shared);
+      const uint32_t incl = wave_inclusive_sum(cnt);
+      const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+      uint32_t at = 0;
+      if (lane == 0) at = atomicAdd(nlist, total);
+      at = uniform(at);
+      if (at + total <= (uint32_t)Shape::kWords) {
+        at += incl - cnt;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e)
+          if (shared & (1u << e)) m.word[at++] = pk[e];
+      }
+    }
+    __syncthreads();
+    const int listed = (int)uniform(*nlist);
+    if (listed <= Shape::kWords) {                  // (a list that does not fit: full buckets everywhere)
+      constexpr int kHold = Shape::kWords / T;      // listed keys of a thread
+      const int mine = listed - tid;                // listed key k exists iff k * T < mine
+      uint32_t to[kHold], tk[kHold];
+#pragma unroll
+      for (int k = 0; k < kHold; ++k) {
+        if (k * T < mine) {
+          const uint32_t w = m.word[tid + k * T], p0 = w & 0x3fffu, c = __builtin_amdgcn_ubfe(w, 14u, 6u);
+          const uint64_t me = m.list[p0 + (w >> 20)];
+          const float s = pair_score(me);
+          tk[k] = pair_token(me);
+          to[k] = p0;
+          uint64_t x[3];
+#pragma unroll
+          for (int q = 0; q < 3; ++q) x[q] = m.list[p0 + q];   // (pairs past the bucket come later than it)
+#pragma unroll
+          for (int q = 0; q < 3; ++q) to[k] += (uint32_t)q < c ? ahead_of(x[q], s, tk[k]) : 0u;
+#pragma unroll 1
+          for (uint32_t q = 3; q < c; ++q) to[k] += ahead_of(m.list[p0 + q], s, tk[k]);
+        }
+      }
+      __syncthreads();
+      uint32_t* const token = reinterpret_cast<uint32_t*>(m.list) + 1;
+#pragma unroll
+      for (int k = 0; k < kHold; ++k)
+        if (k * T < mine) token[2 * to[k]] = tk[k];
+      __syncthreads();
+      for (int i = tid; i < n; i += T) out[i] = (int32_t)token[2 * i];
+      return;
+    }
+    __syncthreads();
+  }
+  int n2 = 1;
+  while (n2 < n) n2 <<= 1;
+  for (int i = n + tid; i < n2; i += T) m.all[i] = ~0ull;
+#pragma unroll
+  for (int e = 0; e < kPer; ++e)
+    if (tid + e * T < n) m.all[tid + e * T] = ((uint64_t)(~ordered_u32(f[e])) << 32) | tok[e];
+  __syncthreads();
+  bitonic_sort_lds(m.all, n2, tid, T);
+  for (int i = tid; i < n; i += T) out[i] = (int32_t)(uint32_t)m.all[i];
+}
+
+// ---------------------------------------------------------------------------------------
 // One workgroup per (z, h, n): q_mean, s_Q and Q_perm of the segment in one pass over Q.
+template <class Shape>
 __global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch sc) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int n2 = next_pow2(a.S);
-  uint64_t* keys = reinterpret_cast<uint64_t*>(smem);               // [n2]
-  float* red = reinterpret_cast<float*>(smem + (size_t)n2 * 8);     // [4 wavefronts][128]
+  static_assert(Shape::kThreads == 256, "the row loop is written for 256 threads");
+  float* sq = reinterpret_cast<float*>(smem);                       // [S] scores; the sort's LDS later
+  float* red = sq + Shape::kCap;                                    // [4 wavefronts][128]
+  static_assert(4 * (size_t)Shape::kCap >= 4 * 4 * kD, "the partial sums fit behind the scores");
 
   const int G = a.H / a.Hkv;
   const int64_t row_id = blockIdx.x;                                // (z*H + h)*N + n
@@ -301,10 +556,6 @@ __global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch s
 #pragma unroll
     for (int j = 0; j < 8; ++j) a.k_guide[((int64_t)z * a.Hkv + g) * kD + 8 * c + j] = kgv[j];
   }
-
-  // the scatter's bucket cursors of this row start at zero
-  if (tid < kNBMax) sc.cursor[row_id * kNBMax + tid] = 0u;
-  if (tid == kNBMax) sc.rowflag[row_id] = 0u;
 
   // Four rows of a thread per trip, all four 16-byte loads issued before the first is used
   // (S is a multiple of 64: no tail).
@@ -331,12 +582,11 @@ __global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch s
       dot += __shfl_xor(dot, 2);
       dot += __shfl_xor(dot, 1);
       if (c == 0) {
-        keys[row] = sort_key(dot, (uint32_t)row);
+        sq[row] = dot;
         if (a.s_q) a.s_q[row_id * a.S + row] = dot;
       }
     }
   }
-  for (int i = a.S + tid; i < n2; i += 256) keys[i] = ~0ull;
   // ---- q_mean: column sums over the wavefront's four row groups, then over the wavefronts
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -351,7 +601,6 @@ __global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch s
   if (tid < kD) {
     float s = (red[tid] + red[kD + tid]) + (red[2 * kD + tid] + red[3 * kD + tid]);
     s *= 1.0f / (float)a.S;
-    sc.qmean[row_id * kD + tid] = s;
     if (a.q_mean) a.q_mean[row_id * kD + tid] = s;
     // exact three-way bf16 split (truncation keeps every step exact in fp32)
     const uint32_t u = __float_as_uint(s);
@@ -364,8 +613,17 @@ __global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch s
     qs[kD + tid] = (uint16_t)(__float_as_uint(mid) >> 16);
     qs[2 * kD + tid] = (uint16_t)(__float_as_uint(lo) >> 16);   // 8 bits left: exact
   }
-  bitonic_sort_lds(keys, n2, tid, 256);
-  for (int i = tid; i < a.S; i += 256) a.q_perm[row_id * a.S + i] = (int32_t)(uint32_t)keys[i];
+  float f[Shape::kPerThread];
+  uint32_t tok[Shape::kPerThread];
+#pragma unroll
+  for (int e = 0; e < Shape::kPerThread; ++e) {
+    const int i = tid + e * 256;
+    tok[e] = (uint32_t)i;
+    f[e] = sort_score(i < a.S ? sq[i] : 0.f);
+  }
+  __syncthreads();                                // the scores and partial sums have been read
+  const SortLds<Shape> m(smem);
+  block_sort<Shape>(m, a.S, f, tok, false, 0.f, 0.f, a.q_perm + row_id * a.S);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -408,10 +666,16 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(PlanArgs a, Scr
   const int rb = kScoreWaves * rbg + wave;
 
   auto row_limit = [&](int r) { return r < R ? (int)kv_row_len(r % a.N, a.S, a.L, a.non_causal) : 0; };
+  // longest of the rows first .. first + count - 1 (row r has segment r % N: if the run wraps it
+  // contains a last segment, else its own last row is the longest)
+  auto run_limit = [&](int first, int count) {
+    const int last = min(first + count, R) - 1;
+    if (first > last) return 0;
+    return (int)kv_row_len(first / a.N != last / a.N ? a.N - 1 : last % a.N, a.S, a.L, a.non_causal);
+  };
   // token limits: of the workgroup's rows (uniform) and of this wavefront's rows
-  int lim_wg = 0, lim_wave = 0;
-  for (int i = 0; i < 32 * kScoreWaves; ++i) lim_wg = max(lim_wg, row_limit(32 * kScoreWaves * rbg + i));
-  for (int i = 0; i < 32; ++i) lim_wave = max(lim_wave, row_limit(32 * rb + i));
+  const int lim_wg = run_limit(32 * kScoreWaves * rbg, 32 * kScoreWaves);
+  const int lim_wave = run_limit(32 * rb, 32);
   const int t_begin = chunk * sc.chunk;
   if (t_begin >= lim_wg) return;
   const int t_end = min(t_begin + sc.chunk, lim_wg);
@@ -481,14 +745,10 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(PlanArgs a, Scr
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk], bq[tt][kk], acc, 0, 0, 0);
         // lim is a multiple of 64, so a 32-token block is valid for this row as a whole or not at all
         if (t0 + 32 * sb < lim) {
-          // sample: one token of every 64, at a position that varies from block to block
+          // sample: one token of the 32, its place among eight varying from block to block
           const int blk = (t0 + 32 * sb) / kSampleStride;
-          const int off = ((blk * 37 + 11) & 63) - 32 * (sb & 1);   // offset inside this 32-token block
-          if (off >= 0 && off < 32 && ((off >> 2) & 1) == hh) {
-            const int idx = 4 * (off >> 3) + (off & 3);               // register holding that token
-            float v = acc[0];
-#pragma unroll
-            for (int i = 1; i < 16; ++i) v = idx == i ? acc[i] : v;
+          if (((blk >> 2) & 1) == hh) {
+            const float v = (blk & 2) ? ((blk & 1) ? acc[15] : acc[10]) : ((blk & 1) ? acc[5] : acc[0]);
             sc.samples[row_id * samples_per_row + blk] = v;
           }
           // the four registers of a group are four consecutive tokens
@@ -504,678 +764,562 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(PlanArgs a, Scr
   }
 }
 
-__device__ inline int64_t row_base(const PlanArgs& a, int64_t row_id) {
-  const int n = (int)(row_id % a.N);
-  const int64_t zh = row_id / a.N;
+__device__ inline int64_t row_base(const PlanArgs& a, int64_t zh, int n) {
   return zh * kv_rows_total(a.N, a.S, a.L, a.non_causal) + kv_row_start(n, a.S, a.L, a.non_causal);
 }
 
-// First pair slot of a row's regions.
-__device__ inline uint64_t* row_pairs(const PlanArgs& a, const Scratch& sc, int64_t row_id) {
-  const int n = (int)(row_id % a.N);
-  return sc.pairs + (row_id / a.N) * sc.pairs_per_head + region_base(n, a.S, a.L, a.non_causal);
-}
-// The same two for a row given as (head index zh = z*H + h, segment n): the sorts look rows up
-// once per span and per thread, where the 64-bit divisions above would cost as much as ranking
-// a few keys.
-__device__ inline int64_t row_base(const PlanArgs& a, int zh, int n) {
-  return (int64_t)zh * kv_rows_total(a.N, a.S, a.L, a.non_causal) + kv_row_start(n, a.S, a.L, a.non_causal);
-}
-__device__ inline uint64_t* row_pairs(const PlanArgs& a, const Scratch& sc, int zh, int n) {
-  return sc.pairs + (int64_t)zh * sc.pairs_per_head + region_base(n, a.S, a.L, a.non_causal);
-}
-
-// Bucket of a score = number of the row's (descending) splitters above it.  Two levels, both
-// by counting instead of a dependent binary search: every 8th splitter sits in a register
-// (top[k] = splitter 8k+7), the group of 7 below the hit comes from LDS with two 16-byte reads.
-__device__ inline int bucket_of_score(const float* spl, const float (&top)[7], float sv) {
-  int gi = 0;
-#pragma unroll
-  for (int k = 0; k < 7; ++k) gi += top[k] > sv ? 1 : 0;
-  const f32x4 lo = *reinterpret_cast<const f32x4*>(spl + 8 * gi);
-  const f32x4 hi = *reinterpret_cast<const f32x4*>(spl + 8 * gi + 4);
-  int bk = 8 * gi;
-  bk += lo[0] > sv ? 1 : 0; bk += lo[1] > sv ? 1 : 0; bk += lo[2] > sv ? 1 : 0; bk += lo[3] > sv ? 1 : 0;
-  bk += hi[0] > sv ? 1 : 0; bk += hi[1] > sv ? 1 : 0; bk += hi[2] > sv ? 1 : 0;
-  return bk;
-}
-
-// Counting and scatter passes of the sample sort, streaming over the stored scores: one
-// workgroup per (prefix row, cell of sc.cell tokens), threads striding over the tokens.  All
-// lanes work on the same row, so the splitter reads are broadcasts, the kernels need a few
-// dozen registers, and enough wavefronts are resident to hide the LDS round trips
-// (re-computing the scores with MFMA in these passes kept them latency-bound at a quarter
-// of the issue rate).
-// Exact path, pass 1 (only for the rows on the redo list): bucket counts per cell.
-__global__ __launch_bounds__(256) void count_kernel(PlanArgs a, Scratch sc, int64_t rows) {
-  __shared__ __attribute__((aligned(16))) float spl[kNBMax];
-  __shared__ uint32_t cnt[kNBMax];
-  const int64_t nredo = min((int64_t)sc.counters[3], rows);
-  for (int64_t item = blockIdx.x; item < nredo * sc.maxch; item += gridDim.x) {
-    const int64_t row_id = sc.redo[item / sc.maxch];
-    const int cellno = (int)(item % sc.maxch);
-    const int lim = (int)kv_row_len(row_id % a.N, a.S, a.L, a.non_causal);   // keys this row ranks
-    const int t_begin = cellno * sc.cell;
-    if (t_begin >= lim) continue;
-    const int t_end = min(t_begin + sc.cell, lim);
-    const int tid = threadIdx.x;
-    // four consecutive scores per thread, requested before the splitters are staged (cells and
-    // prefix lengths are multiples of 4 tokens and rows start 16-byte aligned)
-    const float* sk = (a.s_k ? a.s_k : sc.sk) + row_base(a, row_id);
-    const int t0 = t_begin + 4 * tid;
-    f32x4 sv4 = {0.f, 0.f, 0.f, 0.f};
-    if (t0 < t_end) sv4 = *reinterpret_cast<const f32x4*>(sk + t0);
-    __syncthreads();                      // the previous item's counters have been written out
-    if (tid < kNBMax) {
-      spl[tid] = sc.splitters[row_id * kNBMax + tid];
-      cnt[tid] = 0u;
-    }
-    __syncthreads();
-    float top[7];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) top[k] = spl[8 * k + 7];
-    if (t0 < t_end) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) atomicAdd(&cnt[bucket_of_score(spl, top, sv4[e])], 1u);
-    }
-    __syncthreads();
-    if (tid < kNBMax) sc.chist[(row_id * sc.maxch + cellno) * kNBMax + tid] = (uint16_t)cnt[tid];
-  }
-}
-
-// Scatter: the cell's (key, token) pairs are first placed in LDS sorted by bucket (rank from an
-// LDS cursor that starts at the bucket's offset inside the cell), each with its destination;
-// the staged pairs are then written out in staged order, so that the lanes of a store
-// instruction hit runs of consecutive addresses (a bucket's run of this cell) instead of 64
-// different cache lines.
-//
-// scatter_kernel (every row): the cell counts its own buckets in LDS, claims a run for each in
-// the bucket's region with one atomic add on the row's cursor and writes there.  The order of
-// the runs inside a region depends on which workgroup claims first; the sorts that follow order
-// by (score, token), so the maps do not.  A bucket that would outgrow its region marks the row
-// for the exact path and writes nothing.
-constexpr int kCellsPerWg = 1;     // consecutive cells of a row per scatter workgroup (a later cell's scores are
-                                   // requested before the earlier cell is worked on).  2 is slower at 128K (532
-                                   // against 476 us): the kernel lives on the number of independent workgroups
-                                   // in flight, not on the latency of one
-
-__global__ __launch_bounds__(kScatterThreads) void scatter_kernel(PlanArgs a, Scratch sc) {
-  __shared__ __attribute__((aligned(16))) float spl[kNBMax];
-  __shared__ uint32_t cnt[kNBMax];              // population of each bucket in this cell
-  __shared__ uint32_t cur[kNBMax];              // first staging slot of each bucket
-  __shared__ uint32_t delta[kNBMax];            // slot in the row's regions - staging slot; ~0: no room
-  __shared__ uint64_t stage[kCellMax];
-  __shared__ uint32_t sdst[kCellMax];
-  const int cgroups = (sc.maxch + kCellsPerWg - 1) / kCellsPerWg;
-  const int64_t row_id = blockIdx.x / cgroups;
-  const int cell0 = (int)(blockIdx.x % cgroups) * kCellsPerWg;
-  const int lim = (int)kv_row_len(row_id % a.N, a.S, a.L, a.non_causal);
-  if (cell0 * sc.cell >= lim) return;
-  const int tid = threadIdx.x;
-  const float* sk = (a.s_k ? a.s_k : sc.sk) + row_base(a, row_id);
-  // four consecutive scores per thread (cells and prefix lengths are multiples of 4 tokens and
-  // rows start 16-byte aligned)
-  auto load4 = [&](int cellno) {
-    const int t = cellno * sc.cell + 4 * tid;
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (t < min((cellno + 1) * sc.cell, lim)) v = *reinterpret_cast<const f32x4*>(sk + t);
-    return v;
-  };
-  f32x4 sv4 = load4(cell0);
-  if (tid < kNBMax) {
-    spl[tid] = sc.splitters[row_id * kNBMax + tid];
-    cnt[tid] = 0u;
-  }
-  __syncthreads();
-  float top[7];
-#pragma unroll
-  for (int k = 0; k < 7; ++k) top[k] = spl[8 * k + 7];
-  const uint32_t cap = bucket_cap(lim);
-  uint64_t* dstp = row_pairs(a, sc, row_id);
-  for (int ci = 0; ci < kCellsPerWg; ++ci) {
-    const int cellno = cell0 + ci;
-    const int t_begin = cellno * sc.cell;
-    if (t_begin >= lim) break;
-    const int t_end = min(t_begin + sc.cell, lim);
-    const int t0 = t_begin + 4 * tid;
-    f32x4 svn = {0.f, 0.f, 0.f, 0.f};
-    if (ci + 1 < kCellsPerWg) svn = load4(cellno + 1);
-    // the counting atomic also ranks the pair inside its (cell, bucket) run
-    int bk[4] = {0, 0, 0, 0};
-    uint32_t rk[4] = {0, 0, 0, 0};
-    if (t0 < t_end) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        bk[e] = bucket_of_score(spl, top, sv4[e]);
-        rk[e] = atomicAdd(&cnt[bk[e]], 1u);
-      }
-    }
-    __syncthreads();                            // also: the previous cell's staging has been written out
-    if (tid < kNBMax) {                         // one wavefront: staging offsets and the claims
-      const uint32_t v = cnt[tid];
-      cnt[tid] = 0u;                            // for the next cell
-      uint32_t incl = v;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t u = __shfl_up(incl, o);
-        if (tid >= o) incl += u;
-      }
-      const uint32_t excl = incl - v;
-      cur[tid] = excl;
-      uint32_t d = 0xffffffffu;
-      if (v > 0) {
-        const uint32_t at = atomicAdd(&sc.cursor[row_id * kNBMax + tid], v);
-        if (at + v <= cap) d = (uint32_t)tid * cap + at - excl;
-        else sc.rowflag[row_id] = 1u;
-      }
-      delta[tid] = d;
-    }
-    __syncthreads();
-    if (t0 < t_end) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t slot = cur[bk[e]] + rk[e];
-        if (slot < (uint32_t)kCellMax) {
-          stage[slot] = sort_key(sv4[e], (uint32_t)(t0 + e));
-          const uint32_t d = delta[bk[e]];
-          sdst[slot] = d == 0xffffffffu ? d : d + slot;
-        } else {
-          raise(a, sc, 1u);
-        }
-      }
-    }
-    __syncthreads();
-    const int n_here = t_end - t_begin;
-    for (int i = tid; i < n_here; i += kScatterThreads) {
-      const uint32_t d = sdst[i];
-      if (d != 0xffffffffu) dstp[d] = stage[i];
-    }
-    sv4 = svn;
-  }
-}
-
-// Exact path, pass 3 (rows on the redo list): the same staging, destinations from the counted
-// offsets; the row's pairs end up compact, in bucket order, from the start of its regions.
-__global__ __launch_bounds__(256) void scatter_exact_kernel(PlanArgs a, Scratch sc, int64_t rows) {
-  __shared__ __attribute__((aligned(16))) float spl[kNBMax];
-  __shared__ uint32_t cur[kNBMax];              // next free staging slot of each bucket
-  __shared__ uint32_t delta[kNBMax];            // global offset of the bucket's run - its first slot
-  __shared__ uint64_t stage[kCellMax];
-  __shared__ uint32_t sdst[kCellMax];
-  const int64_t nredo = min((int64_t)sc.counters[3], rows);
-  for (int64_t item = blockIdx.x; item < nredo * sc.maxch; item += gridDim.x) {
-    const int64_t row_id = sc.redo[item / sc.maxch];
-    const int cellno = (int)(item % sc.maxch);
-    const int lim = (int)kv_row_len(row_id % a.N, a.S, a.L, a.non_causal);
-    const int t_begin = cellno * sc.cell;
-    if (t_begin >= lim) continue;
-    const int t_end = min(t_begin + sc.cell, lim);
-    const int tid = threadIdx.x;
-    const int64_t cell = (row_id * sc.maxch + cellno) * kNBMax;
-    const float* sk = (a.s_k ? a.s_k : sc.sk) + row_base(a, row_id);
-    const int t0 = t_begin + 4 * tid;
-    f32x4 sv4 = {0.f, 0.f, 0.f, 0.f};
-    if (t0 < t_end) sv4 = *reinterpret_cast<const f32x4*>(sk + t0);
-    __syncthreads();                            // the previous item's staging has been written out
-    if (tid < kNBMax) {                         // one wavefront: exclusive scan of the cell's counts
-      spl[tid] = sc.splitters[row_id * kNBMax + tid];
-      const uint32_t v = sc.chist[cell + tid];
-      uint32_t incl = v;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t u = __shfl_up(incl, o);
-        if (tid >= o) incl += u;
-      }
-      cur[tid] = incl - v;
-      delta[tid] = sc.coffs[cell + tid] - (incl - v);
-    }
-    __syncthreads();
-    float top[7];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) top[k] = spl[8 * k + 7];
-    if (t0 < t_end) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float sv = sv4[e];
-        const int bk = bucket_of_score(spl, top, sv);
-        const uint32_t slot = atomicAdd(&cur[bk], 1u);
-        if (slot < (uint32_t)kCellMax) {
-          stage[slot] = sort_key(sv, (uint32_t)(t0 + e));
-          sdst[slot] = delta[bk] + slot;
-        } else {
-          raise(a, sc, 1u);
-        }
-      }
-    }
-    __syncthreads();
-    uint64_t* dstp = row_pairs(a, sc, row_id);
-    const int n_here = t_end - t_begin;
-    for (int i = tid; i < n_here; i += 256) {
-      const uint32_t d = sdst[i];
-      if (d < (uint32_t)lim) dstp[d] = stage[i];
-      else raise(a, sc, 8u);
-    }
-  }
-}
-
-
-// Per prefix row: sort the sampled scores (descending) and keep every (ns / nb)-th one as a
-// splitter; bucket k of the row then holds the scores s with exactly k splitters above s.
-__global__ __launch_bounds__(256) void splitter_kernel(PlanArgs a, Scratch sc) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  uint64_t* keys = reinterpret_cast<uint64_t*>(smem);
+// Per row longer than one LDS sort: the lower ends of its score ranges.  A linear histogram of
+// the sampled scores is cut at equal shares, interpolating inside a bin.  Nothing depends on the
+// cuts being good but the balance between workgroups, and row_sort_kernel cuts again where a
+// range does not fit; they only have to be in descending order.
+constexpr int kThrBins = 1024;
+__global__ __launch_bounds__(256) void threshold_kernel(PlanArgs a, Scratch sc) {
+  __shared__ uint32_t hist[kThrBins + 1];
+  __shared__ float red[8];
+  __shared__ uint32_t wsum[4];
   const int64_t row_id = blockIdx.x;
   const int n = (int)(row_id % a.N);
-  float* out = sc.splitters + row_id * kNBMax;
   const int len = (int)kv_row_len(n, a.S, a.L, a.non_causal);
-  const int nb = row_buckets(len);
-  if (nb == 1) {
-    if (threadIdx.x < kNBMax) out[threadIdx.x] = -INFINITY;
-    return;
-  }
+  const int nr = row_ranges(len, sc.cap);
+  if (nr <= 1) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ns = len / kSampleStride;
-  const int n2 = next_pow2(ns);
   const float* smp = sc.samples + row_id * (a.L / kSampleStride);
-  for (int i = threadIdx.x; i < n2; i += 256) keys[i] = i < ns ? sort_key(smp[i], (uint32_t)i) : ~0ull;
-  __syncthreads();
-  bitonic_sort_lds(keys, n2, threadIdx.x, 256);
-  if (threadIdx.x < kNBMax) {
-    const int k = threadIdx.x + 1;     // splitter k separates buckets k-1 and k
-    float v = -INFINITY;
-    if (k < nb) v = ordered_to_float(~(uint32_t)(keys[(int64_t)k * ns / nb] >> 32));
-    out[threadIdx.x] = v;
-  }
-}
-
-// Span records handed to the sorts: (row, first rank, end rank, w).  w & 0xffff = first bucket
-// of the span; w & kCompact: the row's pairs lie compact in rank order from the start of its
-// regions (exact path), otherwise bucket k's pairs lie at k * bucket_cap from there and
-// sc.bst[row][k] is the rank at which bucket k starts.
-constexpr int kCompact = 0x10000;
-// w & kFewBuckets: the span lies inside its first four buckets, whose first ranks are the second
-// half of the record -- the sort then finds a pair's region without a trip to memory.
-constexpr int kFewBuckets = 0x20000;
-
-// Cuts a row's buckets (populations tot[0..nb)) into spans that fit the LDS sort and buckets
-// that do not, and appends both lists to the global ones.  Called by thread 0 .. of a
-// workgroup of at least kNBMax + 1 threads; bstart receives the ranks at which the buckets start.
-__device__ inline void emit_spans(const PlanArgs& a, const Scratch& sc, int64_t row_id, int nb, int len,
-                                  const uint32_t* tot, uint32_t* bstart, int layout, int2* lspan, int* lk0,
-                                  int2* lbig, int* lbk, uint32_t* nsp, uint32_t* gbase) {
-  if (threadIdx.x == 0) {
-    uint32_t off = 0, span_begin = 0, ns = 0, nbig = 0;
-    int span_k0 = 0;
-    for (int k = 0; k < nb; ++k) {
-      const uint32_t cnt = tot[k];
-      bstart[k] = off;
-      if (cnt > (uint32_t)kSpanCap) {
-        if (off > span_begin) { lk0[ns] = span_k0; lspan[ns++] = make_int2((int)span_begin, (int)off); }
-        lbk[nbig] = k;
-        lbig[nbig++] = make_int2((int)off, (int)(off + cnt));
-        span_begin = off + cnt;
-        span_k0 = k + 1;
-      } else if (off + cnt - span_begin > (uint32_t)kSpanCap) {
-        lk0[ns] = span_k0;
-        lspan[ns++] = make_int2((int)span_begin, (int)off);
-        span_begin = off;
-        span_k0 = k;
-      }
-      off += cnt;
-    }
-    bstart[nb] = off;
-    if (off > span_begin) { lk0[ns] = span_k0; lspan[ns++] = make_int2((int)span_begin, (int)off); }
-    if (off != (uint32_t)len) raise(a, sc, 2u);
-    nsp[0] = ns; nsp[1] = nbig;
-    // one reservation per list instead of one (slow, serialised) atomic per span
-    gbase[0] = ns ? atomicAdd(&sc.counters[0], ns) : 0u;
-    gbase[1] = nbig ? atomicAdd(&sc.counters[1], nbig) : 0u;
-  }
-  __syncthreads();
-  if (threadIdx.x < nsp[0]) {
-    if ((int64_t)(gbase[0] + threadIdx.x) < sc.max_spans) {
-      const int k0 = lk0[threadIdx.x];
-      const uint32_t q0 = bstart[min(k0, nb)], q1 = bstart[min(k0 + 1, nb)], q2 = bstart[min(k0 + 2, nb)],
-                     q3 = bstart[min(k0 + 3, nb)], q4 = bstart[min(k0 + 4, nb)];
-      const int few = (uint32_t)lspan[threadIdx.x].y <= q4 ? kFewBuckets : 0;
-      sc.spans[2 * (gbase[0] + threadIdx.x)] =
-          make_int4((int)row_id, lspan[threadIdx.x].x, lspan[threadIdx.x].y, k0 | layout | few);
-      sc.spans[2 * (gbase[0] + threadIdx.x) + 1] = make_int4((int)q0, (int)q1, (int)q2, (int)q3);
-    } else {
-      raise(a, sc, 4u);
-    }
-  }
-  if (threadIdx.x < nsp[1]) {
-    if ((int64_t)(gbase[1] + threadIdx.x) < sc.max_spans)
-      sc.bigspans[gbase[1] + threadIdx.x] =
-          make_int4((int)row_id, lbig[threadIdx.x].x, lbig[threadIdx.x].y, lbk[threadIdx.x] | layout);
-    else raise(a, sc, 4u);
-  }
-  if (threadIdx.x <= (unsigned)nb) sc.bst[row_id * (kNBMax + 1) + threadIdx.x] = bstart[threadIdx.x];
-}
-
-// Per prefix row, after the scatter: the bucket populations are the final cursor values; cut
-// them into spans, or put the row on the redo list if one of its buckets did not fit.
-__global__ __launch_bounds__(2 * kNBMax) void span_kernel(PlanArgs a, Scratch sc) {
-  __shared__ uint32_t tot[kNBMax];
-  __shared__ uint32_t bstart[kNBMax + 1];
-  __shared__ int2 lspan[kNBMax + 1], lbig[kNBMax];
-  __shared__ int lk0[kNBMax + 1], lbk[kNBMax];
-  __shared__ uint32_t nsp[2], gbase[2];
-  const int64_t row_id = blockIdx.x;
-  const int len = (int)kv_row_len(row_id % a.N, a.S, a.L, a.non_causal);
-  if (len == 0) return;
-  if (sc.rowflag[row_id]) {
-    if (threadIdx.x == 0) sc.redo[atomicAdd(&sc.counters[3], 1u)] = (int32_t)row_id;
-    return;
-  }
-  const int nb = row_buckets(len);
-  if (threadIdx.x < kNBMax) tot[threadIdx.x] = (int)threadIdx.x < nb ? sc.cursor[row_id * kNBMax + threadIdx.x] : 0u;
-  __syncthreads();
-  emit_spans(a, sc, row_id, nb, len, tot, bstart, 0, lspan, lk0, lbig, lbk, nsp, gbase);
-}
-
-// Exact path, pass 2 (rows on the redo list): offsets of the (cell, bucket) runs in
-// bucket-major order, and the row's spans.
-__global__ __launch_bounds__(4 * kNBMax) void scan_exact_kernel(PlanArgs a, Scratch sc, int64_t rows) {
-  __shared__ uint32_t part[4][kNBMax];   // counts of bucket b in chunk group q
-  __shared__ uint32_t tot[kNBMax];
-  __shared__ uint32_t bstart[kNBMax + 1];
-  __shared__ int2 lspan[kNBMax + 1], lbig[kNBMax];
-  __shared__ int lk0[kNBMax + 1], lbk[kNBMax];
-  __shared__ uint32_t nsp[2], gbase[2];
-  const int64_t nredo = min((int64_t)sc.counters[3], rows);
-  for (int64_t item = blockIdx.x; item < nredo; item += gridDim.x) {
-    const int64_t row_id = sc.redo[item];
-    const int len = (int)kv_row_len(row_id % a.N, a.S, a.L, a.non_causal);
-    const int b = threadIdx.x % kNBMax, q = threadIdx.x / kNBMax;
-    const int nb = row_buckets(len);
-    const int nch = (len + sc.cell - 1) / sc.cell;
-    const int c0 = (nch * q) / 4, c1 = (nch * (q + 1)) / 4;   // this thread's chunk range
-    const uint16_t* ch = sc.chist + row_id * sc.maxch * kNBMax;
-    uint32_t* co = sc.coffs + row_id * sc.maxch * kNBMax;
-    uint32_t t = 0;
-    if (b < nb)
-      for (int c = c0; c < c1; ++c) t += ch[c * kNBMax + b];
-    __syncthreads();                     // the previous row's tables are no longer read
-    part[q][b] = t;
-    __syncthreads();
-    if (q == 0) tot[b] = part[0][b] + part[1][b] + part[2][b] + part[3][b];
-    __syncthreads();
-    emit_spans(a, sc, row_id, nb, len, tot, bstart, kCompact, lspan, lk0, lbig, lbk, nsp, gbase);
-    __syncthreads();
-    if (b < nb) {
-      uint32_t running = bstart[b];
-      for (int k = 0; k < q; ++k) running += part[k][b];
-      for (int c = c0; c < c1; ++c) {
-        co[c * kNBMax + b] = running;
-        running += ch[c * kNBMax + b];
-      }
-    }
-  }
-}
-
-constexpr int kSortThreads = 256;
-constexpr int kPerThread = kSubBuckets / kSortThreads;   // sub-bucket counters scanned per thread
-
-__global__ __launch_bounds__(kSortThreads) void span_sort_kernel(PlanArgs a, Scratch sc) {
-  __shared__ uint64_t keys[kSpanCap];           // the span's keys grouped by sub-bucket (fallback: as loaded)
-  static_assert((kSpanCap & (kSpanCap - 1)) == 0, "the fallback pads a span to a power of two in place");
-  __shared__ uint32_t start[kSubBuckets + 1];
-  __shared__ uint32_t fill[kSubBuckets];
-  __shared__ uint32_t wsum[kSortThreads / 64];
-  __shared__ uint32_t red[3];          // min / max of the ordered score bits, fullest sub-bucket
-  const int tid = threadIdx.x;
-  const uint32_t nspans = min(sc.counters[0], (uint32_t)sc.max_spans);
-  // A workgroup sorts spans blockIdx.x, blockIdx.x + gridDim.x, ...  A thread keeps its (up to
-  // kPerLoad) pairs of the span in registers until they are grouped, and requests the next
-  // span's pairs as soon as those registers are free, while the current span is ranked.
-  constexpr int kPerLoad = (kSpanCap + kSortThreads - 1) / kSortThreads;
-  int4 sp = make_int4(0, 0, 0, 0);
-  uint64_t held[kPerLoad];
-  auto fetch = [&](uint32_t w) {
-    sp = sc.spans[2 * w];
-    const int4 sq = sc.spans[2 * w + 1];
-    const int row_n = sp.x % a.N, row_zh = sp.x / a.N;
-    const uint64_t* src = row_pairs(a, sc, row_zh, row_n);
-    const int n = sp.z - sp.y;
-    if (sp.w & kCompact) {
+  float lo = INFINITY, hi = -INFINITY;
+  for (int i = tid; i < ns; i += 256) { const float v = smp[i]; lo = fminf(lo, v); hi = fmaxf(hi, v); }
 #pragma unroll
-      for (int e = 0; e < kPerLoad; ++e) {
-        const int i = tid + e * kSortThreads;
-        held[e] = i < n ? src[sp.y + i] : 0ull;
-      }
-    } else {
-      // rank r of the row lies in the bucket k with bst[k] <= r < bst[k+1], at slot r - bst[k]
-      // of that bucket's region
-      const uint32_t cap = bucket_cap(kv_row_len(row_n, a.S, a.L, a.non_causal));
-      const int k0 = sp.w & 0xffff;
-      if (sp.w & kFewBuckets) {
-        // the span's first ranks per bucket came with the record; m = buckets after the first
-        // that begin inside the span (uniform over the workgroup)
-        const uint32_t q0 = (uint32_t)sq.x, q1 = (uint32_t)sq.y, q2 = (uint32_t)sq.z, q3 = (uint32_t)sq.w;
-        const uint32_t end = (uint32_t)sp.z;
-        const int m = (q1 < end ? 1 : 0) + (q2 < end ? 1 : 0) + (q3 < end ? 1 : 0);
-        const uint32_t base0 = (uint32_t)k0 * cap - q0;
+  for (int d = 32; d > 0; d >>= 1) { lo = fminf(lo, __shfl_xor(lo, d)); hi = fmaxf(hi, __shfl_xor(hi, d)); }
+  if (lane == 0) { red[wave] = lo; red[4 + wave] = hi; }
+  for (int i = tid; i <= kThrBins; i += 256) hist[i] = 0u;
+  __syncthreads();
+  lo = fminf(fminf(red[0], red[1]), fminf(red[2], red[3]));
+  hi = fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]));
+  const float width = (hi - lo) / (float)kThrBins;
+  const float inv = width > 0.f ? 1.0f / width : 0.f;
+  for (int i = tid; i < ns; i += 256)
+    atomicAdd(&hist[min(max((int)((hi - smp[i]) * inv), 0), kThrBins - 1)], 1u);
+  __syncthreads();
+  // exclusive scan, four bins per thread
+  uint32_t v[4], run = 0;
 #pragma unroll
-        for (int e = 0; e < kPerLoad; ++e) {
-          const int i = tid + e * kSortThreads;
-          uint64_t v = 0ull;
-          if (i < n) {
-            const uint32_t r = (uint32_t)(sp.y + i);
-            uint32_t off = base0;                               // region start - first rank of the bucket
-            if (m > 0 && r >= q1) off = (uint32_t)(k0 + 1) * cap - q1;
-            if (m > 1 && r >= q2) off = (uint32_t)(k0 + 2) * cap - q2;
-            if (m > 2 && r >= q3) off = (uint32_t)(k0 + 3) * cap - q3;
-            v = src[off + r];
-          }
-          held[e] = v;
-        }
-      } else {                                  // many (nearly) empty buckets in one span
-        const uint32_t* bst = sc.bst + (int64_t)sp.x * (kNBMax + 1);
-        int k = k0;
-        uint32_t b0 = bst[k], b1 = bst[k + 1];
+  for (int k = 0; k < 4; ++k) { v[k] = run; run += hist[4 * tid + k]; }
+  const uint32_t incl = wave_inclusive_sum(run);
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  uint32_t base = incl - run;
+  for (int w = 0; w < wave; ++w) base += wsum[w];
 #pragma unroll
-        for (int e = 0; e < kPerLoad; ++e) {
-          const int i = tid + e * kSortThreads;
-          uint64_t v = 0ull;
-          if (i < n) {
-            const uint32_t r = (uint32_t)(sp.y + i);
-            while (r >= b1) { ++k; b0 = b1; b1 = bst[k + 1]; }
-            v = src[(uint32_t)k * cap + (r - b0)];
-          }
-          held[e] = v;
-        }
-      }
-    }
+  for (int k = 0; k < 4; ++k) hist[4 * tid + k] = base + v[k];
+  if (tid == 255) hist[kThrBins] = base + run;
+  __syncthreads();
+  float* out = sc.thr + row_id * (sc.max_ranges + 2);
+  if (tid == 0) { out[nr] = hi; out[nr + 1] = lo; }
+  for (int r = tid; r < nr; r += 256) {
+    // position (r + 1) / nr of the sample: the last bin that starts at or before it
+    const float at = (float)ns * ((float)(r + 1) / (float)nr);
+    int b = 0;
+#pragma unroll
+    for (int step = kThrBins / 2; step > 0; step >>= 1)
+      if ((float)hist[b + step] <= at) b += step;
+    const float in = (float)(hist[b + 1] - hist[b]);
+    const float frac = in > 0.f ? fminf((at - (float)hist[b]) / in, 1.0f) : 0.f;
+    const float t = hi - ((float)b + frac) * width;
+    out[r] = t == t ? t : -INFINITY;
+  }
+}
+
+// A piece of the ranking of one row: score range r of the nr the row is cut into.
+struct RowItem {
+  int len, r, nr;
+  int64_t base, row_id;    // of the row in s_K / KV_perm; (z*H + h)*N + n
+  bool valid;
+};
+
+// Workgroup list (none in memory): rows n and N-n of a head are taken together, their lengths add
+// up to N*S, so every pair needs about the same number of pieces (`slots`; a few hold nothing).
+// The pieces of a pair go to workgroups whose ids land on one XCD (block ids are dealt round-robin
+// to the 8 XCDs) and that work on them at about the same time: the row is read from HBM once
+// and from that XCD's L2 for every further range.
+__device__ __forceinline__ RowItem row_item(const PlanArgs& a, const Scratch& sc, int slots, int pairs, int xcd, int idx) {
+  RowItem it;
+  it.valid = false;
+  it.len = 0; it.r = 0; it.nr = 0; it.base = 0; it.row_id = 0;
+  const int ZH = a.Z * a.H, u = (idx / slots) * 8 + xcd;
+  if (u >= ZH * pairs) return it;
+  int r = idx % slots, n = u / ZH;
+  const int zh = u % ZH;
+  if (!a.non_causal) {
+    const int p = n;
+    n = a.N - 1 - p;
+    const int first = row_ranges((int64_t)n * a.S, sc.cap);
+    if (r >= first) { r -= first; n = 1 + p < n ? 1 + p : 0; }
+  }
+  it.len = (int)kv_row_len(n, a.S, a.L, a.non_causal);
+  it.nr = row_ranges(it.len, sc.cap);
+  it.r = r;
+  it.base = row_base(a, zh, n);
+  it.row_id = (int64_t)zh * a.N + n;
+  it.valid = r < it.nr;
+  return it;
+}
+
+// Deals a row's keys out to its ranges' regions: cells of 6144 keys are bucketed in LDS (a table
+// over 256 linear pieces of the score gives the range but for three comparisons), counted with
+// replicated counters, staged range by range and copied out as runs of a few hundred pairs.
+// counts[r] = keys of range r (regions hold the first kCap at most; a range with more is
+// incomplete there); lower[r] = its lower end.
+template <class Shape>
+__device__ __forceinline__ void split_row(const SortLds<Shape>& m, uint32_t* counts, float* lower, const float* sk, int len,
+                                          int nr, const float* thr, uint64_t* regions) {
+  constexpr int T = Shape::kThreads, kCap = Shape::kCap, kVec = 3, kCell = 4 * kVec * T, kLut = 256;
+  constexpr int kCounters = 4 * T, kIdShift = 20;      // tokens are below 2^20
+  static_assert(kCell <= Shape::kCap, "a cell is staged in the pair list");
+  static_assert(Shape::kWords >= 4 * kLut + kMaxSplit + kCounters, "tables");
+  const int tid = fresh(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  u32x4* const lut = reinterpret_cast<u32x4*>(m.word);                     // three thresholds to compare with, range
+  uint32_t* const delta = m.word + 4 * kLut;                               // [nr] region slot - staging slot
+  uint32_t* const cnt = m.word + 4 * kLut + kMaxSplit;                     // [nr][rep] counters, then first staging slots
+  u32x4* const c4 = reinterpret_cast<u32x4*>(cnt);
+  uint32_t* const wsum = m.misc;
+  uint32_t rs = 5;                               // 2^rs copies of the counters against conflicts, rotated by range
+  while ((nr << rs) > kCounters) --rs;
+  const uint32_t rep = (uint32_t)(4 * wave + (lane & 3)), rmask = (1u << rs) - 1u;
+  const float hi = thr[nr], range = hi - thr[nr + 1];
+  const float inv = range > 0.f ? ((float)kLut - 0.5f) / range : 0.f;
+  __syncthreads();                               // the previous row is out of LDS
+  if (tid < nr + 3) lower[tid] = tid < nr - 1 ? thr[tid] : -INFINITY;
+  if (tid < nr) counts[tid] = 0u;
+  __syncthreads();
+  if (tid < kLut) {
+    // keys of piece b lie below the upper end of piece b - 1, whatever the rounding
+    const float end = tid == 0 ? INFINITY : hi - (float)(tid - 1) * (range / ((float)kLut - 0.5f));
+    uint32_t id = 0;
+    for (int k = 0; k < nr - 1; ++k) id += lower[k] > end ? 1u : 0u;
+    const u32x4 l = {__float_as_uint(lower[id]), __float_as_uint(lower[id + 1]), __float_as_uint(lower[id + 2]), id};
+    lut[tid] = l;
+  }
+  f32x4 v[kVec];
+  auto load = [&](int t0) {
+#pragma unroll
+    for (int q = 0; q < kVec; ++q)
+      v[q] = *reinterpret_cast<const f32x4*>(sk + min(t0 + 4 * (q * T + tid), len - 4));
   };
-  if (blockIdx.x < nspans) fetch(blockIdx.x);
-  for (uint32_t w = blockIdx.x; w < nspans; w += gridDim.x) {
-    const int64_t base = row_base(a, sp.x / a.N, sp.x % a.N) + sp.y;
-    const int len = sp.z - sp.y;
-    const bool more = w + gridDim.x < nspans;
-    if (tid == 0) { red[0] = 0xffffffffu; red[1] = 0u; red[2] = 0u; }
-    for (int i = tid; i < kSubBuckets; i += kSortThreads) fill[i] = 0;
-    uint32_t lo = 0xffffffffu, hi = 0u;
+  load(0);
+  for (int t0 = 0; t0 < len; t0 += kCell) {
+    {
+      const u32x4 z = {0u, 0u, 0u, 0u};
+      c4[tid] = z;
+    }
+    __syncthreads();                             // also: the table is there, the previous cell has been copied out
+    uint32_t at[4 * kVec];                       // counter | rank << 16
+    float s[4 * kVec];
+    uint32_t further = 0;                        // bit k: the range of key k lies beyond the table's three
 #pragma unroll
-    for (int e = 0; e < kPerLoad; ++e) {
-      if (tid + e * kSortThreads < len) {
-        const uint32_t o = ~(uint32_t)(held[e] >> 32);   // ordered score bits (ascending = ascending score)
-        lo = min(lo, o); hi = max(hi, o);
-      }
+    for (int k = 0; k < 4 * kVec; ++k) {
+      s[k] = sort_score(v[k / 4][k & 3]);
+      const u32x4 l = lut[min((uint32_t)((hi - s[k]) * inv), (uint32_t)(kLut - 1))];
+      at[k] = l[3] + (s[k] < __uint_as_float(l[0]) ? 1u : 0u) + (s[k] < __uint_as_float(l[1]) ? 1u : 0u) +
+              (s[k] < __uint_as_float(l[2]) ? 1u : 0u);
+      if (s[k] < __uint_as_float(l[2])) further |= 1u << k;
+    }
+    if (further != 0u) {
+#pragma unroll
+      for (int k = 0; k < 4 * kVec; ++k)
+        if (further & (1u << k))
+          while (s[k] < lower[at[k]]) ++at[k];   // (ends at the last range: nothing is below -inf)
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      lo = min(lo, (uint32_t)__shfl_xor((int)lo, o));
-      hi = max(hi, (uint32_t)__shfl_xor((int)hi, o));
-    }
-    __syncthreads();                              // red and fill are initialised
-    if ((tid & 63) == 0) { atomicMin(&red[0], lo); atomicMax(&red[1], hi); }
+    for (int k = 0; k < 4 * kVec; ++k) at[k] = (at[k] << rs) + ((rep + at[k]) & rmask);
+    if (t0 + kCell < len) load(t0 + kCell);
+#pragma unroll
+    for (int k = 0; k < 4 * kVec; ++k)
+      if (t0 + 4 * ((k / 4) * T + tid) < len) at[k] |= atomicAdd(&cnt[at[k]], 1u) << 16;
     __syncthreads();
-    const float flo = ordered_to_float(red[0]);
-    const float fhi = ordered_to_float(red[1]);
-    const float range = fhi - flo;
-    const float scale = range > 0.f ? (float)kSubBuckets / range : 0.f;
-    // fine bucket of a key: descending score -> ascending sub-bucket (monotone in the key)
-    auto sub = [&](uint64_t k) {
-      const float f = ordered_to_float(~(uint32_t)(k >> 32));
-      return min(max((int)((fhi - f) * scale), 0), kSubBuckets - 1);
-    };
-    bool fallback = len < 64;
-    if (!fallback) {
-      int sb[kPerLoad];
-#pragma unroll
-      for (int e = 0; e < kPerLoad; ++e) {
-        sb[e] = sub(held[e]);
-        if (tid + e * kSortThreads < len) atomicAdd(&fill[sb[e]], 1u);
-      }
+    {
+      u32x4 x = c4[tid];
+      const uint32_t run = x[0] + x[1] + x[2] + x[3];
+      const uint32_t incl = wave_inclusive_sum(run);
+      if (lane == 63) wsum[wave] = incl;
       __syncthreads();
-      // exclusive scan of the sub-bucket counts: kPerThread per thread, then across threads
-      uint32_t cnt[kPerThread], run = 0, mx = 0;
+      uint32_t base = incl - run;
 #pragma unroll
-      for (int e = 0; e < kPerThread; ++e) {
-        cnt[e] = fill[kPerThread * tid + e]; run += cnt[e]; mx = max(mx, cnt[e]);
+      for (int w = 0; w < T / 64; ++w) base += w < wave ? wsum[w] : 0u;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) { const uint32_t c = x[k]; x[k] = base; base += c; }
+      c4[tid] = x;
+    }
+    __syncthreads();
+    const int ncell = min(kCell, len - t0);
+    if (tid < nr) {
+      const uint32_t begin = cnt[tid << rs], end = tid + 1 < nr ? cnt[(tid + 1) << rs] : (uint32_t)ncell;
+      const uint32_t have = counts[tid], c = end - begin;
+      // (a staging slot is below a region's size, so a delta is never negative)
+      delta[tid] = have + c <= (uint32_t)kCap ? (uint32_t)(tid * kCap) + have - begin : 0xffffffffu;
+      counts[tid] = have + c;
+    }
+#pragma unroll
+    for (int k = 0; k < 4 * kVec; ++k) {
+      const int t = t0 + 4 * ((k / 4) * T + tid) + (k & 3);
+      if (t < len) {
+        const uint32_t slot = at[k] & 0xffffu;
+        m.list[cnt[slot] + (at[k] >> 16)] = pair_of(s[k], (uint32_t)t | ((slot >> rs) << kIdShift));
       }
-      uint32_t incl = run;
+    }
+    __syncthreads();
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t v = __shfl_up(incl, o);
-        if ((tid & 63) >= o) incl += v;
+    for (int k = 0; k < 4 * kVec; ++k) {
+      const int i = tid + k * T;
+      if (i < ncell) {
+        const uint64_t x = m.list[i];
+        const uint32_t d = delta[pair_token(x) >> kIdShift];
+        if (d != 0xffffffffu) regions[d + (uint32_t)i] = x & ((1ull << (32 + kIdShift)) - 1ull);
       }
+    }
+  }
+  __syncthreads();                               // the regions are complete
+}
+
+// Ranks rows longer than one sort: a workgroup takes row after row, deals its keys out to the
+// ranges' regions (split_row) and sorts range after range from there.  A range that did not fit
+// its region is left to row_sort_kernel.
+//
+// What bounds it: LDS and vector instructions at 16 wavefronts per CU: a range of 4600 keys takes 9
+// us to sort and 3 us to arrive, a cell of 6144 keys 7.7 us to deal out, two workgroups per CU.
+// The rows are taken from a ticket, the longest first, so that the last ones to finish are short.
+// 128K, 2016 rows: 935 us, against 1370 us with one piece per (row, range) and a scan each.
+template <class Shape>
+__global__ __launch_bounds__(Shape::kThreads, 4) void split_sort_kernel(PlanArgs a, Scratch sc, int nrows) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int T = Shape::kThreads, kPer = Shape::kPerThread, kCap = Shape::kCap;
+  const SortLds<Shape> m(smem);
+  uint32_t* const counts = reinterpret_cast<uint32_t*>(smem + Shape::kLds);            // [max_ranges]
+  float* const lower = reinterpret_cast<float*>(smem + Shape::kLds + 4 * kMaxSplit);   // [max_ranges + 3], the last -inf
+  uint32_t* const taken = m.misc + 52;
+  uint64_t* const regions = sc.pairs + (int64_t)blockIdx.x * sc.max_ranges * kCap;
+  for (;;) {
+    if (threadIdx.x == 0) *taken = atomicAdd(&sc.ticket[0], 1u);
+    __syncthreads();
+    const int idx = (int)uniform(*taken);
+    if (idx >= nrows) break;
+    const int zh = idx % (a.Z * a.H), n = a.N - 1 - idx / (a.Z * a.H);
+    const int len = (int)kv_row_len(n, a.S, a.L, a.non_causal), nr = row_ranges(len, kCap);
+    const int64_t base = row_base(a, zh, n), row_id = (int64_t)zh * a.N + n;
+    const float* const sk = (a.s_k ? a.s_k : sc.sk) + base;
+    const float* const thr = sc.thr + row_id * (sc.max_ranges + 2);
+    if (nr > 1) split_row<Shape>(m, counts, lower, sk, len, nr, thr, regions);
+    int rank = 0;                                // first rank of the range
+    for (int r = 0; r < nr; ++r) {
+      const int tid = fresh(threadIdx.x);
+      const int count = nr > 1 ? (int)uniform(counts[r]) : len;
+      if (count > kCap) {
+        if (tid == 0) sc.left_over[atomicAdd(&sc.ticket[1], 1u)] = make_int2((int)row_id, r);
+      } else if (count > 0) {
+        float f[kPer], fa = 0.f, fb = 0.f;
+        uint32_t tok[kPer];
+        const bool bounded = r > 0 && r < nr - 1;
+        if (bounded) { fa = lower[r - 1]; fb = lower[r]; }
+        __syncthreads();                         // the previous keys are out of LDS
+        if (nr > 1) {
+          const uint64_t* const src = regions + (int64_t)r * kCap;
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o));
-      if ((tid & 63) == 63) wsum[tid >> 6] = incl;
-      if ((tid & 63) == 0) atomicMax(&red[2], mx);
-      __syncthreads();
-      uint32_t woff = 0;
-      for (int k = 0; k < (tid >> 6); ++k) woff += wsum[k];
-      uint32_t ex = woff + incl - run;
+          for (int e = 0; e < kPer; ++e) {
+            const uint64_t x = src[tid + e * T]; // (whatever lies past the count is not looked at)
+            f[e] = pair_score(x);
+            tok[e] = pair_token(x);
+          }
+        } else {                                 // the whole row fits
 #pragma unroll
-      for (int e = 0; e < kPerThread; ++e) {
-        start[kPerThread * tid + e] = ex; ex += cnt[e]; fill[kPerThread * tid + e] = 0;
-      }
-      if (tid == kSortThreads - 1) start[kSubBuckets] = ex;
-      fallback = red[2] > (uint32_t)kSubMax;
-      __syncthreads();
-      if (!fallback) {
-#pragma unroll
-        for (int e = 0; e < kPerLoad; ++e)
-          if (tid + e * kSortThreads < len) keys[start[sb[e]] + atomicAdd(&fill[sb[e]], 1u)] = held[e];
-        if (more) fetch(w + gridDim.x);
-        __syncthreads();
-        // rank inside the sub-bucket by direct comparison
-        for (int p = tid; p < len; p += kSortThreads) {
-          const uint64_t k = keys[p];
-          const int sbk = sub(k);
-          const uint32_t s0 = start[sbk], s1 = start[sbk + 1];
-          uint32_t rank = s0;
-          for (uint32_t qd = s0; qd < s1; ++qd) rank += keys[qd] < k ? 1u : 0u;
-          a.kv_perm[base + rank] = (int32_t)(uint32_t)k;
+          for (int e = 0; e < kPer; ++e) {
+            const int i = tid + e * T;
+            tok[e] = (uint32_t)i;
+            f[e] = sort_score(sk[min(i, len - 1)]);
+          }
         }
+        block_sort<Shape>(m, count, f, tok, bounded, fb, fa, a.kv_perm + base + rank);
       }
+      rank += count;
     }
-    if (fallback) {
-      const int n2 = next_pow2(len);
-#pragma unroll
-      for (int e = 0; e < kPerLoad; ++e) {
-        const int i = tid + e * kSortThreads;
-        if (i < n2) keys[i] = i < len ? held[e] : ~0ull;
-      }
-      if (more) fetch(w + gridDim.x);
-      __syncthreads();
-      bitonic_sort_lds(keys, n2, tid, kSortThreads);
-      for (int i = tid; i < len; i += kSortThreads) a.kv_perm[base + i] = (int32_t)(uint32_t)keys[i];
-    }
-    __syncthreads();
+    if (rank != len && threadIdx.x == 0) raise(a, 2u);
+    __syncthreads();                             // the ticket word may be written again
   }
 }
 
-// Fallback: stable LSD radix sort (8 passes of 8 bits) of one oversized bucket by one
-// workgroup, ping-ponging between the pair scratch and a private buffer.
-__global__ __launch_bounds__(256) void big_sort_kernel(PlanArgs a, Scratch sc) {
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t basep[256];
-  __shared__ uint32_t dig[256];
-  const int tid = threadIdx.x;
-  const uint32_t nbig = min(sc.counters[1], (uint32_t)sc.max_spans);
-  uint64_t* mine = sc.alt + (int64_t)blockIdx.x * a.L;
-  for (uint32_t w = blockIdx.x; w < nbig; w += gridDim.x) {
-    const int4 sp = sc.bigspans[w];
-    const int64_t base = row_base(a, sp.x) + sp.y;
-    const int len = sp.z - sp.y;
-    // the bucket's pairs: at its rank in a compact row, else at the start of its region
-    uint64_t* const home = row_pairs(a, sc, sp.x) +
-        ((sp.w & kCompact) ? (int64_t)sp.y
-                           : (int64_t)(sp.w & 0xffff) * bucket_cap(kv_row_len(sp.x % a.N, a.S, a.L, a.non_causal)));
-    uint64_t* src = home;
-    uint64_t* dst = mine;
-    for (int pass = 0; pass < 8; ++pass) {
-      const int shift = 8 * pass;
-      hist[tid] = 0;
-      __syncthreads();
-      for (int i = tid; i < len; i += 256) atomicAdd(&hist[(src[i] >> shift) & 255u], 1u);
-      __syncthreads();
-      if (tid == 0) {
-        uint32_t o = 0;
-        for (int d = 0; d < 256; ++d) { basep[d] = o; o += hist[d]; }
-      }
-      __syncthreads();
-      for (int c0 = 0; c0 < len; c0 += 256) {
-        const int i = c0 + tid;
-        uint64_t key = 0;
-        uint32_t d = 256u;
-        if (i < len) { key = src[i]; d = (uint32_t)(key >> shift) & 255u; }
-        dig[tid] = d;
+// Ranks the rows of KV_perm, one (row, score range) after the other.  Range r of a row holds the
+// scores s with thr[r] <= s < thr[r-1] (the first range has no upper end, the last one takes
+// all the rest, NaN included).
+//
+// kWhole     every row fits one sort.
+// kScan      a range's keys are collected by scanning the row (two comparisons per score); the
+//            number of keys above the range, counted on the way, is its first rank.
+// kLeftOver  the same for the ranges that split_sort_kernel has listed: normally none.
+//
+// What bounds it: LDS and vector instructions; a scan reads the row from L2.  A workgroup takes
+// piece after piece: a new workgroup could only start at an old one's end.
+enum RowMode { kWhole, kScan, kLeftOver };
+
+template <class Shape, RowMode kMode>
+__global__ __launch_bounds__(Shape::kThreads, 4) void row_sort_kernel(PlanArgs a, Scratch sc, int slots, int pairs) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int T = Shape::kThreads, kPer = Shape::kPerThread, kCap = Shape::kCap;
+  constexpr int kVec = 4, kTrip = 4 * kVec * T;  // 16-byte loads per thread and trip of a scan, scores per trip
+  constexpr uint32_t kBottom = 0x007fffffu, kTop = 0xff800001u;   // ordered_u32: -inf; one past +inf
+  const SortLds<Shape> m(smem);
+  const float* const scores = a.s_k ? a.s_k : sc.sk;
+  const int xcd = (int)blockIdx.x & 7;
+  // items of this XCD's workgroups, or of all (kLeftOver)
+  const int nitems = kMode == kLeftOver ? (int)uniform(sc.ticket[1]) : (a.Z * a.H * pairs + 7) / 8 * slots;
+  const int stride = kMode == kLeftOver ? (int)gridDim.x : (int)gridDim.x >> 3;
+  uint32_t* const cursor = m.misc + 50;          // keys collected
+  uint32_t* const nabove = m.misc + 51;          // keys above the range
+  for (int idx = kMode == kLeftOver ? (int)blockIdx.x : (int)blockIdx.x >> 3; idx < nitems; idx += stride) {
+    RowItem cur;
+    if (kMode == kLeftOver) {
+      const int2 it = sc.left_over[idx];
+      const int n = (int)uniform((uint32_t)it.x) % a.N;
+      cur.row_id = (int64_t)uniform((uint32_t)it.x);
+      cur.r = (int)uniform((uint32_t)it.y);
+      cur.len = (int)kv_row_len(n, a.S, a.L, a.non_causal);
+      cur.nr = row_ranges(cur.len, kCap);
+      cur.base = row_base(a, cur.row_id / a.N, n);
+      cur.valid = true;
+    } else {
+      cur = row_item(a, sc, slots, pairs, xcd, idx);
+    }
+    if (!cur.valid) continue;
+    const float* const sk = scores + cur.base;
+    int32_t* const out = a.kv_perm + cur.base;
+    const int len = cur.len, nr = kMode == kWhole ? 1 : cur.nr;
+    const bool last = cur.r == nr - 1;
+    // the range as [lo, hi) in the order of ordered_u32 (one past +inf: no upper end)
+    uint32_t range_lo = kBottom, hi = kTop;
+    if (kMode != kWhole) {
+      const float* const thr = sc.thr + cur.row_id * (sc.max_ranges + 2);
+      if (!last) range_lo = uniform(ordered_u32(thr[cur.r]));
+      if (cur.r > 0) hi = max(uniform(ordered_u32(thr[cur.r - 1])), range_lo);
+    }
+    uint32_t lo = range_lo;
+    // The whole range at once; if its keys do not fit, its upper part first.
+    for (bool more = hi > lo || last; more; more = hi > lo) {
+      const int tid = fresh(threadIdx.x), lane = tid & 63;
+      float f[kPer];
+      uint32_t tok[kPer];
+      int count = len, first = 0;
+      const bool bounded = hi != kTop && lo != kBottom;
+      const float fa = hi == kTop ? __uint_as_float(0x7fc00000u) : ordered_to_float(hi);   // s >= NaN is false
+      const float fb = ordered_to_float(lo);
+      __syncthreads();                           // the previous keys are out of LDS
+      if (nr == 1) {                             // the whole row fits
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+          const int i = tid + e * T;
+          tok[e] = (uint32_t)i;
+          f[e] = sort_score(sk[min(i, len - 1)]);
+        }
+        hi = lo;
+      } else if (kMode != kWhole) {
+        f32x4 v[kVec];
+        auto load = [&](f32x4 (&x)[kVec], int t0) {
+          const int tid_ = fresh(threadIdx.x);
+#pragma unroll
+          for (int q = 0; q < kVec; ++q)
+            x[q] = *reinterpret_cast<const f32x4*>(sk + min(t0 + 4 * (q * T + tid_), len - 4));
+        };
+        load(v, 0);
+        if (tid == 0) { *cursor = 0u; *nabove = 0u; }
         __syncthreads();
-        uint32_t pos = 0;
-        if (i < len) {
-          uint32_t rank = 0;
-          for (int t = 0; t < tid; ++t) rank += (dig[t] == d) ? 1u : 0u;
-          pos = basep[d] + rank;
+        const uint64_t rest = lo == kBottom && last ? ~0ull : 0ull;   // the last part takes NaN scores, too
+        const uint32_t list_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)m.list;
+        uint32_t above = 0;
+        // one trip: compare, rank the hits among the wavefront's, append them
+        auto trip = [&](int t0, auto whole_, auto last_) {
+          constexpr bool kWhole = decltype(whole_)::value, kLast = decltype(last_)::value;
+          uint64_t in[kVec][4];
+          uint32_t mine = 0;
+#pragma unroll
+          for (int q = 0; q < kVec; ++q) {
+            const uint64_t valid = kWhole ? ~0ull : __builtin_amdgcn_ballot_w64(t0 + 4 * (q * T + tid) < len);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const uint64_t up = __builtin_amdgcn_ballot_w64(v[q][e] >= fa) & valid;
+              if (kLast) in[q][e] = ~up & valid;      // NaN scores, too
+              else in[q][e] = __builtin_amdgcn_ballot_w64(v[q][e] >= fb) & valid & ~up;
+              // per-lane counts, one more where the lane's bit is set
+              asm("v_addc_co_u32 %0, vcc, 0, %0, %1" : "+v"(above) : "s"(up) : "vcc");
+              asm("v_addc_co_u32 %0, vcc, 0, %0, %1" : "+v"(mine) : "s"(in[q][e]) : "vcc");
+            }
+          }
+          const uint32_t incl = wave_inclusive_sum(mine);
+          const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+          uint32_t at = 0;
+          if (lane == 0) at = atomicAdd(cursor, total);
+          at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+          if (at + total > (uint32_t)kCap) return;   // the count says so
+          uint32_t dst = list_lds + 8u * (at + incl - mine), t = (uint32_t)(t0 + 4 * tid);
+#pragma unroll
+          for (int q = 0; q < kVec; ++q) {
+            // (score, token) pairs from every lane of each mask, to the lane's next place
+            uint32_t tk;
+            asm volatile(
+                "s_mov_b64 exec, %[i0]\n\t"
+                "v_add_u32 %[tk], %[d], %[t]\n\t"
+                "ds_write2_b32 %[dst], %[s0], %[tk] offset1:1\n\t"
+                "v_add_u32 %[dst], 8, %[dst]\n\t"
+                "s_mov_b64 exec, %[i1]\n\t"
+                "v_add3_u32 %[tk], %[t], %[d], 1\n\t"
+                "ds_write2_b32 %[dst], %[s1], %[tk] offset1:1\n\t"
+                "v_add_u32 %[dst], 8, %[dst]\n\t"
+                "s_mov_b64 exec, %[i2]\n\t"
+                "v_add3_u32 %[tk], %[t], %[d], 2\n\t"
+                "ds_write2_b32 %[dst], %[s2], %[tk] offset1:1\n\t"
+                "v_add_u32 %[dst], 8, %[dst]\n\t"
+                "s_mov_b64 exec, %[i3]\n\t"
+                "v_add3_u32 %[tk], %[t], %[d], 3\n\t"
+                "ds_write2_b32 %[dst], %[s3], %[tk] offset1:1\n\t"
+                "v_add_u32 %[dst], 8, %[dst]\n\t"
+                "s_mov_b64 exec, -1"
+                : [dst] "+v"(dst), [tk] "=&v"(tk)
+                : [i0] "s"(in[q][0]), [i1] "s"(in[q][1]), [i2] "s"(in[q][2]), [i3] "s"(in[q][3]), [t] "v"(t),
+                  [s0] "v"(v[q][0]), [s1] "v"(v[q][1]), [s2] "v"(v[q][2]), [s3] "v"(v[q][3]), [d] "s"(4 * q * T)
+                : "memory");
+          }
+        };
+        auto scan = [&](auto last_) {
+          int t0 = 0;
+          for (; t0 + kTrip <= len; t0 += kTrip) {
+            f32x4 w[kVec];                     // the next trip's scores are on their way during a trip
+            load(w, t0 + kTrip);
+            trip(t0, std::true_type{}, last_);
+#pragma unroll
+            for (int q = 0; q < kVec; ++q) v[q] = w[q];
+          }
+          if (t0 < len) trip(t0, std::false_type{}, last_);
+        };
+        if (lo == kBottom && last) scan(std::true_type{});
+        else scan(std::false_type{});
+        {
+          const uint32_t sum = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(above), 63);
+          if (lane == 0) atomicAdd(nabove, sum);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the appended pairs, which the compiler does not know of
+        __syncthreads();
+        count = (int)uniform(*cursor);
+        first = (int)uniform(*nabove);
+        if (count > kCap && hi - lo > 1u) {    // too many: the upper half of the range
+          lo += (hi - lo) / 2;
+          continue;
+        }
+        if (count > kCap) {                    // more equal scores than fit: they keep their order
+          uint32_t done = 0;
+          for (int t1 = 0; t1 < len; t1 += T) {
+            const int t = t1 + tid;
+            const float s = t < len ? sk[t] : 0.f;
+            const bool mine = t < len && !(s >= fa) && (s >= fb || rest != 0ull);
+            const uint64_t hits = __builtin_amdgcn_ballot_w64(mine);
+            if (lane == 0) m.misc[tid >> 6] = (uint32_t)__builtin_popcountll(hits);
+            __syncthreads();
+            uint32_t at = done + (uint32_t)__builtin_popcountll(hits & ((1ull << lane) - 1ull));
+            for (int k = 0; k < T / 64; ++k) {
+              const uint32_t c = m.misc[k];
+              at += k < (tid >> 6) ? c : 0u;
+              done += c;
+            }
+            if (mine && first + at < (uint32_t)len) out[first + at] = t;
+            __syncthreads();
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+          const uint64_t x = m.list[tid + e * T];   // (whatever lies past the count is not looked at)
+          f[e] = sort_score(pair_score(x));
+          tok[e] = pair_token(x);
         }
         __syncthreads();
-        if (i < len) { dst[pos] = key; atomicMax(&basep[d], pos + 1); }
-        __syncthreads();
+        if (rest != 0ull && tid == 0 && first + count != len) raise(a, 2u);
+        if (first + count > len) { raise(a, 8u); count = 0; }
+        hi = lo;
+        lo = range_lo;
       }
-      uint64_t* t = src; src = dst; dst = t;
-      __threadfence();
-      __syncthreads();
+      if (count > 0 && count <= kCap) block_sort<Shape>(m, count, f, tok, bounded, fb, fa, out + first);
     }
-    // 8 passes: the sorted data is back in the pair scratch
-    for (int i = tid; i < len; i += 256) a.kv_perm[base + i] = (int32_t)(uint32_t)home[i];
-    __syncthreads();
   }
 }
 
 // ---------------------------------------------------------------------------------------
+template <class Shape, RowMode kMode>
+static void launch_row_sort(const PlanArgs& a, const Scratch& sc, int cus, hipStream_t stream) {
+  int slots = 1, pairs = a.N;
+  if (a.non_causal) {
+    slots = row_ranges(a.L, Shape::kCap);
+  } else {
+    pairs = a.N / 2;                             // rows 1 .. N-1: (N-1, 1), (N-2, 2), ..., the middle one alone
+    for (int p = 0; p < pairs; ++p) {
+      const int hi = a.N - 1 - p, lo = 1 + p;
+      const int k = row_ranges((int64_t)hi * a.S, Shape::kCap) + (lo < hi ? row_ranges((int64_t)lo * a.S, Shape::kCap) : 0);
+      slots = k > slots ? k : slots;
+    }
+  }
+  const int64_t per_xcd = ((int64_t)a.Z * a.H * pairs + 7) / 8 * slots;
+  const int64_t by_lds = 163840 / (int64_t)Shape::kLds, by_threads = 2048 / Shape::kThreads;
+  const int64_t fit = cus / 8 * (by_lds < by_threads ? by_lds : by_threads);
+  const int64_t groups = per_xcd < fit || fit < 1 ? per_xcd : fit;
+  hipLaunchKernelGGL((row_sort_kernel<Shape, kMode>), dim3((unsigned)(8 * groups)), dim3(Shape::kThreads), Shape::kLds,
+                     stream, a, sc, slots, pairs);
+}
+
+static void launch_split_sort(const PlanArgs& a, const Scratch& sc, hipStream_t stream) {
+  const int64_t rows = (int64_t)a.Z * a.H * (a.non_causal ? a.N : a.N - 1);
+  hipLaunchKernelGGL(split_sort_kernel<MidSort>, dim3((unsigned)(rows < kSplitGroups ? rows : kSplitGroups)),
+                     dim3(MidSort::kThreads), MidSort::kLds + kSplitLds, stream, a, sc, (int)rows);
+  hipLaunchKernelGGL((row_sort_kernel<MidSort, kLeftOver>), dim3(kSplitGroups), dim3(MidSort::kThreads), MidSort::kLds,
+                     stream, a, sc, 1, 1);
+}
+
+using PoolSort512 = SortShape<256, 2>;
+using PoolSort8192 = SortShape<256, 32>;
+
 hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
   const Scratch sc = carve(a.scratch, a.Z, a.H, a.Hkv, a.L, a.S, a.non_causal);
   if (sc.total > a.scratch_bytes) return hipErrorInvalidValue;
-  if ((int64_t)a.Z * a.H * a.N * sc.maxch > 0x7fffffff) return hipErrorInvalidValue;
   const int64_t rows = (int64_t)a.Z * a.H * a.N;
+  if (rows * (sc.max_ranges + 8) > 0x7fffffff || (sc.split && sc.max_ranges > kMaxSplit - 3)) return hipErrorInvalidValue;
   const int G = a.H / a.Hkv;
+  int cus = 0;
   // dynamic LDS limits of the kernels that need more than the default
   constexpr size_t kScoreLds = (size_t)kSub * kKStride * 2;
-  constexpr size_t kSplitterLdsMax = 128 * 1024;   // a row's sample (L / 64 scores, 8-byte keys) is sorted in LDS
   {
     static std::mutex mu;
     static uint64_t done = 0;
     const hipError_t se = once_per_device(mu, done, [] {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&pool_sq_sort_kernel),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, 8192 * 8 + 4 * kD * 4);
-      if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&splitter_kernel),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSplitterLdsMax);
-      return e;
+      const struct { const void* f; size_t lds; } big[] = {
+          {reinterpret_cast<const void*>(&pool_sq_sort_kernel<PoolSort8192>), PoolSort8192::kLds},
+          {reinterpret_cast<const void*>(&row_sort_kernel<MidSort, kWhole>), MidSort::kLds},
+          {reinterpret_cast<const void*>(&row_sort_kernel<MidSort, kScan>), MidSort::kLds},
+          {reinterpret_cast<const void*>(&row_sort_kernel<MidSort, kLeftOver>), MidSort::kLds},
+          {reinterpret_cast<const void*>(&split_sort_kernel<MidSort>), MidSort::kLds + kSplitLds},
+          {reinterpret_cast<const void*>(&row_sort_kernel<LargeSort, kWhole>), LargeSort::kLds}};
+      static_assert(2 * (MidSort::kLds + kSplitLds) <= 163840, "two workgroups per CU");
+      for (const auto& b : big) {
+        const hipError_t e = hipFuncSetAttribute(b.f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)b.lds);
+        if (e != hipSuccess) return e;
+      }
+      return hipSuccess;
     });
     if (se != hipSuccess) return se;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
   }
 
-  hipLaunchKernelGGL(init_kernel, dim3(1), dim3(64), 0, stream, sc, rows, a.status);
   hipLaunchKernelGGL(kguide_kernel, dim3(a.Z * a.Hkv * kGuideParts), dim3(256), 0, stream, a, sc);
   {
-    int n2 = 1;
-    while (n2 < a.S) n2 <<= 1;
-    const size_t lds = (size_t)n2 * 8 + 4 * kD * 4;
-    hipLaunchKernelGGL(pool_sq_sort_kernel, dim3((unsigned)rows), dim3(256), lds, stream, a, sc);
+    const dim3 grid((unsigned)rows), block(256);
+    if (a.S <= PoolSort512::kCap)
+      hipLaunchKernelGGL(pool_sq_sort_kernel<PoolSort512>, grid, block, PoolSort512::kLds, stream, a, sc);
+    else if (a.S <= SmallSort::kCap)
+      hipLaunchKernelGGL(pool_sq_sort_kernel<SmallSort>, grid, block, SmallSort::kLds, stream, a, sc);
+    else
+      hipLaunchKernelGGL(pool_sq_sort_kernel<PoolSort8192>, grid, block, PoolSort8192::kLds, stream, a, sc);
   }
   if (a.N > 1 || a.non_causal) {
     const int RB = (G * a.N + 31) / 32;
@@ -1183,25 +1327,13 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
     const int nchunks = (a.L + sc.chunk - 1) / sc.chunk;
     const dim3 grid((unsigned)((int64_t)a.Z * a.Hkv * RBG * nchunks));
     hipLaunchKernelGGL(score_kernel, grid, dim3(64 * kScoreWaves), kScoreLds, stream, a, sc);
-    {
-      int ns2 = 1;
-      while (ns2 < a.L / kSampleStride) ns2 <<= 1;
-      if ((size_t)ns2 * 8 > kSplitterLdsMax) return hipErrorInvalidValue;   // unreachable: the API refuses L > 1M tokens
-      hipLaunchKernelGGL(splitter_kernel, dim3((unsigned)rows), dim3(256), (size_t)ns2 * 8, stream, a, sc);
-    }
-    const dim3 cgrid((unsigned)(rows * ((sc.maxch + kCellsPerWg - 1) / kCellsPerWg)));
-    hipLaunchKernelGGL(scatter_kernel, cgrid, dim3(kScatterThreads), 0, stream, a, sc);
-    hipLaunchKernelGGL(span_kernel, dim3((unsigned)rows), dim3(2 * kNBMax), 0, stream, a, sc);
-    // the exact path for rows in which a bucket outgrew its region: normally none, and these
-    // three launches find an empty list
-    const dim3 rgrid((unsigned)(rows * sc.maxch < kRedoGrid ? rows * sc.maxch : kRedoGrid));
-    hipLaunchKernelGGL(count_kernel, rgrid, dim3(256), 0, stream, a, sc, rows);
-    hipLaunchKernelGGL(scan_exact_kernel, dim3((unsigned)(rows < kRedoGrid ? rows : kRedoGrid)), dim3(4 * kNBMax), 0,
-                       stream, a, sc, rows);
-    hipLaunchKernelGGL(scatter_exact_kernel, rgrid, dim3(256), 0, stream, a, sc, rows);
-    const int64_t sort_grid = sc.max_spans < 8192 ? sc.max_spans : 8192;
-    hipLaunchKernelGGL(span_sort_kernel, dim3((unsigned)sort_grid), dim3(kSortThreads), 0, stream, a, sc);
-    hipLaunchKernelGGL(big_sort_kernel, dim3(kBigGrid), dim3(256), 0, stream, a, sc);
+    if (sc.max_ranges > 1)
+      hipLaunchKernelGGL(threshold_kernel, dim3((unsigned)rows), dim3(256), 0, stream, a, sc);
+    if (sc.cap == SmallSort::kCap) launch_row_sort<SmallSort, kWhole>(a, sc, cus, stream);
+    else if (sc.cap == LargeSort::kCap) launch_row_sort<LargeSort, kWhole>(a, sc, cus, stream);
+    else if (sc.max_ranges == 1) launch_row_sort<MidSort, kWhole>(a, sc, cus, stream);
+    else if (!sc.split) launch_row_sort<MidSort, kScan>(a, sc, cus, stream);
+    else launch_split_sort(a, sc, stream);
   }
   return hipGetLastError();
 }

@@ -1,0 +1,58 @@
+"""The plan's row sort at the edges of its shapes: rows that just fill one LDS sort and rows one
+query tile longer (2048, 6656 and 13312 keys), rows cut into ranges and scanned once per range,
+rows dealt out to the ranges first, ranges that have to be cut again because of many equal
+scores, and far-off scores.  The scores come from the plan itself, so the maps must equal the
+stable argsort of them entry for entry."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2602_22575_amd import inputs
+import gpu_util as gu
+
+
+def _check(w, Qb, Kb, rows, non_causal=0):
+    print(f"case: row sort L={w.L} S={w.S} H={w.H} non_causal={non_causal}", flush=True)
+    _, pg = gu.gpu_plan(w, gu.to_dev(Qb), gu.to_dev(Kb), non_causal=non_causal)
+    assert np.array_equal(pg["q_perm"], np.argsort(-pg["s_q"], axis=-1, kind="stable"))
+    for h in range(w.H):
+        for n in rows:
+            o, ln = (n * w.L, w.L) if non_causal else (w.S * n * (n - 1) // 2, n * w.S)
+            sk = pg["s_k"][0, h, o:o + ln]
+            assert np.array_equal(pg["kv_perm"][0, h, o:o + ln], np.argsort(-sk, kind="stable")), (h, n)
+
+
+@pytest.mark.parametrize("L,S", [(2112, 64), (2176, 64), (6720, 64), (6784, 64), (13376, 64), (13440, 64),
+                                 (16384, 8192), (24576, 512)])
+def test_row_lengths_around_the_sort_capacities(gpu, L, S):
+    w = inputs.workload("llama8k", L=L, S=S, H=2, Hkv=1, seed=L)
+    Qb, Kb, _ = inputs.make_qkv(w)
+    N = w.N
+    _check(w, Qb, Kb, sorted({1, 2, N // 2, N - 2, N - 1} - {0}))
+
+
+def test_non_causal_rows_cut_into_ranges(gpu):
+    w = inputs.workload("llama8k", L=20480, S=2048, H=2, Hkv=1, seed=4)
+    Qb, Kb, _ = inputs.make_qkv(w)
+    _check(w, Qb, Kb, (0, 9), non_causal=1)
+
+
+@pytest.mark.parametrize("kind", ["plain", "equal", "few values", "far-off"])
+@pytest.mark.parametrize("H", [1, 9])
+def test_long_rows(gpu, H, kind):
+    """32K tokens in 128 segments: one head is scanned per range, nine heads (1143 rows) are dealt
+    out.  Equal scores overflow ranges and regions; a far-off score stretches the range."""
+    w = inputs.workload("llama8k", L=32768, S=256, H=H, Hkv=1, seed=7)
+    Qb, Kb, _ = inputs.make_qkv(w)
+    if kind == "equal":
+        Kb[0, 0, 3000:25000] = Kb[0, 0, 3000]
+    elif kind == "few values":
+        Kb[:] = Kb[0, 0, 7]
+        Kb[0, 0, ::3, 0] ^= 0x8000
+    elif kind == "far-off":
+        K = inputs.bf16_bits_to_f32(Kb)
+        K[0, 0, 5] *= 1000
+        K[0, 0, -300] *= -3000
+        Kb = inputs.f32_to_bf16_bits(K)
+    _check(w, Qb, Kb, (1, 26, 27, 100, 126, 127) if H == 1 else (60, 127))
