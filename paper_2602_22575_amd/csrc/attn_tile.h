@@ -1,7 +1,6 @@
-// Per-wavefront building blocks shared by the three S2O attention kernels for gfx950
-// (attention.hip: both passes in one launch; local.hip: own-segment pass, paper Alg. 2;
-// prefix.hip: prefix walk, paper Alg. 3): one wavefront = 32 query rows against one
-// 64-token key tile staged in LDS.
+// Per-wavefront building blocks shared by the S2O attention kernels for gfx950 (local.hip:
+// own-segment pass, paper Alg. 2; prefix.hip: prefix walk, paper Alg. 3, and both in one launch):
+// one wavefront = 32 query rows against one 64-token key tile staged in LDS.
 //
 // MFMA formulation (v_mfma_f32_32x32x16_bf16), transposed so that a query row lives in one
 // lane pair and softmax statistics need a single cross-lane step:
@@ -21,6 +20,7 @@
 // swz(r) = 4*(r%4) + 2*((r/4)%2) + (r/8)%2: the 16 rows a 16-byte K read touches land on 16
 // different chunks, and the 4 rows x 64 bytes that half a wavefront touches in a transposing
 // V read land on the four 16-bank groups.
+// Contraction slots (hh, jj) of a 16-key step: keys 4*hh + jj for jj < 4, 8 + 4*hh + jj - 4 behind.
 // The K operand is a plain 16-byte read of a row; the V^T operand is read with the
 // transposing LDS load ds_read_b64_tr_b16: within each group of 16 lanes, lane i receives
 // element (i % 4) of the four 8-byte rows pointed to by lanes i/4, 4 + i/4, 8 + i/4 and
@@ -47,8 +47,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef short i16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 typedef __attribute__((address_space(1))) void gvoid;
 typedef __attribute__((address_space(3))) void lvoid;
 
@@ -107,63 +105,8 @@ __device__ __forceinline__ void load_q(const uint16_t* qrow, int hh, bf16x8 (&qf
   for (int kk = 0; kk < 8; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qrow + 16 * kk + 8 * hh);
 }
 
-// contraction slots (hh, jj): jj < 4 -> keys key0 + 4*hh + jj, jj >= 4 -> keys key0 + 8 + 4*hh + jj - 4
-__device__ __forceinline__ bf16x8 read_vt(const uint16_t* vt, int key0, const int (&off)[2]) {
-  const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vt + key0 * kRowElems + off[0]));
-  const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vt + key0 * kRowElems + off[1]));
-  const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
-  const u32x4 w = {l2.x, l2.y, h2.x, h2.y};
-  return __builtin_bit_cast(bf16x8, w);
-}
-
-// S^T = K Q^T for the key tile at `ks`
-__device__ __forceinline__ void qk_tile(const uint16_t* ks, const Operands& op, const bf16x8 (&qf)[8],
-                                        f32x16 (&s)[2]) {
-#pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s[nb][i] = 0.f;
-  // K fragments are fetched from LDS two contraction steps ahead of the MFMA that uses them
-  bf16x8 ka[3][2];
-#pragma unroll
-  for (int pre = 0; pre < 2; ++pre)
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-      ka[pre][nb] = *reinterpret_cast<const bf16x8*>(ks + 32 * nb * kRowElems + op.koff[pre]);
-#pragma unroll
-  for (int kk = 0; kk < 8; ++kk) {
-    if (kk + 2 < 8) {
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-        ka[(kk + 2) % 3][nb] = *reinterpret_cast<const bf16x8*>(ks + 32 * nb * kRowElems + op.koff[kk + 2]);
-    }
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-      s[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk % 3][nb], qf[kk], s[nb], 0, 0, 0);
-  }
-}
-
-// O^T += V^T P^T with the V tile at `vt`
-__device__ __forceinline__ void pv_tile(const uint16_t* vt, const Operands& op, const bf16x8 (&pb)[4],
-                                        f32x16 (&o)[4]) {
-  // V^T fragments are fetched one contraction step (4 blocks of 32 dims) ahead
-  bf16x8 va[2][4];
-#pragma unroll
-  for (int db = 0; db < 4; ++db) va[0][db] = read_vt(vt, 0, op.voff[db]);
-#pragma unroll
-  for (int st = 0; st < 4; ++st) {
-    if (st + 1 < 4) {
-#pragma unroll
-      for (int db = 0; db < 4; ++db) va[(st + 1) & 1][db] = read_vt(vt, 16 * (st + 1), op.voff[db]);
-    }
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[st & 1][db], pb[st], o[db], 0, 0, 0);
-  }
-}
-
 // ---------------------------------------------------------------------------------------
-// Explicitly scheduled operand reads (used by local.hip and prefix.hip).
+// Explicitly scheduled operand reads.
 //
 // The compiler cannot tell an LDS read of one tile buffer from the asynchronous global->LDS
 // load that is filling another, so it drains every outstanding global load (s_waitcnt
@@ -173,7 +116,7 @@ __device__ __forceinline__ void pv_tile(const uint16_t* vt, const Operands& op, 
 // compiler's wait insertion does not look into, and every fragment is handed to its MFMA
 // through an explicit `s_waitcnt lgkmcnt(n)` that names how many younger LDS reads may still be
 // in flight (LDS reads complete in order).  The kernels wait for their own tile fetches
-// themselves (wait_tile_loads) right before the barrier that publishes a tile.
+// themselves (wait_fetches) right before the barrier that publishes a tile.
 //
 // Addresses: one VGPR per fragment slot (the swizzle makes them lane-dependent), fixed for the
 // whole kernel; tile buffer and sub-block are selected with the instruction's immediate offset.
@@ -241,9 +184,15 @@ template <int kYounger>
 __device__ __forceinline__ void lds_wait(uint32_t& a) { asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(a) : "n"(kYounger)); }
 // All global->LDS tile loads (and every other global load) of this wavefront have landed.
 __device__ __forceinline__ void wait_tile_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-// ... all but the kYoungest most recent vector-memory instructions of the wavefront (they complete in order)
+// The same wait, for all but the kYoungest most recent vector-memory instructions of the
+// wavefront (they complete in order), through the builtin, so that the compiler's own bookkeeping
+// of outstanding loads sees it.
 template <int kYoungest>
-__device__ __forceinline__ void wait_older_loads() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kYoungest) : "memory"); }
+__device__ __forceinline__ void wait_fetches() {
+  // s_waitcnt immediate: vmcnt in bits 3..0 and 15..14, every other counter left at its maximum
+  __builtin_amdgcn_s_waitcnt((kYoungest & 15) | ((kYoungest >> 4) << 14) | 0x0f70);
+  asm volatile("" ::: "memory");
+}
 
 // Byte addresses of a lane's operand fragments inside a tile that starts at LDS address `base`
 // (a multiple of 256).  The swizzle is an XOR on the 16-byte chunk index, i.e. on address bits
@@ -629,19 +578,6 @@ __device__ __forceinline__ void store_o_rows(uint16_t* head, int64_t row_stride,
     const int t = __builtin_amdgcn_ds_bpermute(4 * row, tok);
     *reinterpret_cast<u32x4*>(head + (int64_t)t * row_stride + 8 * chunk) = v;
   }
-}
-
-// Normalise and store a lane's share of its output row: dims 32*db + 8*(i/4) + 4*hh + i%4.
-__device__ __forceinline__ void store_o(uint16_t* orow, int hh, const f32x16 (&o)[4], float inv) {
-#pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-      u32x2 w;
-      w.x = pack_bf16x2(o[db][4 * i4] * inv, o[db][4 * i4 + 1] * inv);
-      w.y = pack_bf16x2(o[db][4 * i4 + 2] * inv, o[db][4 * i4 + 3] * inv);
-      *reinterpret_cast<u32x2*>(orow + 32 * db + 8 * i4 + 4 * hh) = w;
-    }
 }
 
 // block id -> (head index z*H + h, segment counted from the last, position inside the

@@ -33,16 +33,9 @@ constexpr int kRowsPerWg = kWaves * kRowsPerWave;
 constexpr size_t kLocalLds = (size_t)(4 * kTileElems) * 2;   // K x2, V x2
 constexpr int kStateStores = 16;   // store instructions a wavefront needs at least for its 16 KB of state
 
-// The end-of-step wait and barrier.  Tiles reach LDS by global->LDS loads only, so the barrier
-// needs the vector-memory counter and no LDS fence; the fragment reads of a step are all
-// consumed by its MFMAs before the wavefront gets here.  The wait goes through the builtin so
-// that the compiler's own bookkeeping of outstanding loads sees it.
-template <int kYoungest>
-__device__ __forceinline__ void wait_fetches() {
-  // s_waitcnt immediate: vmcnt in bits 3..0 and 15..14, every other counter left at its maximum
-  __builtin_amdgcn_s_waitcnt((kYoungest & 15) | ((kYoungest >> 4) << 14) | 0x0f70);
-  asm volatile("" ::: "memory");
-}
+// The end-of-step barrier.  Tiles reach LDS by global->LDS loads only, so the barrier needs the
+// vector-memory counter (wait_fetches) and no LDS fence; the fragment reads of a step are all
+// consumed by its MFMAs before the wavefront gets here.
 __device__ __forceinline__ void tile_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a) {

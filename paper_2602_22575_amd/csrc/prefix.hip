@@ -18,6 +18,20 @@
 // for the wavefront's own fetches  ->  barrier.  The fetches are issued first and waited for
 // last, so they have the whole step to land; nothing between depends on them (the indices
 // loaded in step k are first touched at the top of step k+1).
+//
+// The wait that ends a step goes through the builtin (wait_fetches): behind a wait it cannot see,
+// the compiler guards the accumulator, loaded from the state in front of the loop, with waits of
+// its own for all fetches in flight, in the middle of every step.  Walk without a stop rule,
+// contiguous 8K keys x 32 heads: 1090 -> 1000 us together with the PV product moved one step
+// late as in the walk with votes (with either one alone 1065 to 1088); a layer of 128K tokens
+// at 5e-3 1.04 -> 1.09 of the speed before.
+//
+// The single-launch form (no state buffer) runs the own-segment tiles through the same
+// pipeline first.  It is bound by the matrix products: a query tile in permuted order has rows
+// anywhere in the segment and needs all S/64 own tiles where one in original order stops at its
+// diagonal, which is why a caller with a state buffer gets two launches.  16K tokens, 32 heads,
+// original order, threshold 5e-3: 740 us of ranking and attention against 960 us with the
+// 8-wavefront workgroups (one per CU, operand reads placed by the compiler) it replaces.
 #include "attn_tile.h"
 #include "s2o_internal.h"
 
@@ -31,8 +45,6 @@ constexpr int kWaves = 4, kThreads = 64 * kWaves;
 constexpr int kKBytes0 = 0, kVBytes0 = 2 * kTileBytes;             // K x2 at 0, V x2 behind them
 constexpr size_t kPrefixLds = (size_t)(4 * kTileBytes) + 64 + 4 * kWaves * 64;   // + vote flags + index ring
 
-template <int P> using Par = std::integral_constant<int, P>;
-
 // min(max(x, 0), hi) in one instruction (the compiler emits two: it cannot know that hi >= 0)
 __device__ __forceinline__ uint32_t clamp_token(int x, int hi) {
   int r;
@@ -44,7 +56,10 @@ __device__ __forceinline__ uint32_t clamp_token(int x, int hi) {
 // of its own, so that neither loop's registers weigh on the other.
 // kMapped: the walk follows a KV_perm row (always, except the non-causal walk in storage order,
 // which then does not carry the map's registers and selects).
-template <bool kNoStop, bool kMapped>
+// kOwn: the single-launch form for callers without a state buffer.  The key tiles of the
+// segment itself are folded in first, with the causal mask per row, and the state never leaves
+// the registers.  Tiles are numbered through: 0 .. nloc-1 the own segment's, then the prefix's.
+template <bool kNoStop, bool kMapped, bool kOwn>
 __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs a) {
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];   // OperandAddr needs a 256-byte base
   uint16_t* Ks = reinterpret_cast<uint16_t*>(smem);
@@ -64,6 +79,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
 
   int zh_, nr, jg;
   map_block(blockIdx.x, a.Z * a.H, JG, zh_, nr, jg);
+  if (kOwn) jg = JG - 1 - jg;       // original order: the tiles with most own-segment keys first
   const int n = a.N - 1 - nr, z = zh_ / a.H, h = zh_ % a.H;
   const int g = h / G;
   const uint16_t* Qh = a.Q + z * a.qs[0] + h * a.qs[1];
@@ -85,6 +101,28 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   const int j = jg * tpw + tile_l;              // this wavefront's permuted query tile
   const bool active = j < TJ;
 
+  // ---- the query row of this lane
+  int qoff;
+  {
+    const int r = min(j, TJ - 1) * BM + kRowsPerWave * part + m_;
+    qoff = a.use_q_perm ? a.q_perm[(zh * a.N + n) * a.S + r] : r;
+    qoff = min(max(qoff, 0), a.S - 1);
+  }
+  // own-segment tiles: of the workgroup, of this wavefront; row_lo = the wavefront's first row
+  int nloc = 0, myn = 0, row_lo = 0;
+  if constexpr (kOwn) {
+    int lo = qoff, hi = qoff;
+#pragma unroll
+    for (int d = 16; d > 0; d >>= 1) { lo = min(lo, __shfl_xor(lo, d)); hi = max(hi, __shfl_xor(hi, d)); }
+    row_lo = __builtin_amdgcn_readfirstlane(lo);
+    myn = active ? __builtin_amdgcn_readfirstlane(hi) / kBN + 1 : 0;
+    if (lane == 0) sflag[2 * kWaves + wave] = myn;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) nloc = max(nloc, __builtin_amdgcn_readfirstlane(sflag[2 * kWaves + w]));
+  }
+  const int nall = nloc + ntiles;               // tiles of this launch
+
   // ---- loader: every wavefront moves 16 rows of K and 16 rows of V per step, 4 rows per
   // instruction (lane l of group gi moves a chunk of tile row 16*wave + 4*gi + l/16).  The map
   // entries of its rows travel through a small ring in LDS, private to the wavefront: the 16
@@ -99,7 +137,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   auto ring_slot = [&](int t) { return ring + (t & 3) * (16 * kWaves) + 16 * wave; };
   // (lane l < 16 requests the entry of tile row 16*wave + 4*(l%4) + l/4)
   auto fetch_index = [&](int t) {       // map entries of tile t (clamped tile number) -> ring; ntiles > 0
-    if (kMapped && lane < 16) {
+    if (kMapped && (!kOwn || (t >= nloc && t < nall)) && lane < 16) {
       // scalar base + 32-bit lane offset: no 64-bit per-lane pointer is kept across the walk
       // The lane's offset is worked out again at every call (opaque lane id): kept across the
       // walk it would be a 64-bit per-lane pointer, two registers that the allocator spills
@@ -107,12 +145,16 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
       int l = lane;
       asm volatile("" : "+v"(l));
       const uint32_t row4 = (uint32_t)(4 * (16 * wave + 4 * (l & 3) + ((l >> 2) & 3)));
-      const char* tile_idx = reinterpret_cast<const char*>(kvrow + (int64_t)min(t, ntiles - 1) * kBN);
+      const char* tile_idx = reinterpret_cast<const char*>(kvrow + (int64_t)min(t - nloc, ntiles - 1) * kBN);
       __builtin_amdgcn_global_load_lds((const gvoid*)(tile_idx + (uint64_t)row4), (lvoid*)ring_slot(t), 4, 0, 0);
     }
   };
   auto tokens = [&](int t, uint32_t (&tok)[4]) {   // this lane's four tokens of tile t, clamped to the sequence
-    if (kMapped) {
+    if (kOwn && t < nloc) {             // the segment's own keys
+#pragma unroll
+      for (int gi = 0; gi < 4; ++gi)
+        tok[gi] = (uint32_t)min(nS + t * kBN + 16 * wave + 4 * gi + (lane >> 4), a.L - 1);
+    } else if (kMapped) {
       const int4 e = *reinterpret_cast<const int4*>(ring_slot(t) + 4 * (lane >> 4));
       const int ev[4] = {e.x, e.y, e.z, e.w};
 #pragma unroll
@@ -137,7 +179,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
       load_rows_to_lds(reinterpret_cast<const char*>(Vh) + (uint64_t)(__umul24(tok[gi], v_stride_bytes) + goff[gi]),
                        vd + (16 * wave + 4 * gi) * kRowElems);
   };
-  // the fetches of step t (top of the step): K(t+1), V(t) (no stop rule: V(t+1)), indices of tile t+2
+  // the fetches of step t (top of the step): K(t+1), V(t), indices of tile t+2
   // A wavefront calls fetch_step for t = 0, 1, 2, ... in turn (working or draining), so the
   // tokens of tile t, which V(t) needs, are the ones the previous call worked out for K(t):
   // they stay in four registers instead of being read from the ring and clamped again.
@@ -145,34 +187,23 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   auto fetch_step = [&](int t) {
     uint32_t tn[4];
     tokens(t + 1, tn);
-    if (kNoStop) {
-      if (t + 1 < ntiles) { load_k(t + 1, tn); load_v(t + 1, tn); }
-    } else {
-      if (t + 1 < ntiles) load_k(t + 1, tn);
-      load_v(t, tok_cur);
+    if (t + 1 < nall) load_k(t + 1, tn);
+    load_v(t, tok_cur);
 #pragma unroll
-      for (int gi = 0; gi < 4; ++gi) tok_cur[gi] = tn[gi];
-    }
+    for (int gi = 0; gi < 4; ++gi) tok_cur[gi] = tn[gi];
     fetch_index(t + 2);
   };
-  if (ntiles > 0) {
+  if (nall > 0) {
     fetch_index(0);
     fetch_index(1);
-    wait_tile_loads();
+    if (!kOwn) wait_tile_loads();
     tokens(0, tok_cur);
     load_k(0, tok_cur);
-    if (kNoStop) load_v(0, tok_cur);
   }
 
-  // ---- the query row of this lane and its Q fragments
-  int qoff;
+  // ---- the Q fragments of the row
   bf16x8 qf[8];
-  {
-    const int r = min(j, TJ - 1) * BM + kRowsPerWave * part + m_;
-    qoff = a.use_q_perm ? a.q_perm[(zh * a.N + n) * a.S + r] : r;
-    qoff = min(max(qoff, 0), a.S - 1);
-    load_q(Qh + (int64_t)(nS + qoff) * a.qs[2], hh, qf);
-  }
+  load_q(Qh + (int64_t)(nS + qoff) * a.qs[2], hh, qf);
   OperandAddr oa;
   oa.init(lane, lds_address(smem));
 
@@ -182,13 +213,15 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   // row are requested after the first tile's scores have been issued and arrive behind them.
   const float c2 = a.scale_log2e;
   // Without causality there is no own-segment pass: every row starts from the empty state.
+  // Neither is there a state to resume in the single-launch form.
   const int64_t st_row = zh * a.L + nS + qoff;
   float m_ref = -INFINITY, l_run = 0.f;
-  if (!a.non_causal) { m_ref = a.st_m[st_row]; l_run = a.st_l[st_row]; }
+  const bool no_state = kOwn || a.non_causal;
+  if (!no_state) { m_ref = a.st_m[st_row]; l_run = a.st_l[st_row]; }
   f32x16 o[4];
   const float* st_acc_row = a.st_acc + st_row * kD + 16 * hh;
   auto init_acc = [&] {
-    if (a.non_causal) zero_acc(o);
+    if (no_state) zero_acc(o);
     else load_acc(st_acc_row, o);
   };
   int committed = 0, issued = 0;
@@ -236,54 +269,112 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
     return v;
   };
   auto end_step = [&] {                 // this wavefront's fetches have landed; everyone's after the barrier
-    wait_tile_loads();
+    wait_fetches<0>();
     __syncthreads();
   };
 
-  bool acc_loaded = false;
+  // A wavefront's tile whose PV product is due: K(it) sits in K buffer it & 1, V(it-1) in V buffer
+  // (it-1) & 1.  The operand addresses `fa` carry the current buffers and are moved to the other
+  // ones at the end of every step (sixteen additions, outside the sequence of reads and MFMAs), so
+  // one loop body serves both parities -- two bodies with the buffer as a constant get the
+  // accumulator different registers and pay a 32-move shuffle between them on every step.
+  bool acc_loaded = false, pending = false;
+  int it = 0;
+  auto aim_next = [&](OperandAddr& fa, int it_) {   // step it_ -> it_ + 1: K moves to the other buffer, V the other way
+    const uint32_t dk = (it_ & 1) ? (uint32_t)(-kTileBytes) : (uint32_t)kTileBytes;
+    fa.shift(dk, 0u - dk);
+  };
+  // The scores of a tile next to the PV product of the one before it; the products of the first
+  // tile stand alone.
+  auto products = [&](const OperandAddr& fa) {
+    if (pending) {
+      u32x2 vfr[16][2];
+      qk_tile_sched<0, 0, true>(fa, qf, s, vfr);
+      rescale(o, alpha_pend, grow_pend);
+      pv_tile_sched<0, true>(fa, pb_pend, o, vfr);
+    } else {
+      qk_tile_only<0>(fa, qf, s);
+    }
+  };
+  auto pv_pending = [&](const OperandAddr& fa) {
+    if (pending) {
+      rescale(o, alpha_pend, grow_pend);
+      pv_tile_only<0>(fa, pb_pend, o);
+      pending = false;
+    }
+  };
+  auto fold = [&] {                             // a tile that is kept without a vote
+    pack_p(s, pb_pend);
+    alpha_pend = ts.alpha; grow_pend = ts.grow;
+    l_run = ts.prev + ts.mass; m_ref = ts.m_use;
+    pending = true;
+  };
+  OperandAddr fa = oa.at((uint32_t)kKBytes0, (uint32_t)(kVBytes0 + kTileBytes));   // step 0
+
+  if constexpr (kOwn) {
+    // ---- the segment's own tiles (Pass-1: dense, causal mask where a row ends inside the tile).
+    // A wavefront without a query tile (myn = 0) only fetches.
+    zero_acc(o);
+    acc_loaded = true;
+    wait_fetches<0>();
+    __syncthreads();                            // K tile 0 has landed
+    for (; it < nloc; ++it) {
+      fetch_step(it);
+      if (it < myn) {
+        products(fa);
+        const bool masked = it * kBN + kBN - 1 > row_lo;
+        ts = masked ? softmax_tile<true>(s, c2, m_ref, l_run, it * kBN, qoff, hh)
+                    : softmax_tile<false>(s, c2, m_ref, l_run, it * kBN, qoff, hh);
+        fold();
+      } else {
+        pv_pending(fa);                         // this wavefront's last tile, one step after its scores
+      }
+      aim_next(fa, it);
+      wait_fetches<0>();
+      __syncthreads();
+    }
+    pv_pending(fa);
+  }
+
   if (kNoStop && ntiles > 0) {
-    // ---- every prefix tile is folded in (no votes, nothing deferred): step k reads K(k) and
-    // V(k) while K(k+1) and V(k+1) arrive
-    end_step();                                   // K and V tile 0 have landed
-    auto plain_step = [&](auto par_, int it) {
-      constexpr int P = decltype(par_)::value;
+    // ---- every prefix tile is folded in: no votes
+    if (!kOwn) {
+      init_acc(); acc_loaded = true;
+      wait_fetches<0>();                          // K tile 0 has landed
+      __syncthreads();
+    }
+    for (; it < nall; ++it) {
       fetch_step(it);
       if (active) {
-        qk_tile_only<kKBytes0 + P * kTileBytes>(oa, qf, s);
-        if (!acc_loaded) { init_acc(); acc_loaded = true; }
-        softmax();
-        pack_p(s, pb_pend);
-        rescale(o, ts.alpha, ts.grow);
-        pv_tile_only<kVBytes0 + P * kTileBytes>(oa, pb_pend, o);
-        l_run = ts.prev + ts.mass; m_ref = ts.m_use;
-        ++committed; ++issued;
+        products(fa);
+        bool redo;
+        ts = softmax_tile_keep_reference(s, c2, m_ref, l_run, redo);
+        if (__builtin_amdgcn_ballot_w64(redo) != 0ull) {   // rare: the tile moves some row's reference
+          qk_tile_only<0>(fa, qf, s);
+          softmax();
+        }
+        fold();
       }
-      end_step();
-    };
-    for (int it = 0; it < ntiles; it += 2) {
-      plain_step(Par<0>{}, it);
-      if (it + 1 < ntiles) plain_step(Par<1>{}, it + 1);
+      aim_next(fa, it);
+      wait_fetches<0>();
+      __syncthreads();
     }
+    pv_pending(fa);
+    if (active) committed = issued = ntiles;
   } else if (ntiles > 0) {
-    end_step();                                   // K tile 0 has landed
-    int it = 0;
+    if (!kOwn) end_step();                        // K tile 0 has landed
     bool wg_done = false;
     if (active) {
       // first tile: scores only
-      fetch_step(0);
-      qk_tile_only<kKBytes0>(oa, qf, s);
-      init_acc(); acc_loaded = true;
+      fetch_step(it);
+      qk_tile_only<0>(fa, qf, s);
+      if (!kOwn) { init_acc(); acc_loaded = true; }
       softmax();
-      publish(0);
+      publish(it);
       end_step();
-      bool pending = true;                      // a scored tile waits for its vote
-      // One step.  K(it) sits in K buffer it & 1, V(it-1) in V buffer (it-1) & 1: the operand
-      // addresses `fa` carry the current buffers and are moved to the other buffers at the end of
-      // every completed step (sixteen additions, outside the sequence of reads and MFMAs), so one
-      // loop body serves both parities -- two bodies with the buffer as a constant get the
-      // accumulator different registers and pay a 32-move shuffle between them on every step.
+      pending = true;                           // a scored tile waits for its vote
       // Returns false when the query tile stops at this step.
-      OperandAddr fa = oa.at((uint32_t)(kKBytes0 + kTileBytes), (uint32_t)kVBytes0);   // step 1
+      aim_next(fa, it);
       auto step = [&](int it_) -> bool {
         const Votes vf = read_votes(it_ - 1);
         const int votes = vf.mine;
@@ -313,23 +404,20 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
           softmax();
         }
         publish(it_);
-        {                                       // step it_ + 1: K moves to the other buffer, V the other way
-          const uint32_t dk = (it_ & 1) ? (uint32_t)(-kTileBytes) : (uint32_t)kTileBytes;
-          fa.shift(dk, 0u - dk);
-        }
-        wait_tile_loads();
+        aim_next(fa, it_);
+        wait_fetches<0>();
         __syncthreads();
         return true;
       };
-      for (it = 1; it < ntiles; ++it)
+      for (++it; it < nall; ++it)
         if (!step(it)) break;
       if (pending) {                            // the last tile: its vote is visible now
-        const bool stop = read_votes(ntiles - 1).mine == 0;
+        const bool stop = read_votes(nall - 1).mine == 0;
         if (stop && a.stop_mode == 0) {
           l_run = l_save; m_ref = m_save;
         } else {
           rescale(o, alpha_pend, grow_pend);
-          pv_tile_only<0>(fa, pb_pend, o);      // fa stands at step ntiles: V(ntiles-1)
+          pv_tile_only<0>(fa, pb_pend, o);      // fa stands at step nall: V(nall-1)
           ++committed;
         }
         wg_done = true;
@@ -337,8 +425,8 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
     }
     // ---- drain: keep the tile pipeline fed until every query tile of the workgroup has stopped
     if (!wg_done) {
-      for (; it < ntiles; ++it) {
-        if (it > 0 && read_votes(it - 1).any == 0) break;
+      for (; it < nall; ++it) {
+        if (it > nloc && read_votes(it - 1).any == 0) break;
         fetch_step(it);
         if (lane == 0) vote_flags(it)[wave] = 0;
         end_step();
@@ -365,10 +453,12 @@ hipError_t launch_prefix(const AttnArgs& a, hipStream_t stream) {
   static std::mutex mu;
   static uint64_t done = 0;
   const hipError_t se = once_per_device(mu, done, [] {
-    const void* fns[4] = {reinterpret_cast<const void*>(&s2o_prefix_kernel<false, true>),
-                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, true>),
-                          reinterpret_cast<const void*>(&s2o_prefix_kernel<false, false>),
-                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, false>)};
+    const void* fns[6] = {reinterpret_cast<const void*>(&s2o_prefix_kernel<false, true, false>),
+                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, true, false>),
+                          reinterpret_cast<const void*>(&s2o_prefix_kernel<false, false, false>),
+                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, false, false>),
+                          reinterpret_cast<const void*>(&s2o_prefix_kernel<false, true, true>),
+                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, true, true>)};
     for (const void* f : fns) {
       const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPrefixLds);
       if (e != hipSuccess) return e;
@@ -382,13 +472,11 @@ hipError_t launch_prefix(const AttnArgs& a, hipStream_t stream) {
   const int64_t blocks = (int64_t)a.Z * a.H * a.N * JG;
   if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kThreads);
-  if (a.kv_perm) {
-    if (a.stop_mode == 2) hipLaunchKernelGGL((s2o_prefix_kernel<true, true>), grid, block, kPrefixLds, stream, a);
-    else hipLaunchKernelGGL((s2o_prefix_kernel<false, true>), grid, block, kPrefixLds, stream, a);
-  } else {
-    if (a.stop_mode == 2) hipLaunchKernelGGL((s2o_prefix_kernel<true, false>), grid, block, kPrefixLds, stream, a);
-    else hipLaunchKernelGGL((s2o_prefix_kernel<false, false>), grid, block, kPrefixLds, stream, a);
-  }
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, kPrefixLds, stream, a); };
+  const bool no_stop = a.stop_mode == 2;
+  if (a.passes == 0) no_stop ? launch(s2o_prefix_kernel<true, true, true>) : launch(s2o_prefix_kernel<false, true, true>);
+  else if (a.kv_perm) no_stop ? launch(s2o_prefix_kernel<true, true, false>) : launch(s2o_prefix_kernel<false, true, false>);
+  else no_stop ? launch(s2o_prefix_kernel<true, false, false>) : launch(s2o_prefix_kernel<false, false, false>);
   return hipGetLastError();
 }
 
