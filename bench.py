@@ -364,7 +364,7 @@ def main():
         "plan_frac_of_hbm_peak": plan_bytes(w) / (plan_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
         "input_generation_s": t_gen,
         "roofline": {"bound": "mfma",
-                     "kernel": "s2o_attention_kernel (fused)" if args.fused else "s2o_prefix_kernel (prefix walk)",
+                     "kernel": "s2o_prefix_kernel (single launch)" if args.fused else "s2o_prefix_kernel (prefix walk)",
                      "achieved": dom_tflops, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": dom_tflops / PEAK_BF16_TFLOPS, "ms_per_launch": prefix_ms,
                      "flops_per_launch": dom_flops,

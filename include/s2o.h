@@ -103,9 +103,9 @@ typedef struct s2o_plan_out {
 
 /* bits of *s2o_plan_out.status */
 enum {
-  S2O_PLAN_STAGE_OVERFLOW = 1,  /* a bucket received more keys than were counted for it       */
-  S2O_PLAN_COUNT_MISMATCH = 2,  /* a row's bucket counts do not add up to its length          */
-  S2O_PLAN_SPAN_OVERFLOW = 4,   /* more sort spans than the scratch buffer has room for       */
+  S2O_PLAN_STAGE_OVERFLOW = 1,  /* not raised any more                                          */
+  S2O_PLAN_COUNT_MISMATCH = 2,  /* a row's range counts do not add up to its length            */
+  S2O_PLAN_SPAN_OVERFLOW = 4,   /* not raised any more                                          */
   S2O_PLAN_BAD_RANK = 8         /* a key was ranked outside its row                           */
 };
 

@@ -53,7 +53,7 @@ int check_params(const s2o_params* p, Shape* s, bool for_plan = false) {
   if ((p->block_m != 64 && p->block_m != 128) || p->block_n != 64) return S2O_EUNSUPPORTED;
   if (p->seg_len % p->block_m != 0) return S2O_EUNSUPPORTED;
   if (for_plan && p->seg_len > 8192) return S2O_EUNSUPPORTED;   // a segment's query scores are sorted in LDS
-  if (for_plan && p->seq_len > (1 << 20)) return S2O_EUNSUPPORTED;   // a row's sample (L/64 scores) is sorted in LDS
+  if (for_plan && p->seq_len > (1 << 20)) return S2O_EUNSUPPORTED;   // a split row's ranges (kMaxSplit) are counted in LDS
   if ((int64_t)p->batch * p->q_heads * (p->seq_len / p->seg_len) > (1 << 24)) return S2O_EUNSUPPORTED;
   s->Z = p->batch; s->H = p->q_heads; s->Hkv = p->kv_heads; s->L = p->seq_len;
   s->D = p->head_dim; s->S = p->seg_len; s->N = p->seq_len / p->seg_len; s->nc = p->non_causal;
