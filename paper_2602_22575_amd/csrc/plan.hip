@@ -4,6 +4,8 @@
 //   pool_sq_sort_kernel  one workgroup per (z, h, segment): a single pass over the
 //                        segment's Q rows gives q_mean and s_Q; the S scores are then
 //                        Argsort-ed in LDS (block_sort) -> Q_perm.
+//   mean_guide_kernel,   small inputs: the same work in two launches instead of three, s_Q and
+//   score_sort_kernel    Q_perm beside the scores (pool_segment, guide_part, score_block).
 //   score_kernel         s_K[n, t] = <q_mean[n], K[t]> as an MFMA contraction per KV head:
 //                        columns = (query head of the group, segment), rows = key tokens
 //                        staged through LDS.  q_mean is split exactly into three bf16 terms
@@ -196,14 +198,14 @@ __device__ inline void raise(const PlanArgs& a, uint32_t bit) {
 // Partial column sums of the first key segment: workgroup (z, g, part) adds the rows of its
 // eighth of the segment; the consumers add the eight partial sums in a fixed order, so k_guide
 // is reproducible bit for bit without a serial pass over the segment by one workgroup.
-__global__ __launch_bounds__(256) void kguide_kernel(PlanArgs a, Scratch sc) {
+__device__ __forceinline__ void guide_part(const PlanArgs& a, const Scratch& sc, int block) {
   __shared__ float red[16][kD];
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (block == 0 && threadIdx.x == 0) {
     if (a.status) *a.status = 0;
     sc.ticket[0] = 0u;
     sc.ticket[1] = 0u;
   }
-  const int unit = blockIdx.x / kGuideParts, part = blockIdx.x % kGuideParts;
+  const int unit = block / kGuideParts, part = block % kGuideParts;
   const int z = unit / a.Hkv, g = unit % a.Hkv;
   const int c = threadIdx.x & 15, r = threadIdx.x >> 4;
   const uint16_t* Kh = a.K + z * a.ks[0] + g * a.ks[1];
@@ -231,9 +233,11 @@ __global__ __launch_bounds__(256) void kguide_kernel(PlanArgs a, Scratch sc) {
     float s = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) s += red[i][threadIdx.x];
-    sc.kguide[(int64_t)blockIdx.x * kD + threadIdx.x] = s;
+    sc.kguide[(int64_t)block * kD + threadIdx.x] = s;
   }
 }
+
+__global__ __launch_bounds__(256) void kguide_kernel(PlanArgs a, Scratch sc) { guide_part(a, sc, (int)blockIdx.x); }
 
 // ---------------------------------------------------------------------------------------
 // Sum over the lanes up to and including this one (data-parallel-primitive moves, no LDS).
@@ -525,18 +529,17 @@ __device__ __forceinline__ void block_sort(const SortLds<Shape>& m, int n, float
 }
 
 // ---------------------------------------------------------------------------------------
-// One workgroup per (z, h, n): q_mean, s_Q and Q_perm of the segment in one pass over Q.
-template <class Shape>
-__global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch sc) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+// One workgroup per (z, h, n) = row_id: q_mean (kMean), s_Q and Q_perm (kSort) of the segment in
+// one pass over Q.
+template <class Shape, bool kMean, bool kSort>
+__device__ __forceinline__ void pool_segment(const PlanArgs& a, const Scratch& sc, int64_t row_id, unsigned char* smem) {
   static_assert(Shape::kThreads == 256, "the row loop is written for 256 threads");
   float* sq = reinterpret_cast<float*>(smem);                       // [S] scores; the sort's LDS later
-  float* red = sq + Shape::kCap;                                    // [4 wavefronts][128]
+  float* red = sq + (kSort ? Shape::kCap : 0);                      // [4 wavefronts][128]
   static_assert(4 * (size_t)Shape::kCap >= 4 * 4 * kD, "the partial sums fit behind the scores");
 
   const int G = a.H / a.Hkv;
-  const int64_t row_id = blockIdx.x;                                // (z*H + h)*N + n
-  const int n = (int)(row_id % a.N);
+  const int n = (int)(row_id % a.N);                                // row_id = (z*H + h)*N + n
   const int h = (int)((row_id / a.N) % a.H);
   const int z = (int)(row_id / ((int64_t)a.N * a.H));
   const int g = h / G;
@@ -545,14 +548,16 @@ __global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch s
   // k_guide = mean of the first key segment, from the partial sums in a fixed order
   const float* kg = sc.kguide + ((int64_t)z * a.Hkv + g) * kGuideParts * kD + 8 * c;
   float kgv[8];
+  if constexpr (kSort) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    float t = 0.f;
+    for (int j = 0; j < 8; ++j) {
+      float t = 0.f;
 #pragma unroll
-    for (int pp = 0; pp < kGuideParts; ++pp) t += kg[pp * kD + j];
-    kgv[j] = t * (1.0f / (float)a.S);
+      for (int pp = 0; pp < kGuideParts; ++pp) t += kg[pp * kD + j];
+      kgv[j] = t * (1.0f / (float)a.S);
+    }
   }
-  if (a.k_guide && n == 0 && h % G == 0 && r == 0) {
+  if (kSort && a.k_guide && n == 0 && h % G == 0 && r == 0) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) a.k_guide[((int64_t)z * a.Hkv + g) * kD + 8 * c + j] = kgv[j];
   }
@@ -573,10 +578,13 @@ __global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch s
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const float x0 = bf16_lo(v[q]), x1 = bf16_hi(v[q]);
-        acc[2 * q] += x0; acc[2 * q + 1] += x1;
-        dot = fmaf(x0, kgv[2 * q], dot);
-        dot = fmaf(x1, kgv[2 * q + 1], dot);
+        if constexpr (kMean) { acc[2 * q] += x0; acc[2 * q + 1] += x1; }
+        if constexpr (kSort) {
+          dot = fmaf(x0, kgv[2 * q], dot);
+          dot = fmaf(x1, kgv[2 * q + 1], dot);
+        }
       }
+      if constexpr (!kSort) continue;
       dot += __shfl_xor(dot, 8);
       dot += __shfl_xor(dot, 4);
       dot += __shfl_xor(dot, 2);
@@ -593,12 +601,12 @@ __global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch s
     acc[j] += __shfl_xor(acc[j], 16);
     acc[j] += __shfl_xor(acc[j], 32);
   }
-  if ((tid & 63) < 16) {
+  if (kMean && (tid & 63) < 16) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) red[(tid >> 6) * kD + 8 * c + j] = acc[j];
   }
   __syncthreads();
-  if (tid < kD) {
+  if (kMean && tid < kD) {
     float s = (red[tid] + red[kD + tid]) + (red[2 * kD + tid] + red[3 * kD + tid]);
     s *= 1.0f / (float)a.S;
     if (a.q_mean) a.q_mean[row_id * kD + tid] = s;
@@ -613,6 +621,7 @@ __global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch s
     qs[kD + tid] = (uint16_t)(__float_as_uint(mid) >> 16);
     qs[2 * kD + tid] = (uint16_t)(__float_as_uint(lo) >> 16);   // 8 bits left: exact
   }
+  if constexpr (!kSort) return;
   float f[Shape::kPerThread];
   uint32_t tok[Shape::kPerThread];
 #pragma unroll
@@ -626,6 +635,22 @@ __global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch s
   block_sort<Shape>(m, a.S, f, tok, false, 0.f, 0.f, a.q_perm + row_id * a.S);
 }
 
+template <class Shape>
+__global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch sc) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  pool_segment<Shape, true, true>(a, sc, blockIdx.x, smem);
+}
+
+// Short sequences: the first launch takes q_mean of all rows and, in further workgroups, k_guide's
+// partial sums, neither of which needs the other; s_Q and its Argsort then run beside the scores
+// (score_sort_kernel).
+constexpr size_t kMeanLds = 4 * kD * sizeof(float);
+__global__ __launch_bounds__(256) void mean_guide_kernel(PlanArgs a, Scratch sc, int rows) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if ((int)blockIdx.x < rows) pool_segment<SortShape<256, 2>, true, false>(a, sc, blockIdx.x, smem);
+  else guide_part(a, sc, (int)blockIdx.x - rows);
+}
+
 // ---------------------------------------------------------------------------------------
 // s_K scoring.  Workgroup = (z, g, group of kScoreWaves row blocks, chunk of sc.chunk tokens);
 // wavefront w owns row block kScoreWaves*group + w (32 rows of the contraction's N side) and keeps
@@ -637,8 +662,7 @@ __global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch s
 //   B (16 dims x 32 rows)  : q_mean split terms, lane (row = l%32, hh) holds the same dims
 //   C (32 tokens x 32 rows): register i of lane l = [token 8*(i/4) + 4*hh + i%4][row l%32],
 //                            so a lane sees one row only and its meta data are scalars
-__global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(PlanArgs a, Scratch sc) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+__device__ __forceinline__ void score_block(const PlanArgs& a, const Scratch& sc, int block, unsigned char* smem) {
   uint16_t* Kt = reinterpret_cast<uint16_t*>(smem);                          // [kSub][kKStride]
 
   const int G = a.H / a.Hkv;
@@ -648,7 +672,7 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(PlanArgs a, Scr
   // the row blocks of a head read the same K chunks
   int unit, rest;
   {
-    const int U = a.Z * a.Hkv, b = blockIdx.x;
+    const int U = a.Z * a.Hkv, b = block;
     if (U % 8 == 0) {
       const int xcd = b & 7, idx = b >> 3, per = U / 8;
       unit = (idx % per) * 8 + xcd;
@@ -762,6 +786,21 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(PlanArgs a, Scr
       }
     }
   }
+}
+
+__global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(PlanArgs a, Scratch sc) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  score_block(a, sc, (int)blockIdx.x, smem);
+}
+
+// The scores and, in workgroups of their own in front, s_Q and Q_perm of all rows.
+constexpr size_t kScoreLds = (size_t)kSub * kKStride * 2;
+template <class Shape>
+__global__ __launch_bounds__(64 * kScoreWaves) void score_sort_kernel(PlanArgs a, Scratch sc, int rows) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  static_assert(Shape::kLds <= kScoreLds && Shape::kThreads == 64 * kScoreWaves, "one launch shape for both");
+  if ((int)blockIdx.x < rows) pool_segment<Shape, false, true>(a, sc, blockIdx.x, smem);
+  else score_block(a, sc, (int)blockIdx.x - rows, smem);
 }
 
 __device__ inline int64_t row_base(const PlanArgs& a, int64_t zh, int n) {
@@ -1274,6 +1313,15 @@ static void launch_split_sort(const PlanArgs& a, const Scratch& sc, hipStream_t 
                      stream, a, sc, 1, 1);
 }
 
+
+// Small inputs: s_Q and its Argsort run beside the scores, k_guide beside q_mean -- one launch less
+// in the chain, and the query sort out of it, for a second read of Q that the caches serve.  Worth
+// it as long as the chip is not full (one workgroup per CU for the query rows) and Q is small; us
+// for the whole ranking, sort in front / beside (32 heads over 8): 8 rows of 64 20.1 / 14.7, 256
+// rows of 256 27.0 / 22.3, 256 rows of 512 34.2 / 31.3, 128 rows of 1024 43.8 / 42.0; on the other
+// side 256 rows of 1024 50.9 / 50.9, 512 rows of 512 53.9 / 59.5, 1024 rows of 256 78.5 / 87.4, 256
+// rows of 2048 87.0 / 89.6.
+constexpr int64_t kBesideRows = 256, kBesideQueries = 1 << 17;
 using PoolSort512 = SortShape<256, 2>;
 using PoolSort8192 = SortShape<256, 32>;
 
@@ -1285,7 +1333,6 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
   const int G = a.H / a.Hkv;
   int cus = 0;
   // dynamic LDS limits of the kernels that need more than the default
-  constexpr size_t kScoreLds = (size_t)kSub * kKStride * 2;
   {
     static std::mutex mu;
     static uint64_t done = 0;
@@ -1311,22 +1358,35 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
     if (e != hipSuccess) return e;
   }
 
-  hipLaunchKernelGGL(kguide_kernel, dim3(a.Z * a.Hkv * kGuideParts), dim3(256), 0, stream, a, sc);
-  {
-    const dim3 grid((unsigned)rows), block(256);
+  const dim3 block(256);
+  const int guide_blocks = a.Z * a.Hkv * kGuideParts;
+  int64_t score_blocks = 0;
+  if (a.N > 1 || a.non_causal) {
+    const int RB = (G * a.N + 31) / 32;
+    const int RBG = (RB + kScoreWaves - 1) / kScoreWaves;
+    const int nchunks = (a.L + sc.chunk - 1) / sc.chunk;
+    score_blocks = (int64_t)a.Z * a.Hkv * RBG * nchunks;
+  }
+  if (a.S <= SmallSort::kCap && rows <= kBesideRows && rows * a.S <= kBesideQueries) {
+    hipLaunchKernelGGL(mean_guide_kernel, dim3((unsigned)(rows + guide_blocks)), block, kMeanLds, stream, a, sc, (int)rows);
+    const dim3 grid((unsigned)(rows + score_blocks));
+    if (a.S <= PoolSort512::kCap)
+      hipLaunchKernelGGL(score_sort_kernel<PoolSort512>, grid, block, kScoreLds, stream, a, sc, (int)rows);
+    else
+      hipLaunchKernelGGL(score_sort_kernel<SmallSort>, grid, block, kScoreLds, stream, a, sc, (int)rows);
+  } else {
+    hipLaunchKernelGGL(kguide_kernel, dim3(guide_blocks), block, 0, stream, a, sc);
+    const dim3 grid((unsigned)rows);
     if (a.S <= PoolSort512::kCap)
       hipLaunchKernelGGL(pool_sq_sort_kernel<PoolSort512>, grid, block, PoolSort512::kLds, stream, a, sc);
     else if (a.S <= SmallSort::kCap)
       hipLaunchKernelGGL(pool_sq_sort_kernel<SmallSort>, grid, block, SmallSort::kLds, stream, a, sc);
     else
       hipLaunchKernelGGL(pool_sq_sort_kernel<PoolSort8192>, grid, block, PoolSort8192::kLds, stream, a, sc);
+    if (score_blocks > 0)
+      hipLaunchKernelGGL(score_kernel, dim3((unsigned)score_blocks), dim3(64 * kScoreWaves), kScoreLds, stream, a, sc);
   }
-  if (a.N > 1 || a.non_causal) {
-    const int RB = (G * a.N + 31) / 32;
-    const int RBG = (RB + kScoreWaves - 1) / kScoreWaves;
-    const int nchunks = (a.L + sc.chunk - 1) / sc.chunk;
-    const dim3 grid((unsigned)((int64_t)a.Z * a.Hkv * RBG * nchunks));
-    hipLaunchKernelGGL(score_kernel, grid, dim3(64 * kScoreWaves), kScoreLds, stream, a, sc);
+  if (score_blocks > 0) {
     if (sc.max_ranges > 1)
       hipLaunchKernelGGL(threshold_kernel, dim3((unsigned)rows), dim3(256), 0, stream, a, sc);
     if (sc.cap == SmallSort::kCap) launch_row_sort<SmallSort, kWhole>(a, sc, cus, stream);
