@@ -424,7 +424,26 @@ __device__ __forceinline__ TileStats softmax_tile(f32x16 (&s)[2], float c2, floa
 // P value and every accumulator term by it.  `redo` (a larger mass, an overflow to infinity, or
 // a row that has no reference yet) tells the caller to score the tile again and take
 // softmax_tile.
-constexpr float kMassLimit = 65536.0f;
+//
+// The reference decides at which scale the bf16 rounding of P falls, so the limit is part of the
+// result.  kMassLimit lets the reference lag by up to 2^16: the walk with votes from a state
+// buffer.  The other loops (no stop rule, single launch) give the bits that softmax_tile gives for
+// every tile: for them `redo` is already set by a mass above kSameMass, and confirm_redo drops it
+// again unless some numerator is near 2^kLazy, where softmax_tile would move the reference.  (A
+// row's mass is above kSameMass at every few tiles of a top-k walk; scoring all of these again cost
+// 6 % of it.)
+constexpr float kMassLimit = 65536.0f, kSameMass = 128.0f;
+constexpr float kSameMax = 240.0f;       // 2^kLazy less the rounding of logits up to 2^16
+static_assert(kLazy == 8.0f && 64.0f * kSameMax < kMassLimit, "kSameMax lies just below 2^kLazy");
+__device__ __forceinline__ bool confirm_redo(const f32x16 (&s)[2], float mass) {
+  float mx = 0.f;
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[nb][i]);
+  return !(xhalf_max(mx) <= kSameMax && mass <= kMassLimit);    // (NaN: confirmed)
+}
+template <bool kExactReference>
 __device__ __forceinline__ TileStats softmax_tile_keep_reference(f32x16 (&s)[2], float c2, float m_ref, float l_run,
                                                                  bool& redo) {
   TileStats t;
@@ -443,7 +462,7 @@ __device__ __forceinline__ TileStats softmax_tile_keep_reference(f32x16 (&s)[2],
       sum += pe;
     }
   t.mass = xhalf_sum(sum);
-  redo = !(t.mass <= kMassLimit);
+  redo = !(t.mass <= (kExactReference ? kSameMass : kMassLimit));
   return t;
 }
 

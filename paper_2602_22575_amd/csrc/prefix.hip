@@ -306,8 +306,16 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   auto fold = [&] {                             // a tile that is kept without a vote
     pack_p(s, pb_pend);
     alpha_pend = ts.alpha; grow_pend = ts.grow;
-    l_run = ts.prev + ts.mass; m_ref = ts.m_use;
+    l_run = fmaf(l_run, ts.alpha, ts.mass);     // (one rounding, written out: as prev + mass it is up to the compiler)
+    m_ref = ts.m_use;
     pending = true;
+  };
+  // rare: the tile may move some row's reference
+  constexpr bool kExactReference = kNoStop || kOwn;
+  auto again = [&](const OperandAddr& fa) {
+    if (kExactReference && __builtin_amdgcn_ballot_w64(confirm_redo(s, ts.mass)) == 0ull) return;
+    qk_tile_only<0>(fa, qf, s);
+    softmax();
   };
   OperandAddr fa = oa.at((uint32_t)kKBytes0, (uint32_t)(kVBytes0 + kTileBytes));   // step 0
 
@@ -348,11 +356,8 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
       if (active) {
         products(fa);
         bool redo;
-        ts = softmax_tile_keep_reference(s, c2, m_ref, l_run, redo);
-        if (__builtin_amdgcn_ballot_w64(redo) != 0ull) {   // rare: the tile moves some row's reference
-          qk_tile_only<0>(fa, qf, s);
-          softmax();
-        }
+        ts = softmax_tile_keep_reference<kExactReference>(s, c2, m_ref, l_run, redo);
+        if (__builtin_amdgcn_ballot_w64(redo) != 0ull) again(fa);
         fold();
       }
       aim_next(fa, it);
@@ -398,11 +403,8 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
         pv_tile_sched<0, true>(fa, pb_pend, o, vfr);
         ++committed;
         bool redo;
-        ts = softmax_tile_keep_reference(s, c2, m_ref, l_run, redo);
-        if (__builtin_amdgcn_ballot_w64(redo) != 0ull) {   // rare: the tile moves some row's reference
-          qk_tile_only<0>(fa, qf, s);
-          softmax();
-        }
+        ts = softmax_tile_keep_reference<kExactReference>(s, c2, m_ref, l_run, redo);
+        if (__builtin_amdgcn_ballot_w64(redo) != 0ull) again(fa);
         publish(it_);
         aim_next(fa, it_);
         wait_fetches<0>();
