@@ -29,6 +29,8 @@
 // where far-off scores had sent the old spans to their bitonic network.
 //
 // Argsort semantics: descending score, ties by ascending index, -0 == +0.
+#include <float.h>
+
 #include <type_traits>
 
 #include "s2o_internal.h"
@@ -113,7 +115,8 @@ struct Scratch {
                       // highest and lowest score (from entry [ranges of the row] on)
   float* sk;          // [Z*H*P] s_K, used when the caller does not ask for the scores
   uint32_t* ticket;   // next row to take, and number of ranges left over (split rows)
-  int2* left_over;    // [rows][max_ranges] (row_id, range) whose keys did not fit their region (split rows)
+  int2* left_over;    // [rows][max_ranges] (row_id | range << 24, rank behind the range) of the ranges whose keys
+                      // did not fit their region (split rows)
   uint64_t* pairs;    // [kSplitGroups][max_ranges][cap] (score, token) pairs by range (split rows)
   int cap;            // keys of one LDS sort
   int max_ranges;     // ranges of the longest row
@@ -810,7 +813,8 @@ __device__ inline int64_t row_base(const PlanArgs& a, int64_t zh, int n) {
 // Per row longer than one LDS sort: the lower ends of its score ranges.  A linear histogram of
 // the sampled scores is cut at equal shares, interpolating inside a bin.  Nothing depends on the
 // cuts being good but the balance between workgroups, and row_sort_kernel cuts again where a
-// range does not fit; they only have to be in descending order.
+// range does not fit; they only have to be in descending order and finite, so that -inf, and NaN
+// which counts as -inf, belong to the last range whatever the sample holds.
 constexpr int kThrBins = 1024;
 __global__ __launch_bounds__(256) void threshold_kernel(PlanArgs a, Scratch sc) {
   __shared__ uint32_t hist[kThrBins + 1];
@@ -863,7 +867,7 @@ __global__ __launch_bounds__(256) void threshold_kernel(PlanArgs a, Scratch sc) 
     const float in = (float)(hist[b + 1] - hist[b]);
     const float frac = in > 0.f ? fminf((at - (float)hist[b]) / in, 1.0f) : 0.f;
     const float t = hi - ((float)b + frac) * width;
-    out[r] = t == t ? t : -INFINITY;
+    out[r] = t >= -FLT_MAX ? t : -FLT_MAX;        // (NaN: there are infinities in the sample, or nothing but NaN)
   }
 }
 
@@ -1051,7 +1055,7 @@ __global__ __launch_bounds__(Shape::kThreads, 4) void split_sort_kernel(PlanArgs
       const int tid = fresh(threadIdx.x);
       const int count = nr > 1 ? (int)uniform(counts[r]) : len;
       if (count > kCap) {
-        if (tid == 0) sc.left_over[atomicAdd(&sc.ticket[1], 1u)] = make_int2((int)row_id, r);
+        if (tid == 0) sc.left_over[atomicAdd(&sc.ticket[1], 1u)] = make_int2((int)((uint32_t)row_id | ((uint32_t)r << 24)), rank + count);
       } else if (count > 0) {
         float f[kPer], fa = 0.f, fb = 0.f;
         uint32_t tok[kPer];
@@ -1112,11 +1116,14 @@ __global__ __launch_bounds__(Shape::kThreads, 4) void row_sort_kernel(PlanArgs a
   uint32_t* const nabove = m.misc + 51;          // keys above the range
   for (int idx = kMode == kLeftOver ? (int)blockIdx.x : (int)blockIdx.x >> 3; idx < nitems; idx += stride) {
     RowItem cur;
+    int end = 0;                                 // rank behind the range, as the splitter counted it
     if (kMode == kLeftOver) {
       const int2 it = sc.left_over[idx];
-      const int n = (int)uniform((uint32_t)it.x) % a.N;
-      cur.row_id = (int64_t)uniform((uint32_t)it.x);
-      cur.r = (int)uniform((uint32_t)it.y);
+      const uint32_t at = uniform((uint32_t)it.x);
+      const int n = (int)(at & 0xffffffu) % a.N;
+      cur.row_id = (int64_t)(at & 0xffffffu);
+      cur.r = (int)(at >> 24);
+      end = (int)uniform((uint32_t)it.y);
       cur.len = (int)kv_row_len(n, a.S, a.L, a.non_causal);
       cur.nr = row_ranges(cur.len, kCap);
       cur.base = row_base(a, cur.row_id / a.N, n);
@@ -1273,7 +1280,8 @@ __global__ __launch_bounds__(Shape::kThreads, 4) void row_sort_kernel(PlanArgs a
           tok[e] = pair_token(x);
         }
         __syncthreads();
-        if (rest != 0ull && tid == 0 && first + count != len) raise(a, 2u);
+        if (tid == 0 && ((rest != 0ull && first + count != len) || (kMode == kLeftOver && lo == range_lo && first + count != end)))
+          raise(a, 2u);
         if (first + count > len) { raise(a, 8u); count = 0; }
         hi = lo;
         lo = range_lo;

@@ -56,3 +56,50 @@ def test_long_rows(gpu, H, kind):
         K[0, 0, -300] *= -3000
         Kb = inputs.f32_to_bf16_bits(K)
     _check(w, Qb, Kb, (1, 26, 27, 100, 126, 127) if H == 1 else (60, 127))
+
+
+@pytest.mark.parametrize("kind", ["nan query", "nan keys", "nan and infinite keys"])
+@pytest.mark.parametrize("H", [1, 9])
+def test_long_rows_with_nan(gpu, H, kind):
+    """NaN scores are an input error, but every row of the maps stays a permutation, also where all
+    scores of a row are NaN (one NaN in a query) and where infinities stand beside them; the other
+    queries of such a segment attend as ever (here: without skipping, so densely)."""
+    w = inputs.workload("llama8k", L=32768, S=256, H=H, Hkv=1, seed=8)
+    Qb, Kb, Vb = inputs.make_qkv(w)
+    n = 120
+    bad = n * w.S + 77
+    if kind == "nan query":
+        Qb[0, H // 2, bad, 3] = 0x7fc0
+    else:
+        Kb[0, 0, 3000:3005, 9] = 0x7fc0
+    if kind == "nan and infinite keys":
+        Q = inputs.bf16_bits_to_f32(Qb)
+        Qb = inputs.f32_to_bf16_bits(Q + 0.5)                 # every mean is about 0.5, 128 of them times 3e38 overflow
+        Kb[0, 0, 4000:4100] = 0x7f61
+        Kb[0, 0, 5000:5100] = 0xff61
+    Qd, Kd, Vd = (gu.to_dev(x) for x in (Qb, Kb, Vb))
+    print(f"case: row sort with {kind}, L={w.L} S={w.S} H={H}", flush=True)
+    p = gu.params_for(w)
+    maps = (gu.torch.full((1, H, w.N, w.S), -1, dtype=gu.torch.int32, device="cuda:0"),
+            gu.torch.full((1, H, w.S * w.N * (w.N - 1) // 2), -1, dtype=gu.torch.int32, device="cuda:0"))
+    plan = gu.s2o.s2o_plan(Qd, Kd, p, want_scores=True, maps=maps)
+    gu.torch.cuda.synchronize()
+    assert int(plan.status.item()) == 0
+    sk, kv = plan.s_k.cpu().numpy()[0], plan.kv_perm.cpu().numpy()[0]
+    assert np.isnan(sk).any() and np.isinf(sk).any() == (kind == "nan and infinite keys")
+    for row in range(1, w.N):
+        o, ln = w.S * row * (row - 1) // 2, row * w.S
+        assert np.array_equal(np.sort(kv[:, o:o + ln], axis=1), np.broadcast_to(np.arange(ln), (H, ln))), row
+    for row in (20, n, w.N - 1):                              # NaN is taken for -inf
+        o, ln = w.S * row * (row - 1) // 2, row * w.S
+        s = np.where(np.isnan(sk[:, o:o + ln]), -np.inf, sk[:, o:o + ln])
+        assert np.array_equal(kv[:, o:o + ln], np.argsort(-s, axis=1, kind="stable")), row
+    if kind == "nan query":
+        Ob, c, s = gu.gpu_attention(w, Qd, Kd, Vd, plan.q_perm, plan.kv_perm, 0.0)
+        h, rows = H // 2, np.array([0, 76, 78, 255]) + n * w.S
+        f64 = [inputs.bf16_bits_to_f32(x).astype(np.float64) for x in (Qb[0, h, rows], Kb[0, 0], Vb[0, 0])]
+        x = f64[0] @ f64[1].T / np.sqrt(w.D)
+        x[np.arange(w.L)[None, :] > rows[:, None]] = -np.inf
+        e = np.exp(x - x.max(axis=1, keepdims=True))
+        ref = (e / e.sum(axis=1, keepdims=True)) @ f64[2]
+        assert np.abs(inputs.bf16_bits_to_f32(Ob)[0, h, rows] - ref).max() <= 2e-2
