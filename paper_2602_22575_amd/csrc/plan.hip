@@ -298,6 +298,10 @@ struct SortLds {
   }
 };
 
+// x moved into [0, hi], NaN to 0: what a conversion to an unsigned integer is defined for.  Scores
+// lie outside a sampled range as a matter of course, and a range may be infinite or denormal.
+__device__ __forceinline__ float within(float x, float hi) { return __builtin_amdgcn_fmed3f(x, 0.f, hi); }
+
 // What the sort takes for a score: NaN (an input error) counts as -inf.
 __device__ __forceinline__ float sort_score(float s) { return s == s ? s : -INFINITY; }
 __device__ __forceinline__ uint64_t pair_of(float s, uint32_t tok) { return ((uint64_t)tok << 32) | __float_as_uint(s); }
@@ -380,7 +384,7 @@ __device__ __forceinline__ void block_sort(const SortLds<Shape>& m, int n, float
     // The first and the last range of a row, and whole rows, are far from evenly filled (tails, a
     // few far-off keys).  Half of the buckets are spread over the score range evenly, the other
     // half follows a sample, the first key of every thread.
-    if (tid < n) atomicAdd(&hist[min((uint32_t)((fhi - f[0]) * scale), (uint32_t)(kMapBins - 1))], 1u);
+    if (tid < n) atomicAdd(&hist[(uint32_t)within((fhi - f[0]) * scale, (float)(kMapBins - 1))], 1u);
     __syncthreads();
     if (tid < 64) {                                 // one wavefront, four pieces per lane; 1/16 bucket words, exact in fp32
       const u32x4 c = reinterpret_cast<const u32x4*>(hist)[tid];
@@ -405,11 +409,13 @@ __device__ __forceinline__ void block_sort(const SortLds<Shape>& m, int n, float
     if (e * T < left) {
       float y = (fhi - f[e]) * scale;
       if (!bounded) {                               // monotone: a piece ends where the next one begins
-        const uint32_t b = min((uint32_t)y, (uint32_t)(kMapBins - 1));
+        y = within(y, (float)kMapBins - 0.25f);     // (at most kMapBins - 0.5 but for rounding and infinities)
+        const uint32_t b = (uint32_t)y;
         const uint64_t piece = m.map[b];
-        y = fmaf(__uint_as_float((uint32_t)(piece >> 32)), fminf(y - (float)b, 1.0f), __uint_as_float((uint32_t)piece));
+        y = fmaf(__uint_as_float((uint32_t)(piece >> 32)), y - (float)b, __uint_as_float((uint32_t)piece));
       }
-      const uint32_t w = min((uint32_t)y, (uint32_t)(Shape::kWords - 1));
+      y = within(y, (float)Shape::kWords - 0.25f);
+      const uint32_t w = (uint32_t)y;
       const uint32_t sh = __umul24((uint32_t)(3.0f * __builtin_amdgcn_fractf(y)), 6u);   // (three fractions are below 3)
       // (24-bit: a 32-bit multiply takes four times as long)
       old[e] = atomicAdd(&m.word[w], 1u << (sh & 31u));
@@ -840,7 +846,7 @@ __global__ __launch_bounds__(256) void threshold_kernel(PlanArgs a, Scratch sc) 
   const float width = (hi - lo) / (float)kThrBins;
   const float inv = width > 0.f ? 1.0f / width : 0.f;
   for (int i = tid; i < ns; i += 256)
-    atomicAdd(&hist[min(max((int)((hi - smp[i]) * inv), 0), kThrBins - 1)], 1u);
+    atomicAdd(&hist[(uint32_t)within((hi - smp[i]) * inv, (float)(kThrBins - 1))], 1u);
   __syncthreads();
   // exclusive scan, four bins per thread
   uint32_t v[4], run = 0;
@@ -960,7 +966,7 @@ __device__ __forceinline__ void split_row(const SortLds<Shape>& m, uint32_t* cou
 #pragma unroll
     for (int k = 0; k < 4 * kVec; ++k) {
       s[k] = sort_score(v[k / 4][k & 3]);
-      const u32x4 l = lut[min((uint32_t)((hi - s[k]) * inv), (uint32_t)(kLut - 1))];
+      const u32x4 l = lut[(uint32_t)within((hi - s[k]) * inv, (float)(kLut - 1))];
       at[k] = l[3] + (s[k] < __uint_as_float(l[0]) ? 1u : 0u) + (s[k] < __uint_as_float(l[1]) ? 1u : 0u) +
               (s[k] < __uint_as_float(l[2]) ? 1u : 0u);
       if (s[k] < __uint_as_float(l[2])) further |= 1u << k;

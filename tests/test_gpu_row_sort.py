@@ -103,3 +103,24 @@ def test_long_rows_with_nan(gpu, H, kind):
         e = np.exp(x - x.max(axis=1, keepdims=True))
         ref = (e / e.sum(axis=1, keepdims=True)) @ f64[2]
         assert np.abs(inputs.bf16_bits_to_f32(Ob)[0, h, rows] - ref).max() <= 2e-2
+
+
+@pytest.mark.parametrize("kind", ["tiny", "infinite"])
+@pytest.mark.parametrize("L,S", [(2112, 64), (6720, 64), (13376, 64), (32768, 2048)])
+def test_extreme_score_ranges(gpu, L, S, kind):
+    """Scores whose range is denormal (its reciprocal infinite) or infinite: the map from score to
+    bucket has to stay inside the buckets and monotone."""
+    w = inputs.workload("llama8k", L=L, S=S, H=2, Hkv=1, seed=L)
+    Qb, Kb, _ = inputs.make_qkv(w)
+    K = inputs.bf16_bits_to_f32(Kb)
+    Q = inputs.bf16_bits_to_f32(Qb)
+    if kind == "tiny":
+        Q, K = np.zeros_like(Q), np.zeros_like(K)
+        Q[..., 0] = 2.0 ** -70
+        K[..., 0] = 2.0 ** -76 * np.random.default_rng(1).integers(0, 8, L)[None, None, :]
+        K[0, 0, 40] *= -1
+    else:
+        Q += 0.5
+        K[0, 0, S:S + 3] = 3e38
+        K[0, 0, 2 * S - 5:2 * S] = -3e38
+    _check(w, inputs.f32_to_bf16_bits(Q), inputs.f32_to_bf16_bits(K), sorted({1, 2, w.N // 2, w.N - 1}))
