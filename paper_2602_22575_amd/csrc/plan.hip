@@ -1190,15 +1190,32 @@ __global__ __launch_bounds__(Shape::kThreads, 4) void row_sort_kernel(PlanArgs a
 #pragma unroll
           for (int q = 0; q < kVec; ++q) {
             const uint64_t valid = kWhole ? ~0ull : __builtin_amdgcn_ballot_w64(t0 + 4 * (q * T + tid) < len);
+            uint64_t up[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              const uint64_t up = __builtin_amdgcn_ballot_w64(v[q][e] >= fa) & valid;
-              if (kLast) in[q][e] = ~up & valid;      // NaN scores, too
-              else in[q][e] = __builtin_amdgcn_ballot_w64(v[q][e] >= fb) & valid & ~up;
-              // per-lane counts, one more where the lane's bit is set
-              asm("v_addc_co_u32 %0, vcc, 0, %0, %1" : "+v"(above) : "s"(up) : "vcc");
-              asm("v_addc_co_u32 %0, vcc, 0, %0, %1" : "+v"(mine) : "s"(in[q][e]) : "vcc");
+              up[e] = __builtin_amdgcn_ballot_w64(v[q][e] >= fa) & valid;
+              if (kLast) in[q][e] = ~up[e] & valid;   // NaN scores, too
+              else in[q][e] = __builtin_amdgcn_ballot_w64(v[q][e] >= fb) & valid & ~up[e];
             }
+            // Per-lane counts, one more where the lane's bit is set: additions with the mask as carry.
+            // A vector instruction may read a mask two wait states after the comparison that wrote it,
+            // and a data-parallel move a register two after the addition that did; the compiler keeps
+            // neither for a text, so the text idles at both ends.  (Left to the compiler the additions
+            // are two selects and an addition for two masks.)
+            asm("s_nop 1\n\t"
+                "v_addc_co_u32 %[up], vcc, 0, %[up], %[u0]\n\t"
+                "v_addc_co_u32 %[in], vcc, 0, %[in], %[i0]\n\t"
+                "v_addc_co_u32 %[up], vcc, 0, %[up], %[u1]\n\t"
+                "v_addc_co_u32 %[in], vcc, 0, %[in], %[i1]\n\t"
+                "v_addc_co_u32 %[up], vcc, 0, %[up], %[u2]\n\t"
+                "v_addc_co_u32 %[in], vcc, 0, %[in], %[i2]\n\t"
+                "v_addc_co_u32 %[up], vcc, 0, %[up], %[u3]\n\t"
+                "v_addc_co_u32 %[in], vcc, 0, %[in], %[i3]\n\t"
+                "s_nop 1"
+                : [up] "+v"(above), [in] "+v"(mine)
+                : [u0] "s"(up[0]), [u1] "s"(up[1]), [u2] "s"(up[2]), [u3] "s"(up[3]),
+                  [i0] "s"(in[q][0]), [i1] "s"(in[q][1]), [i2] "s"(in[q][2]), [i3] "s"(in[q][3])
+                : "vcc");
           }
           const uint32_t incl = wave_inclusive_sum(mine);
           const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
