@@ -98,12 +98,28 @@ __host__ __device__ inline int row_ranges(int64_t len, int cap) {
 // per range (cap pairs each, in its own part of the scratch) and then sorts range after range;
 // the longest rows first.  Alternatively every (row, range) is a piece of its own whose workgroup
 // scans the whole row for its keys: no pairs in memory, and enough pieces when there are few
-// rows, but a row of 128K tokens is scanned 27 times.  Measured (us, splitting / scanning, for the
-// whole ranking): 2016 rows at 128K 1440 / 1900, at 64K 754 / 845; 480 rows at 32K (6 ranges)
-// 215 / 170, at 16K 111 / 91.
-constexpr int kSplitGroups = 512;  // workgroups of the medium shape that fit the chip at once
-constexpr int kSplitRows = 1024;   // split from this many long rows and this many ranges on: below that the longest
-constexpr int kSplitRanges = 6;    // row alone takes too long, or the scans cost less than the dealing out
+// rows, but a row of 128K tokens is scanned 27 times.
+//
+// Splitting takes as long as its longest row, or as all rows on kSplitGroups workgroups: about 9 us
+// per range.  Scanning takes (4.2 sum(r) + 0.71 sum(r^2)) / 512 us over the rows' ranges r (fitted to
+// 120 shapes from 24K to 256K tokens).  Below kSplitRows rows the longest row decides, and with r
+// spread evenly up to the longest row's (causal) or the same for all rows (non-causal, where up to 512
+// rows take one round and more take two) the line lies where split_pays puts it.  Measured on both
+// sides (us for the whole ranking, splitting / scanning; rows x ranges of the longest): causal 1020 x 7
+// 195 / 191, 744 x 14 383 / 384, 1008 x 14 401 / 427, 508 x 28 491 / 482, 744 x 27 748 / 887, 1020 x 28
+// 649 / 894, 255 x 55 773 / 688, 511 x 55 893 / 1276; non-causal 512 x 7 194 / 172, 960 x 7 335 / 308,
+// 384 x 14 352 / 339, 512 x 14 342 / 396, 768 x 14 529 / 584, 192 x 28 756 / 738, 256 x 28 477 / 555,
+// 512 x 28 667 / 1041, 960 x 28 1240 / 1918.  From kSplitRows rows on: 2016 x 27 1440 / 1900, 2016 x 14
+// 754 / 845; below kSplitRanges ranges: 736 x 5 179 / 160.
+constexpr int kSplitGroups = 512;  // workgroups of the medium shape that fit the 256 CUs at once
+constexpr int kSplitRows = 1024;
+constexpr int kSplitRanges = 6;
+inline bool split_pays(int64_t rows, int64_t ranges, int non_causal) {
+  if (ranges < kSplitRanges) return false;
+  if (rows >= kSplitRows) return true;
+  if (non_causal) return rows * (ranges + 6) >= (rows > kSplitGroups ? 15000 : 8000);
+  return rows * (ranges + 9) >= 19500;
+}
 constexpr int kMaxSplit = 256;      // ranges of a split row at most (L <= 1M tokens: 219)
 constexpr size_t kSplitLds = 8 * kMaxSplit;   // a row's range counts and lower ends, behind the sort's LDS
 
@@ -117,9 +133,10 @@ struct Scratch {
   uint32_t* ticket;   // next row to take, and number of ranges left over (split rows)
   int2* left_over;    // [rows][max_ranges] (row_id | range << 24, rank behind the range) of the ranges whose keys
                       // did not fit their region (split rows)
-  uint64_t* pairs;    // [kSplitGroups][max_ranges][cap] (score, token) pairs by range (split rows)
+  uint64_t* pairs;    // [groups][max_ranges][cap] (score, token) pairs by range (split rows)
   int cap;            // keys of one LDS sort
   int max_ranges;     // ranges of the longest row
+  int groups;         // workgroups of the splitting kernel
   bool split;         // long rows are split by one workgroup each, not scanned once per range
   int chunk;          // key tokens per score workgroup: kChunkMax, less for short sequences
   size_t total;
@@ -143,7 +160,8 @@ static Scratch carve(void* base, int Z, int H, int Hkv, int L, int S, int non_ca
           : longest > MidSort::kCap && longest <= LargeSort::kCap ? LargeSort::kCap : MidSort::kCap;
   s.max_ranges = row_ranges(longest, s.cap);
   const int64_t long_rows = (int64_t)Z * H * (non_causal ? N : N - 1);
-  s.split = s.max_ranges >= kSplitRanges && long_rows >= kSplitRows;
+  s.split = split_pays(long_rows, s.max_ranges, non_causal);
+  s.groups = (int)(long_rows < kSplitGroups ? long_rows : kSplitGroups);
   size_t off = 0;
   // (integer arithmetic: the size query carves from a null base)
   auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return (char*)((uintptr_t)base + o); };
@@ -154,7 +172,7 @@ static Scratch carve(void* base, int Z, int H, int Hkv, int L, int S, int non_ca
   s.ticket = (uint32_t*)take(64);
   s.left_over = (int2*)take(s.split ? (size_t)rows * s.max_ranges * 8 : 0);
   s.sk = (float*)take((size_t)Z * H * P * 4);
-  s.pairs = (uint64_t*)take(s.split ? (size_t)kSplitGroups * s.max_ranges * s.cap * 8 : 0);
+  s.pairs = (uint64_t*)take(s.split ? (size_t)s.groups * s.max_ranges * s.cap * 8 : 0);
   // the size reported to callers stays at no less than 8 bytes per ranked key
   s.total = off > (size_t)Z * H * P * 8 ? off : align256((size_t)Z * H * P * 8);
   return s;
@@ -1338,7 +1356,7 @@ static void launch_row_sort(const PlanArgs& a, const Scratch& sc, int cus, hipSt
 
 static void launch_split_sort(const PlanArgs& a, const Scratch& sc, hipStream_t stream) {
   const int64_t rows = (int64_t)a.Z * a.H * (a.non_causal ? a.N : a.N - 1);
-  hipLaunchKernelGGL(split_sort_kernel<MidSort>, dim3((unsigned)(rows < kSplitGroups ? rows : kSplitGroups)),
+  hipLaunchKernelGGL(split_sort_kernel<MidSort>, dim3((unsigned)sc.groups),
                      dim3(MidSort::kThreads), MidSort::kLds + kSplitLds, stream, a, sc, (int)rows);
   hipLaunchKernelGGL((row_sort_kernel<MidSort, kLeftOver>), dim3(kSplitGroups), dim3(MidSort::kThreads), MidSort::kLds,
                      stream, a, sc, 1, 1);
