@@ -68,7 +68,8 @@ __device__ inline float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0
 
 // ---------------------------------------------------------------------------------------
 constexpr int kMapBins = 256;      // linear pieces of the map
-// Shapes of the LDS sort: threads and keys per thread; 36 fine buckets per thread.
+// Shapes of the LDS sort: threads and keys per thread; 36 fine buckets per thread, that is 4.5, 2.8, 2.8
+// and 2.3 per key for a full set of the shapes below.
 template <int kT, int kPer>
 struct SortShape {
   static constexpr int kThreads = kT, kPerThread = kPer, kCap = kT * kPer;
@@ -83,6 +84,7 @@ struct SortShape {
 using SmallSort = SortShape<256, 8>;     // 2048 keys, 29 KB: five workgroups per CU
 using MidSort = SortShape<512, 13>;      // 6656 keys, 77 KB: two per CU
 using LargeSort = SortShape<1024, 13>;   // 13312 keys, 153 KB: one per CU
+using QuerySort = SortShape<512, 16>;    // 8192 keys, 89 KB: one per CU
 
 // Rows longer than the sort's capacity are cut into ranges of this many keys on average.  The
 // cuts come from a 1-in-32 sample, so the population of a range of the medium shape scatters by
@@ -336,13 +338,14 @@ __device__ __forceinline__ uint32_t ahead_of(uint64_t p, float s, uint32_t tok) 
 // barrier in front.  bounded: all scores are known to lie in [flo, fhi]; otherwise the range is
 // found first.
 //
-// Linear time: a monotone map of the score to 36 x kThreads fine buckets (about three per key) by
+// Linear time: a monotone map of the score to 36 x kThreads fine buckets (two to five per key) by
 // one counting atomic, which also ranks the key inside its bucket, a scan of the counters, and
 // every key is put at its bucket's place.  What is left is the order inside a bucket: keys that
-// share one, about a quarter, are listed, and a full set of lanes works on the list: each is
+// share one, a quarter to a half, are listed, and a full set of lanes works on the list: each is
 // compared with its bucket's pairs and its token put at its final place.  (Comparing from where
 // the keys are, three lanes in four idle, took 37 instead of 17 vector instructions per 64 keys.)
-// A bucket of over 60 keys (many equal scores, or an outlier that stretches the range) sends the
+// A bucket of over 60 keys (many equal scores, or an outlier that stretches the range), or a list of
+// more than kWords, sends the
 // whole set to a bitonic network instead.
 //
 // What bounds it is LDS and vector instructions alike: per 64 keys one atomic, one random 4-byte
@@ -356,6 +359,7 @@ __device__ __forceinline__ void block_sort(const SortLds<Shape>& m, int n, float
   constexpr int T = Shape::kThreads, kPer = Shape::kPerThread, kWaves = T / 64;
   constexpr int kW = Shape::kWords / T;             // bucket words of a thread
   static_assert(Shape::kCap <= 16384 && kW % 4 == 0, "packing of the bucket words");
+  static_assert(3 * Shape::kWords >= 2 * Shape::kCap, "the list of keys that share a bucket has to fit kWords");
   const int tid = fresh(threadIdx.x), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int left = n - tid;                               // key e exists iff e * T < left
   uint32_t* const wlo = m.misc;                     // [16]
@@ -557,27 +561,32 @@ __device__ __forceinline__ void block_sort(const SortLds<Shape>& m, int n, float
 
 // ---------------------------------------------------------------------------------------
 // One workgroup per (z, h, n) = row_id: q_mean (kMean), s_Q and Q_perm (kSort) of the segment in
-// one pass over Q.
+// one pass over Q.  Sixteen rows at a time, each by 16 lanes with 8 columns (256 threads) or 32 lanes
+// with 4 (512 threads, which the sorts of more than 2048 queries need).  The sums are taken in one
+// order whatever the number of threads: a product's 8-column chain runs on from the even lane to the
+// odd one.
 template <class Shape, bool kMean, bool kSort>
 __device__ __forceinline__ void pool_segment(const PlanArgs& a, const Scratch& sc, int64_t row_id, unsigned char* smem) {
-  static_assert(Shape::kThreads == 256, "the row loop is written for 256 threads");
+  constexpr int T = Shape::kThreads, kLanes = T / 16, kCols = kD / kLanes;
+  static_assert(T == 256 || T == 512, "the row loop is written for 16 or 32 lanes a row");
+  typedef uint32_t Piece __attribute__((ext_vector_type(kCols / 2)));
   float* sq = reinterpret_cast<float*>(smem);                       // [S] scores; the sort's LDS later
-  float* red = sq + (kSort ? Shape::kCap : 0);                      // [4 wavefronts][128]
-  static_assert(4 * (size_t)Shape::kCap >= 4 * 4 * kD, "the partial sums fit behind the scores");
+  float* red = sq + (kSort ? Shape::kCap : 0);                      // [wavefronts][128]
+  static_assert(!kSort || 4 * (size_t)Shape::kCap + T / 64 * 4 * kD <= Shape::kLds, "the partial sums fit behind the scores");
 
   const int G = a.H / a.Hkv;
   const int n = (int)(row_id % a.N);                                // row_id = (z*H + h)*N + n
   const int h = (int)((row_id / a.N) % a.H);
   const int z = (int)(row_id / ((int64_t)a.N * a.H));
   const int g = h / G;
-  const int tid = threadIdx.x, c = tid & 15, r = tid >> 4;
+  const int tid = threadIdx.x, c = tid % kLanes, r = tid / kLanes;
   const uint16_t* Qs = a.Q + z * a.qs[0] + h * a.qs[1] + (int64_t)n * a.S * a.qs[2];
   // k_guide = mean of the first key segment, from the partial sums in a fixed order
-  const float* kg = sc.kguide + ((int64_t)z * a.Hkv + g) * kGuideParts * kD + 8 * c;
-  float kgv[8];
+  const float* kg = sc.kguide + ((int64_t)z * a.Hkv + g) * kGuideParts * kD + kCols * c;
+  float kgv[kCols];
   if constexpr (kSort) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < kCols; ++j) {
       float t = 0.f;
 #pragma unroll
       for (int pp = 0; pp < kGuideParts; ++pp) t += kg[pp * kD + j];
@@ -586,55 +595,75 @@ __device__ __forceinline__ void pool_segment(const PlanArgs& a, const Scratch& s
   }
   if (kSort && a.k_guide && n == 0 && h % G == 0 && r == 0) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) a.k_guide[((int64_t)z * a.Hkv + g) * kD + 8 * c + j] = kgv[j];
+    for (int j = 0; j < kCols; ++j) a.k_guide[((int64_t)z * a.Hkv + g) * kD + kCols * c + j] = kgv[j];
   }
 
-  // Four rows of a thread per trip, all four 16-byte loads issued before the first is used
-  // (S is a multiple of 64: no tail).
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int row0 = r; row0 < a.S; row0 += 64) {
-    u32x4 v4[4];
+  // Four rows of a thread per trip, all four loads issued before the first is used (S is a multiple
+  // of 64: no tail).  With 8-byte pieces the next trip's loads are on their way during a trip.
+  constexpr bool kAhead = kLanes == 32;
+  auto load = [&](Piece (&x)[4], int row0) {
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      v4[u] = *reinterpret_cast<const u32x4*>(Qs + (int64_t)(row0 + 16 * u) * a.qs[2] + 8 * c);
+      x[u] = *reinterpret_cast<const Piece*>(Qs + (int64_t)(row0 + 16 * u) * a.qs[2] + kCols * c);
+  };
+  float acc[kCols] = {};
+  Piece v4[4];
+  if constexpr (kAhead) load(v4, r);
+  for (int row0 = r; row0 < a.S; row0 += 64) {
+    Piece next[4];
+    if constexpr (kAhead) load(next, min(row0, a.S - 128 + r) + 64);
+    else load(v4, row0);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int row = row0 + 16 * u;
-      const u32x4 v = v4[u];
-      float dot = 0.f;
+      const Piece v = v4[u];
+      float x[kCols];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float x0 = bf16_lo(v[q]), x1 = bf16_hi(v[q]);
-        if constexpr (kMean) { acc[2 * q] += x0; acc[2 * q + 1] += x1; }
-        if constexpr (kSort) {
-          dot = fmaf(x0, kgv[2 * q], dot);
-          dot = fmaf(x1, kgv[2 * q + 1], dot);
-        }
+      for (int q = 0; q < kCols / 2; ++q) { x[2 * q] = bf16_lo(v[q]); x[2 * q + 1] = bf16_hi(v[q]); }
+      if constexpr (kMean) {
+#pragma unroll
+        for (int j = 0; j < kCols; ++j) acc[j] += x[j];
       }
       if constexpr (!kSort) continue;
-      dot += __shfl_xor(dot, 8);
-      dot += __shfl_xor(dot, 4);
-      dot += __shfl_xor(dot, 2);
-      dot += __shfl_xor(dot, 1);
-      if (c == 0) {
+      auto chain = [&](float t) {
+#pragma unroll
+        for (int j = 0; j < kCols; ++j) t = fmaf(x[j], kgv[j], t);
+        return t;
+      };
+      float dot = chain(0.f);
+      if constexpr (kLanes == 32) {
+        const float even = __shfl_xor(dot, 1);
+        dot = chain((c & 1) ? even : 0.f);        // complete in the odd lanes
+      }
+#pragma unroll
+      for (int d = kLanes / 2; d >= kLanes / 16; d >>= 1) dot += __shfl_xor(dot, d);
+      if (c == kLanes / 16 - 1) {
         sq[row] = dot;
         if (a.s_q) a.s_q[row_id * a.S + row] = dot;
       }
     }
+    if constexpr (kAhead) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v4[u] = next[u];
+    }
   }
   // ---- q_mean: column sums over the wavefront's four row groups, then over the wavefronts
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    acc[j] += __shfl_xor(acc[j], 16);
+  for (int j = 0; j < kCols; ++j) {
+    if constexpr (kLanes == 16) acc[j] += __shfl_xor(acc[j], 16);
     acc[j] += __shfl_xor(acc[j], 32);
   }
-  if (kMean && (tid & 63) < 16) {
+  if (kMean && (tid & 63) < kLanes) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) red[(tid >> 6) * kD + 8 * c + j] = acc[j];
+    for (int j = 0; j < kCols; ++j) red[(tid >> 6) * kD + kCols * c + j] = acc[j];
   }
   __syncthreads();
   if (kMean && tid < kD) {
-    float s = (red[tid] + red[kD + tid]) + (red[2 * kD + tid] + red[3 * kD + tid]);
+    float p[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      p[w] = kLanes == 16 ? red[w * kD + tid] : red[2 * w * kD + tid] + red[(2 * w + 1) * kD + tid];
+    float s = (p[0] + p[1]) + (p[2] + p[3]);
     s *= 1.0f / (float)a.S;
     if (a.q_mean) a.q_mean[row_id * kD + tid] = s;
     // exact three-way bf16 split (truncation keeps every step exact in fp32)
@@ -653,7 +682,7 @@ __device__ __forceinline__ void pool_segment(const PlanArgs& a, const Scratch& s
   uint32_t tok[Shape::kPerThread];
 #pragma unroll
   for (int e = 0; e < Shape::kPerThread; ++e) {
-    const int i = tid + e * 256;
+    const int i = tid + e * T;
     tok[e] = (uint32_t)i;
     f[e] = sort_score(i < a.S ? sq[i] : 0.f);
   }
@@ -662,8 +691,10 @@ __device__ __forceinline__ void pool_segment(const PlanArgs& a, const Scratch& s
   block_sort<Shape>(m, a.S, f, tok, false, 0.f, 0.f, a.q_perm + row_id * a.S);
 }
 
+// (Two workgroups per CU where the sort's LDS allows it.)
 template <class Shape>
-__global__ __launch_bounds__(256) void pool_sq_sort_kernel(PlanArgs a, Scratch sc) {
+__global__ __launch_bounds__(Shape::kThreads, Shape::kThreads == 512 ? (Shape::kLds <= 81920 ? 4 : 2) : 1)
+void pool_sq_sort_kernel(PlanArgs a, Scratch sc) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   pool_segment<Shape, true, true>(a, sc, blockIdx.x, smem);
 }
@@ -1372,7 +1403,6 @@ static void launch_split_sort(const PlanArgs& a, const Scratch& sc, hipStream_t 
 // rows of 2048 87.0 / 89.6.
 constexpr int64_t kBesideRows = 256, kBesideQueries = 1 << 17;
 using PoolSort512 = SortShape<256, 2>;
-using PoolSort8192 = SortShape<256, 32>;
 
 hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
   const Scratch sc = carve(a.scratch, a.Z, a.H, a.Hkv, a.L, a.S, a.non_causal);
@@ -1387,7 +1417,8 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
     static uint64_t done = 0;
     const hipError_t se = once_per_device(mu, done, [] {
       const struct { const void* f; size_t lds; } big[] = {
-          {reinterpret_cast<const void*>(&pool_sq_sort_kernel<PoolSort8192>), PoolSort8192::kLds},
+          {reinterpret_cast<const void*>(&pool_sq_sort_kernel<MidSort>), MidSort::kLds},
+          {reinterpret_cast<const void*>(&pool_sq_sort_kernel<QuerySort>), QuerySort::kLds},
           {reinterpret_cast<const void*>(&row_sort_kernel<MidSort, kWhole>), MidSort::kLds},
           {reinterpret_cast<const void*>(&row_sort_kernel<MidSort, kScan>), MidSort::kLds},
           {reinterpret_cast<const void*>(&row_sort_kernel<MidSort, kLeftOver>), MidSort::kLds},
@@ -1430,8 +1461,13 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
       hipLaunchKernelGGL(pool_sq_sort_kernel<PoolSort512>, grid, block, PoolSort512::kLds, stream, a, sc);
     else if (a.S <= SmallSort::kCap)
       hipLaunchKernelGGL(pool_sq_sort_kernel<SmallSort>, grid, block, SmallSort::kLds, stream, a, sc);
+    // Above 2048 queries 512 threads sort: with 256 and 32 keys each there is about one bucket per key,
+    // and from 5.4K queries on the list of keys that share one overflows into the bitonic network.  32
+    // segments of 4096 88 -> 78 us, of 5632 277 -> 105, of 8192 326 -> 149; 2048 of 5632 1426 -> 687.
+    else if (a.S <= MidSort::kCap)
+      hipLaunchKernelGGL(pool_sq_sort_kernel<MidSort>, grid, dim3(MidSort::kThreads), MidSort::kLds, stream, a, sc);
     else
-      hipLaunchKernelGGL(pool_sq_sort_kernel<PoolSort8192>, grid, block, PoolSort8192::kLds, stream, a, sc);
+      hipLaunchKernelGGL(pool_sq_sort_kernel<QuerySort>, grid, dim3(QuerySort::kThreads), QuerySort::kLds, stream, a, sc);
     if (score_blocks > 0)
       hipLaunchKernelGGL(score_kernel, dim3((unsigned)score_blocks), dim3(64 * kScoreWaves), kScoreLds, stream, a, sc);
   }
