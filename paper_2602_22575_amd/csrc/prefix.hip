@@ -23,8 +23,10 @@
 // the compiler guards the accumulator, loaded from the state in front of the loop, with waits of
 // its own for all fetches in flight, in the middle of every step.  Walk without a stop rule,
 // contiguous 8K keys x 32 heads: 1090 -> 1000 us together with the PV product moved one step
-// late as in the walk with votes (with either one alone 1065 to 1088); a layer of 128K tokens
-// at 5e-3 1.04 -> 1.09 of the speed before.
+// late as in the walk with votes (with either one alone 1065 to 1088).  In the walk with votes, 32
+// heads, time against a wait in assembly text: 128K at 2e-2 0.97, at 5e-3 0.99, at 1e-3 0.99 to 1.01,
+// 32K at 5e-3 0.98; where no tile is skipped (1e-37, say) 1.01 at 32K and 1.02 to 1.03 at 128K, since
+// what a step then spends is power, not cycles.  A threshold of 0 or less has no votes to take.
 //
 // The single-launch form (no state buffer) runs the own-segment tiles through the same
 // pipeline first.  It is bound by the matrix products: a query tile in permuted order has rows
@@ -52,14 +54,15 @@ __device__ __forceinline__ uint32_t clamp_token(int x, int hi) {
   return (uint32_t)r;
 }
 
-// kNoStop: stop_mode 2 (every prefix tile folded in, the paper's kernel C) as an instantiation
-// of its own, so that neither loop's registers weigh on the other.
+// kNoStop: every prefix tile is folded in (stop_mode 2, the paper's kernel C; a state buffer and a
+// threshold of 0 or less), as an instantiation of its own, so that neither loop's registers weigh on the other.
 // kMapped: the walk follows a KV_perm row (always, except the non-causal walk in storage order,
 // which then does not carry the map's registers and selects).
 // kOwn: the single-launch form for callers without a state buffer.  The key tiles of the
 // segment itself are folded in first, with the causal mask per row, and the state never leaves
 // the registers.  Tiles are numbered through: 0 .. nloc-1 the own segment's, then the prefix's.
-template <bool kNoStop, bool kMapped, bool kOwn>
+// kExactReference: the softmax reference moves as in softmax_tile (see attn_tile.h).
+template <bool kNoStop, bool kMapped, bool kOwn, bool kExactReference>
 __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs a) {
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];   // OperandAddr needs a 256-byte base
   uint16_t* Ks = reinterpret_cast<uint16_t*>(smem);
@@ -306,12 +309,16 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   auto fold = [&] {                             // a tile that is kept without a vote
     pack_p(s, pb_pend);
     alpha_pend = ts.alpha; grow_pend = ts.grow;
-    l_run = fmaf(l_run, ts.alpha, ts.mass);     // (one rounding, written out: as prev + mass it is up to the compiler)
+    if constexpr (kExactReference) {
+      l_run = fmaf(l_run, ts.alpha, ts.mass);   // (one rounding, written out: as prev + mass it is up to the compiler)
+    } else {
+#pragma clang fp contract(off)
+      l_run = ts.prev + ts.mass;                // (two roundings, as in the walk with votes)
+    }
     m_ref = ts.m_use;
     pending = true;
   };
   // rare: the tile may move some row's reference
-  constexpr bool kExactReference = kNoStop || kOwn;
   auto again = [&](const OperandAddr& fa) {
     if (kExactReference && __builtin_amdgcn_ballot_w64(confirm_redo(s, ts.mass)) == 0ull) return;
     qk_tile_only<0>(fa, qf, s);
@@ -355,9 +362,13 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
       fetch_step(it);
       if (active) {
         products(fa);
-        bool redo;
-        ts = softmax_tile_keep_reference<kExactReference>(s, c2, m_ref, l_run, redo);
-        if (__builtin_amdgcn_ballot_w64(redo) != 0ull) again(fa);
+        if (!kExactReference && it == nloc) {
+          softmax();                              // (the walk with votes does so with its first tile)
+        } else {
+          bool redo;
+          ts = softmax_tile_keep_reference<kExactReference>(s, c2, m_ref, l_run, redo);
+          if (__builtin_amdgcn_ballot_w64(redo) != 0ull) again(fa);
+        }
         fold();
       }
       aim_next(fa, it);
@@ -455,12 +466,14 @@ hipError_t launch_prefix(const AttnArgs& a, hipStream_t stream) {
   static std::mutex mu;
   static uint64_t done = 0;
   const hipError_t se = once_per_device(mu, done, [] {
-    const void* fns[6] = {reinterpret_cast<const void*>(&s2o_prefix_kernel<false, true, false>),
-                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, true, false>),
-                          reinterpret_cast<const void*>(&s2o_prefix_kernel<false, false, false>),
-                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, false, false>),
-                          reinterpret_cast<const void*>(&s2o_prefix_kernel<false, true, true>),
-                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, true, true>)};
+    const void* fns[8] = {reinterpret_cast<const void*>(&s2o_prefix_kernel<false, true, false, false>),
+                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, true, false, false>),
+                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, true, false, true>),
+                          reinterpret_cast<const void*>(&s2o_prefix_kernel<false, false, false, false>),
+                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, false, false, false>),
+                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, false, false, true>),
+                          reinterpret_cast<const void*>(&s2o_prefix_kernel<false, true, true, true>),
+                          reinterpret_cast<const void*>(&s2o_prefix_kernel<true, true, true, true>)};
     for (const void* f : fns) {
       const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPrefixLds);
       if (e != hipSuccess) return e;
@@ -475,10 +488,18 @@ hipError_t launch_prefix(const AttnArgs& a, hipStream_t stream) {
   if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kThreads);
   auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, kPrefixLds, stream, a); };
-  const bool no_stop = a.stop_mode == 2;
-  if (a.passes == 0) no_stop ? launch(s2o_prefix_kernel<true, true, true>) : launch(s2o_prefix_kernel<false, true, true>);
-  else if (a.kv_perm) no_stop ? launch(s2o_prefix_kernel<true, true, false>) : launch(s2o_prefix_kernel<false, true, false>);
-  else no_stop ? launch(s2o_prefix_kernel<true, false, false>) : launch(s2o_prefix_kernel<false, false, false>);
+  // A threshold of 0 or less never stops, so nothing is lost by leaving the votes out (us with /
+  // without them, 32 heads: 8K 496 / 463, 32K 8018 / 7502, 128K 134462 / 124775).  The reference then
+  // still moves as in the walk with votes, and the results keep its bits.  (The single launch's
+  // normaliser is rounded otherwise without votes: there the votes stay.)
+  const bool rule = a.stop_mode != 2, no_stop = !rule || a.tau <= 0.f;
+  if (a.passes == 0) !rule ? launch(s2o_prefix_kernel<true, true, true, true>) : launch(s2o_prefix_kernel<false, true, true, true>);
+  else if (a.kv_perm)
+    !no_stop ? launch(s2o_prefix_kernel<false, true, false, false>)
+             : rule ? launch(s2o_prefix_kernel<true, true, false, false>) : launch(s2o_prefix_kernel<true, true, false, true>);
+  else
+    !no_stop ? launch(s2o_prefix_kernel<false, false, false, false>)
+             : rule ? launch(s2o_prefix_kernel<true, false, false, false>) : launch(s2o_prefix_kernel<true, false, false, true>);
   return hipGetLastError();
 }
 
