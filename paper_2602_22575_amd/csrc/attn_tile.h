@@ -131,35 +131,13 @@ __device__ __forceinline__ void static_for(F&& f) {
 __device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(lvoid*)p; }
 
 template <int kOff>
-__device__ __forceinline__ void lds_issue_b128(bf16x8& d, uint32_t addr) {
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(kOff) : "memory");
+__device__ __forceinline__ void lds_issue_b128_x2(bf16x8& d0, bf16x8& d1, uint32_t addr) {   // two reads, 32 rows apart
+  asm volatile("ds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4"
+               : "=&v"(d0), "=&v"(d1) : "v"(addr), "n"(kOff), "n"(kOff + kTileElems) : "memory");
 }
 template <int kOff>
 __device__ __forceinline__ void lds_issue_tr64(u32x2& d, uint32_t addr) {
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(kOff) : "memory");
-}
-// The same reads at address (addr ^ kXor): the XOR stays next to its read (a separate statement
-// would be hoisted out of the loop and cost the register it was meant to save).
-template <int kOff, int kXor>
-__device__ __forceinline__ void lds_issue_b128_x2(bf16x8& d0, bf16x8& d1, uint32_t addr) {   // two reads, 32 rows apart
-  if constexpr (kXor == 0) {
-    asm volatile("ds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4"
-                 : "=&v"(d0), "=&v"(d1) : "v"(addr), "n"(kOff), "n"(kOff + kTileElems) : "memory");
-  } else {
-    uint32_t t;
-    asm volatile("v_xor_b32 %2, %5, %3\n\tds_read_b128 %0, %2 offset:%4\n\tds_read_b128 %1, %2 offset:%6"
-                 : "=&v"(d0), "=&v"(d1), "=&v"(t) : "v"(addr), "n"(kOff), "n"(kXor), "n"(kOff + kTileElems) : "memory");
-  }
-}
-template <int kOff, int kXor>
-__device__ __forceinline__ void lds_issue_tr64_x(u32x2& d, uint32_t addr) {
-  if constexpr (kXor == 0) {
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(kOff) : "memory");
-  } else {
-    uint32_t t;
-    asm volatile("v_xor_b32 %1, %4, %2\n\tds_read_b64_tr_b16 %0, %1 offset:%3"
-                 : "=&v"(d), "=&v"(t) : "v"(addr), "n"(kOff), "n"(kXor) : "memory");
-  }
 }
 // The named values are valid once at most kYounger LDS reads issued after them are outstanding.
 template <int kYounger>
@@ -170,18 +148,6 @@ template <int kYounger>
 __device__ __forceinline__ void lds_wait(u32x2& a, u32x2& b) {
   asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(kYounger));
 }
-// Small reads issued among the fragment reads (stop votes, token indices): issue now, claim
-// when at most kYounger reads issued after them may still be in flight.
-__device__ __forceinline__ void lds_issue_word4(u32x4& d, uint32_t addr) {
-  asm volatile("ds_read_b128 %0, %1" : "=v"(d) : "v"(addr) : "memory");
-}
-__device__ __forceinline__ void lds_issue_word(uint32_t& d, uint32_t addr) {
-  asm volatile("ds_read_b32 %0, %1" : "=v"(d) : "v"(addr) : "memory");
-}
-template <int kYounger>
-__device__ __forceinline__ void lds_wait(u32x4& a) { asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(a) : "n"(kYounger)); }
-template <int kYounger>
-__device__ __forceinline__ void lds_wait(uint32_t& a) { asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(a) : "n"(kYounger)); }
 // All global->LDS tile loads (and every other global load) of this wavefront have landed.
 __device__ __forceinline__ void wait_tile_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // The same wait, for all but the kYoungest most recent vector-memory instructions of the
@@ -230,7 +196,6 @@ struct OperandAddr {
 };
 
 constexpr int kTileBytes = kTileElems * 2;          // 16 KB
-constexpr int kHalfTileBytes = kTileBytes / 2;      // key block 1 of a K tile
 constexpr int kVStepBytes = 16 * kRowElems * 2;     // one 16-key contraction step of a V tile
 
 // The 16 K-fragment reads and 32 V^T-fragment reads of one step form one issue sequence
@@ -253,26 +218,20 @@ constexpr int issued_at_qk(int kk, bool with_v) {
 
 template <int kVOff, int c>
 __device__ __forceinline__ void issue_v_fragment(const OperandAddr& oa, u32x2 (&vf)[16][2]) {
-  lds_issue_tr64_x<kVOff + (c / 4) * kVStepBytes, 0>(vf[c][0], oa.v[c % 4]);
-  lds_issue_tr64_x<kVOff + (c / 4) * kVStepBytes + 8 * kRowElems * 2, 0>(vf[c][1], oa.vx[c % 4]);
+  lds_issue_tr64<kVOff + (c / 4) * kVStepBytes>(vf[c][0], oa.v[c % 4]);
+  lds_issue_tr64<kVOff + (c / 4) * kVStepBytes + 8 * kRowElems * 2>(vf[c][1], oa.vx[c % 4]);
 }
 
 // S^T = K Q^T for the K tile at byte offset kKOff from the addresses in `oa`.  kWithV: also
 // start the V^T reads of fragments 0..kVEarly-1 of the V tile at byte offset kVOff.
-// `pre()` runs once the first K reads are out and before the first MFMA waits for them;
-// `mid(kk)` after the MFMAs of contraction step kk have been handed over: work that only issues
-// (LDS reads of its own, tile fetches for the next step) goes there, under the matrix pipe's
-// shadow.  LDS reads issued from the hooks make the fragment waits a little conservative
-// (they count only the fragment reads), never wrong.
-template <int kKOff, int kVOff, bool kWithV, class Pre, class Mid>
+template <int kKOff, int kVOff, bool kWithV>
 __device__ __forceinline__ void qk_tile_sched(const OperandAddr& oa, const bf16x8 (&qf)[8], f32x16 (&s)[2],
-                                              u32x2 (&vf)[16][2], Pre&& pre, Mid&& mid) {
+                                              u32x2 (&vf)[16][2]) {
   bf16x8 ka[8][2];
   static_for<0, kKAhead>([&](auto kk_) {
     constexpr int kk = decltype(kk_)::value;
-    lds_issue_b128_x2<kKOff, 0>(ka[kk][0], ka[kk][1], oa.k[kk]);
+    lds_issue_b128_x2<kKOff>(ka[kk][0], ka[kk][1], oa.k[kk]);
   });
-  pre();
   static_for<0, 8>([&](auto kk_) {
     constexpr int kk = decltype(kk_)::value;
     lds_wait<issued_at_qk(kk, kWithV) - (2 * kk + 2)>(ka[kk][0], ka[kk][1]);
@@ -287,27 +246,13 @@ __device__ __forceinline__ void qk_tile_sched(const OperandAddr& oa, const bf16x
       s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk][1], qf[kk], s[1], 0, 0, 0);
     }
     if constexpr (kk + kKAhead < 8) {
-      lds_issue_b128_x2<kKOff, 0>(ka[kk + kKAhead][0], ka[kk + kKAhead][1], oa.k[kk + kKAhead]);
+      lds_issue_b128_x2<kKOff>(ka[kk + kKAhead][0], ka[kk + kKAhead][1], oa.k[kk + kKAhead]);
     } else if constexpr (kWithV) {
       issue_v_fragment<kVOff, 2 * (kk + kKAhead - 8)>(oa, vf);
       issue_v_fragment<kVOff, 2 * (kk + kKAhead - 8) + 1>(oa, vf);
     }
-    mid(kk_);
   });
 }
-template <int kKOff, int kVOff, bool kWithV>
-__device__ __forceinline__ void qk_tile_sched(const OperandAddr& oa, const bf16x8 (&qf)[8], f32x16 (&s)[2],
-                                              u32x2 (&vf)[16][2]) {
-  qk_tile_sched<kKOff, kVOff, kWithV>(oa, qf, s, vf, [] {}, [](auto) {});
-}
-
-// The V^T reads qk_tile_sched started are not going to be used: their target registers stay
-// claimed until the data has arrived (an LDS read that lands later would overwrite whatever
-// the registers had been given to).
-__device__ __forceinline__ void abandon_v_fragments(u32x2 (&vf)[16][2]) {
-  static_for<0, kVEarly>([&](auto c_) { lds_wait<0>(vf[decltype(c_)::value][0], vf[decltype(c_)::value][1]); });
-}
-
 // O^T accumulate step with the accumulator updated in place.  As a builtin the compiler is free
 // to give the result a tuple of its own, and for the loop-carried 64-register accumulator it
 // does: a copy of O^T (32 two-register moves) per key tile.  In assembly the operand is tied.
@@ -340,16 +285,11 @@ __device__ __forceinline__ void pv_tile_sched(const OperandAddr& oa, const bf16x
   mfma_settle(o);
 }
 
-// The same two products for a step that does them back to back (PV right after its scores).
-template <int kKOff, class Pre, class Mid>
-__device__ __forceinline__ void qk_tile_only(const OperandAddr& oa, const bf16x8 (&qf)[8], f32x16 (&s)[2], Pre&& pre,
-                                             Mid&& mid) {
-  u32x2 none[16][2];
-  qk_tile_sched<kKOff, 0, false>(oa, qf, s, none, pre, mid);
-}
+// The same two products alone, for a step with one of them.
 template <int kKOff>
 __device__ __forceinline__ void qk_tile_only(const OperandAddr& oa, const bf16x8 (&qf)[8], f32x16 (&s)[2]) {
-  qk_tile_only<kKOff>(oa, qf, s, [] {}, [](auto) {});
+  u32x2 none[16][2];
+  qk_tile_sched<kKOff, 0, false>(oa, qf, s, none);
 }
 template <int kVOff>
 __device__ __forceinline__ void pv_tile_only(const OperandAddr& oa, const bf16x8 (&pb)[4], f32x16 (&o)[4]) {
@@ -426,9 +366,9 @@ __device__ __forceinline__ TileStats softmax_tile(f32x16 (&s)[2], float c2, floa
 // softmax_tile.
 //
 // The reference decides at which scale the bf16 rounding of P falls, so the limit is part of the
-// result.  kMassLimit lets the reference lag by up to 2^16: the walk with votes from a state
-// buffer.  The other loops (no stop rule, single launch) give the bits that softmax_tile gives for
-// every tile: for them `redo` is already set by a mass above kSameMass, and confirm_redo drops it
+// result.  kMassLimit lets the reference lag by up to 2^16: the walk under the stop rule, but for the
+// single launch.  The other loops (no stop rule, single launch) give the bits that softmax_tile gives
+// for every tile: for them `redo` is already set by a mass above kSameMass, and confirm_redo drops it
 // again unless some numerator is near 2^kLazy, where softmax_tile would move the reference.  (A
 // row's mass is above kSameMass at every few tiles of a top-k walk; scoring all of these again cost
 // 6 % of it.)
