@@ -133,7 +133,7 @@ int s2o_plan(const void* Q, const void* K, const s2o_params* params, const s2o_p
  * frees nothing (the array's address is looked up once per GPU, on the first call there).
  *   - Limit: configurations whose s2o_plan_sizes scratch_bytes exceed S2O_STATIC_SCRATCH_BYTES
  *     are refused with S2O_ESCRATCH before anything is enqueued (e.g. the Llama-3.1-8B head
- *     shape fits up to 8K tokens at S = 1024; 128K needs s2o_plan with a caller buffer).
+ *     shape fits up to 16K tokens at S = 1024; 128K needs s2o_plan with a caller buffer).
  *   - Every GPU the library is loaded on holds the array until the process ends.
  *   - All calls on one GPU share that GPU's array: calls whose kernels may overlap (different
  *     streams, or other host threads) race; order them.  Contents do not survive the call; what
@@ -164,6 +164,8 @@ int s2o_attention_sizes(const s2o_params* params, size_t* counts_bytes, size_t* 
  *            prev_i = l_i * exp(m_i - m'_i) (the old normaliser in the new scale) the
  *            walk stops at the first tile where mass_i < tau * prev_i for every row i of
  *            the query tile.  tau <= 0 never stops and reproduces dense causal attention.
+ *            (Where the test is evaluated -- tau > 0, or the fused launch at any tau -- a tile whose
+ *            mass is NaN in every row stops the walk.)
  *   O        [Z,H,L,D] bf16, rows in original order.
  *   computed [Z,H,L/B_M] prefix tiles folded into the output of permuted query tile
  *            n*(S/B_M)+j; skipped: prefix tiles never loaded.  n*S/B_N - computed - skipped

@@ -24,9 +24,9 @@
 //
 // Measured against the form this replaces, which scattered (key, token) pairs of all rows to
 // buckets in memory, packed the buckets into spans and sorted those (eight launches of its own,
-// Llama head shape, us): 4K tokens in 512-token segments 76 -> 34 for the whole ranking, 8K 109 ->
-// 52, 32K 285 -> 181, 64K in 1024-token segments 1015 -> 754, 128K 1830 -> 1440, and 3700 -> 1440
-// where far-off scores had sent the old spans to their bitonic network.
+// Llama head shape, us for the whole ranking): 4K tokens in 512-token segments 77 -> 31, 8K in 1024
+// 110 -> 51, 32K in 2048 277 -> 179, 64K in 1024 1005 -> 752, 128K in 2048 1808 -> 1385, in 4096 1129 ->
+// 886, and 3700 -> 1440 where far-off scores had sent the old spans to their bitonic network.
 //
 // Argsort semantics: descending score, ties by ascending index, -0 == +0.
 #include <float.h>
@@ -344,9 +344,9 @@ __device__ __forceinline__ uint32_t ahead_of(uint64_t p, float s, uint32_t tok) 
 // share one, a quarter to a half, are listed, and a full set of lanes works on the list: each is
 // compared with its bucket's pairs and its token put at its final place.  (Comparing from where
 // the keys are, three lanes in four idle, took 37 instead of 17 vector instructions per 64 keys.)
-// A bucket of over 60 keys (many equal scores, or an outlier that stretches the range), or a list of
-// more than kWords, sends the
-// whole set to a bitonic network instead.
+// A bucket of over 60 keys (many equal scores, or an outlier that stretches the range) sends the
+// whole set to a bitonic network instead, and so does a list of more than kWords (full buckets
+// everywhere).
 //
 // What bounds it is LDS and vector instructions alike: per 64 keys one atomic, one random 4-byte
 // read and one random 8-byte write, 9 to 12 clocks each, the list about the same again; and about
@@ -1396,7 +1396,7 @@ static void launch_split_sort(const PlanArgs& a, const Scratch& sc, hipStream_t 
 
 // Small inputs: s_Q and its Argsort run beside the scores, k_guide beside q_mean -- one launch less
 // in the chain, and the query sort out of it, for a second read of Q that the caches serve.  Worth
-// it as long as the chip is not full (one workgroup per CU for the query rows) and Q is small; us
+// it as long as the chip (256 CUs) is not full with one workgroup per query row and Q is small; us
 // for the whole ranking, sort in front / beside (32 heads over 8): 8 rows of 64 20.1 / 14.7, 256
 // rows of 256 27.0 / 22.3, 256 rows of 512 34.2 / 31.3, 128 rows of 1024 43.8 / 42.0; on the other
 // side 256 rows of 1024 50.9 / 50.9, 512 rows of 512 53.9 / 59.5, 1024 rows of 256 78.5 / 87.4, 256

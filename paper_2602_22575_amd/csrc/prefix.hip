@@ -31,9 +31,12 @@
 // The single-launch form (no state buffer) runs the own-segment tiles through the same
 // pipeline first.  It is bound by the matrix products: a query tile in permuted order has rows
 // anywhere in the segment and needs all S/64 own tiles where one in original order stops at its
-// diagonal, which is why a caller with a state buffer gets two launches.  16K tokens, 32 heads,
-// original order, threshold 5e-3: 740 us of ranking and attention against 960 us with the
-// 8-wavefront workgroups (one per CU, operand reads placed by the compiler) it replaces.
+// diagonal, which is why a caller with a state buffer gets two launches.  Single launch against two,
+// permuted order, 32 heads (time, two launches = 1): segments of 64 and 256 tokens 0.82 to 0.95, of
+// 512 0.98, of 1024 1.05, of 2048 1.04 to 1.12, of 4096 1.25, of 8192 1.48; original order 0.80 to 1.00.
+// Against the 8-wavefront workgroups (one per CU, operand reads placed by the compiler) it replaces:
+// permuted order 0.82 to 0.89 from 512-token segments on, original order 0.74 to 0.86; 16K tokens,
+// 32 heads, original order, threshold 5e-3, with the ranking 1028 -> 697 us.
 #include "attn_tile.h"
 #include "s2o_internal.h"
 

@@ -7,7 +7,8 @@
         A  contiguous causal attention (S = L: one segment, no maps)
         B  + indexed gather with identity maps          (stop_mode 2)
         C  + ranked maps from s2o_plan                  (stop_mode 2)
-        D  + the early-stop vote, never stopping        (stop_mode 0, tau = -1)
+        D  + the early-stop vote, never stopping        (stop_mode 0, tau = 1e-37: a threshold
+           of 0 or less would leave the votes out)
       followed by the same four in the non-causal setting (params.non_causal: every query
       walks all L keys; A is the walk without a key map).
   python -m paper_2602_22575_amd.studies topk         fixed budget on the ranked order (the top-k
@@ -27,8 +28,8 @@
       the dense output, for the two-launch form, the fused launch, and original query order.
 
   python -m paper_2602_22575_amd.studies power        is the prefix walk limited by its instruction
-      schedule or by the chip's power budget?  The same dense walk (tau = 0: every tile folded
-      in, identical instruction stream) on the workload's Gaussian data, with V zeroed, and with
+      schedule or by the chip's power budget?  The same dense walk (tau = 1e-37: every tile
+      folded in after its vote, identical instruction stream) on the workload's Gaussian data, with V zeroed, and with
       Q, K and V all zero, with the shader clock the driver reports sampled meanwhile: equal
       time x clock products with very different clocks mean the cycle count is fixed and the
       clock is what the data's switching activity leaves of the power budget.  Followed by the
@@ -42,6 +43,8 @@ from __future__ import annotations
 import sys
 
 import numpy as np
+
+NEVER = 1e-37       # a threshold that is evaluated and that no tile's mass lies below
 
 
 def _timed(fn, iters=3):
@@ -88,7 +91,7 @@ def abcd():
         variants = [lambda: s2o.s2o_attention(Qd, Kd, Vd, pa, None, None, -1.0, **kw),
                     lambda: s2o.s2o_attention(Qd, Kd, Vd, p2, qi, ki, -1.0, **kw),
                     lambda: s2o.s2o_attention(Qd, Kd, Vd, p2, plan.q_perm, plan.kv_perm, -1.0, **kw),
-                    lambda: s2o.s2o_attention(Qd, Kd, Vd, p0, plan.q_perm, plan.kv_perm, -1.0, **kw)]
+                    lambda: s2o.s2o_attention(Qd, Kd, Vd, p0, plan.q_perm, plan.kv_perm, NEVER, **kw)]
         # the clock sags as the chip warms up: interleave the variants and take medians
         times = [[] for _ in variants]
         for rep in range(5):
@@ -121,7 +124,7 @@ def abcd():
         variants = [lambda: s2o.s2o_attention(Qd, Kd, Vd, pa, None, None, -1.0, **kw),
                     lambda: s2o.s2o_attention(Qd, Kd, Vd, p2, qi, ki, -1.0, **kw),
                     lambda: s2o.s2o_attention(Qd, Kd, Vd, p2, plan.q_perm, plan.kv_perm, -1.0, **kw),
-                    lambda: s2o.s2o_attention(Qd, Kd, Vd, p0, plan.q_perm, plan.kv_perm, -1.0, **kw)]
+                    lambda: s2o.s2o_attention(Qd, Kd, Vd, p0, plan.q_perm, plan.kv_perm, NEVER, **kw)]
         times = [[] for _ in variants]
         for rep in range(3):
             for i, fn in enumerate(variants):
@@ -286,7 +289,7 @@ def power():
         return None
 
     dense_flops = 4.0 * w.BM * w.BN * w.D * sum(n * (w.S // w.BN) * (w.S // w.BM) for n in range(w.N)) * w.Z * w.H
-    print(f"workload {w.name}: dense prefix walk (tau = 0, ranked maps of the real data in every case), 64x64 tiles")
+    print(f"workload {w.name}: dense prefix walk (tau = 1e-37, ranked maps of the real data in every case), 64x64 tiles")
     print("| data | ms | TFLOP/s | shader clock MHz (median of samples) | ms x GHz |")
     print("|---|---|---|---|---|")
     zero = lambda t: torch.zeros_like(t)
@@ -306,7 +309,7 @@ def power():
                 time.sleep(0.002)
         th = threading.Thread(target=loop)
         th.start()
-        ms = _timed(lambda: s2o.s2o_attention_prefix(q_, k_, v_, p, plan.q_perm, plan.kv_perm, 0.0, state, O=O), 3)
+        ms = _timed(lambda: s2o.s2o_attention_prefix(q_, k_, v_, p, plan.q_perm, plan.kv_perm, NEVER, state, O=O), 3)
         stop[0] = True
         th.join()
         mhz = float(np.median(samples)) if samples else float("nan")

@@ -156,3 +156,13 @@ def test_inputs_are_deterministic_and_bf16():
     q, k, _ = inputs.make_qkv(w2)
     assert q.shape == (1, 32, 1024, 128) and k.shape == (1, 8, 1024, 128)
     assert inputs.heavy_positions(w2, 0, 3)[:4].tolist() == [0, 1, 2, 3]
+
+
+@pytest.mark.parametrize("S,largest", [(256, 8192), (1024, 16384), (2048, 22528)])
+def test_built_in_scratch_limit(lib, S, largest):
+    """The longest sequence of the Llama-3.1-8B head shape that s2o_plan_static takes, and the next one."""
+    fits, beyond = (b.make_params(1, 32, 8, L, 128, S) for L in (largest, largest + S))
+    assert b.s2o_plan_sizes(fits)["scratch"] <= b.STATIC_SCRATCH_BYTES < b.s2o_plan_sizes(beyond)["scratch"]
+    fake = C.c_void_p(0x10000)
+    out = b.S2OPlanOut(q_perm=0x10000, kv_perm=0x10000)
+    assert lib.s2o_plan_static(fake, fake, C.byref(beyond), C.byref(out), None) == b.S2O_ESCRATCH   # before any HIP call
