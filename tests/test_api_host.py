@@ -67,7 +67,7 @@ def test_size_queries():
     (dict(use_q_perm=5), b.S2O_EINVAL),
     (dict(softmax_scale=-1.0), b.S2O_EINVAL),
     (dict(q_stride=(0, 0, 100)), b.S2O_EINVAL),   # row stride not 16-byte aligned / < D
-    (dict(L=2 << 20, S=2048), b.S2O_EUNSUPPORTED),          # plan: a row's sample no longer fits the LDS sort
+    (dict(L=2 << 20, S=2048), b.S2O_EUNSUPPORTED),          # plan: the ranges of a row no longer fit their table in LDS
     (dict(k_stride=(1 << 40, 1 << 36, 1 << 23)), b.S2O_EUNSUPPORTED),   # a K row stride of 16 MiB
     (dict(L=1 << 20, S=2048, v_stride=(1 << 40, 1 << 36, 4096)), b.S2O_EUNSUPPORTED),   # a V head beyond 4 GiB
 ])
