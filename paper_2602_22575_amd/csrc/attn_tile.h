@@ -540,24 +540,52 @@ __device__ __forceinline__ void store_o_rows(uint16_t* head, int64_t row_stride,
 }
 
 // block id -> (head index z*H + h, segment counted from the last, position inside the
-// segment's run of `per_seg` workgroups).  Longest prefixes first.  Consecutive block ids
-// are dealt round-robin to the 8 XCDs, each with its own L2: the workgroups of one
-// (z, h, segment) walk the same keys at about the same time, so they are given ids that land
-// on one XCD (their K/V tiles then hit in that L2), while the XCD of a head rotates with the
-// segment so that heads that stop early and heads that never stop mix evenly on every XCD.
-__device__ __forceinline__ void map_block(int b, int ZH, int per_seg, int& zh, int& nr, int& pos) {
+// segment's run of `per_seg` workgroups); false: an id that only rounds the grid up.  Longest
+// prefixes first.  Consecutive block ids are dealt round-robin to the 8 XCDs, each with its own
+// L2: workgroups of one (z, h, segment) walk the same keys at about the same time, so they are
+// given ids that land on one XCD (their K/V tiles then hit in that L2).  What an XCD is dealt is
+// fixed, while heads stop at lengths that differ by more than 3x and those of a KV group stop
+// alike: the launch takes as long as the XCD with the longest share.
+//
+// Heads a multiple of 8: a segment's heads go to the 8 XCDs in turn, shifted by 4 from one
+// segment to the next and by 1 every second segment, so that an XCD's share of every group is
+// spread evenly over long and short prefixes.  (Shifted by 1 per segment, as before, an XCD had
+// the long-walking groups in its 4 longest segments or in its 4 shortest: 32 heads, 8K tokens, 8 segments:
+// the longest share 1.18 -> 1.03 of the mean, walk 324 -> 295 us; 32K with two of 8 groups walking
+// four times as far 1.07 -> 1.02, 3290 -> 3090 us.)
+// Otherwise: runs of up to 4 of a segment's workgroups go to the XCDs in turn, shifted by 1
+// every 8 runs.  Dealt out one by one, as before, every XCD fetches every tile for itself: walk with this /
+// with runs, 4 heads, 64K tokens, 1024-token segments 2643 / 2037 us, 128K in 512 721 / 595; 12 heads, 64K in 2048
+// 2118 / 2011, 8K in 256 141 / 133; 4 heads, 128K in 2048 1225 / 1271.  Whole segments share a little more and
+// balance less (4 heads, 64K in 2048: 933 one by one, 938 in runs, 973 whole; 12 heads, 32K in 2048 591, 556, 569).
+// (Runs per segment and workgroups per run come from the host: a division takes 0.15 us of a walk that
+// may take 20.)
+struct WalkGrid {
+  int per_seg, run, runs;
+  int64_t blocks;
+};
+inline WalkGrid walk_grid(int64_t ZH, int64_t N, int per_seg) {
+  WalkGrid g;
+  g.per_seg = per_seg;
+  g.runs = (per_seg + 3) / 4;
+  g.run = (per_seg + g.runs - 1) / g.runs;
+  g.blocks = ZH % 8 == 0 ? ZH * N * per_seg : (ZH * N * g.runs + 7) / 8 * 8 * g.run;
+  return g;
+}
+__device__ __forceinline__ bool map_block(int b, int ZH, int N, const WalkGrid& w, int& zh, int& nr, int& pos) {
+  const int xcd = b & 7, idx = b >> 3;
   if (ZH % 8 == 0) {
-    const int xcd = b & 7, idx = b >> 3, per = ZH / 8;
-    pos = idx % per_seg;
-    const int unit = idx / per_seg;
+    const int per = ZH / 8, unit = idx / w.per_seg;
+    pos = idx % w.per_seg;
     nr = unit / per;
-    zh = ((xcd - nr) & 7) + 8 * (unit % per);
-  } else {
-    pos = b % per_seg;
-    const int unit = b / per_seg;
-    nr = unit / ZH;
-    zh = unit % ZH;
+    zh = ((xcd - 4 * (nr & 1) - (nr >> 1)) & 7) + 8 * (unit % per);
+    return true;
   }
+  const int k = idx / w.run, r = 8 * k + ((xcd - k) & 7), unit = r / w.runs;
+  pos = (r % w.runs) * w.run + idx % w.run;
+  nr = unit / ZH;
+  zh = unit % ZH;
+  return nr < N && pos < w.per_seg;
 }
 
 }  // namespace tile

@@ -66,7 +66,7 @@ __device__ __forceinline__ uint32_t clamp_token(int x, int hi) {
 // the registers.  Tiles are numbered through: 0 .. nloc-1 the own segment's, then the prefix's.
 // kExactReference: the softmax reference moves as in softmax_tile (see attn_tile.h).
 template <bool kNoStop, bool kMapped, bool kOwn, bool kExactReference>
-__global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs a) {
+__global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs a, const WalkGrid grid) {
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];   // OperandAddr needs a 256-byte base
   uint16_t* Ks = reinterpret_cast<uint16_t*>(smem);
   uint16_t* Vt = Ks + 2 * kTileElems;
@@ -76,18 +76,15 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m_ = lane & 31, hh = lane >> 5;
-  const int G = a.H / a.Hkv;
   const int BM = a.BM;                                   // query tile rows: 64 or 128
-  const int wpt = BM / kRowsPerWave;                     // wavefronts per query tile
-  const int tpw = kWaves / wpt;                          // query tiles per workgroup
-  const int TJ = a.S / BM;                               // query tiles per segment
-  const int JG = (TJ + tpw - 1) / tpw;                   // workgroups per (z,h,n)
+  const int tpw = BM == 64 ? 2 : 1;                      // query tiles per workgroup
+  const int TJ = a.S >> (BM == 64 ? 6 : 7);              // query tiles per segment
 
   int zh_, nr, jg;
-  map_block(blockIdx.x, a.Z * a.H, JG, zh_, nr, jg);
-  if (kOwn) jg = JG - 1 - jg;       // original order: the tiles with most own-segment keys first
-  const int n = a.N - 1 - nr, z = zh_ / a.H, h = zh_ % a.H;
-  const int g = h / G;
+  if (!map_block(blockIdx.x, a.Z * a.H, a.N, grid, zh_, nr, jg)) return;
+  if (kOwn) jg = grid.per_seg - 1 - jg;   // original order: the tiles with most own-segment keys first
+  const int n = a.N - 1 - nr, z = a.Z == 1 ? 0 : zh_ / a.H, h = zh_ - z * a.H;
+  const int g = h / (a.H / a.Hkv);
   const uint16_t* Qh = a.Q + z * a.qs[0] + h * a.qs[1];
   const uint16_t* Kh = a.K + z * a.ks[0] + g * a.ks[1];
   const uint16_t* Vh = a.V + z * a.vs[0] + g * a.vs[1];
@@ -103,7 +100,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
 
   // wavefront -> (query tile of the workgroup, 32-row part); the parts of a tile are
   // wavefronts tile, tile + tpw, ...
-  const int tile_l = wave % tpw, part = wave / tpw;
+  const int tile_l = tpw == 2 ? wave & 1 : 0, part = tpw == 2 ? wave >> 1 : wave;
   const int j = jg * tpw + tile_l;              // this wavefront's permuted query tile
   const bool active = j < TJ;
 
@@ -487,10 +484,11 @@ hipError_t launch_prefix(const AttnArgs& a, hipStream_t stream) {
   const int TJ = a.S / a.BM;
   const int tpw = kWaves / (a.BM / kRowsPerWave);
   const int JG = (TJ + tpw - 1) / tpw;
-  const int64_t blocks = (int64_t)a.Z * a.H * a.N * JG;
-  if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks), block(kThreads);
-  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, kPrefixLds, stream, a); };
+  const WalkGrid grid = walk_grid((int64_t)a.Z * a.H, a.N, JG);
+  if (grid.blocks <= 0 || grid.blocks > 0x7fffffff) return hipErrorInvalidValue;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid.blocks), dim3(kThreads), kPrefixLds, stream, a, grid);
+  };
   // A threshold of 0 or less never stops, so nothing is lost by leaving the votes out (us with /
   // without them, 32 heads: 8K 496 / 463, 32K 8018 / 7502, 128K 134462 / 124775).  The reference then
   // still moves as in the walk with votes, and the results keep its bits.  (The single launch's
