@@ -222,16 +222,20 @@ __device__ __forceinline__ void issue_v_fragment(const OperandAddr& oa, u32x2 (&
   lds_issue_tr64<kVOff + (c / 4) * kVStepBytes + 8 * kRowElems * 2>(vf[c][1], oa.vx[c % 4]);
 }
 
-// S^T = K Q^T for the K tile at byte offset kKOff from the addresses in `oa`.  kWithV: also
-// start the V^T reads of fragments 0..kVEarly-1 of the V tile at byte offset kVOff.
-template <int kKOff, int kVOff, bool kWithV>
-__device__ __forceinline__ void qk_tile_sched(const OperandAddr& oa, const bf16x8 (&qf)[8], f32x16 (&s)[2],
-                                              u32x2 (&vf)[16][2]) {
-  bf16x8 ka[8][2];
+// The K reads of the first kKAhead steps of the K tile at byte offset kKOff from the addresses in `oa`.  A caller
+// may have other work between these and qk_tile_begun, but no LDS read.
+template <int kKOff>
+__device__ __forceinline__ void qk_tile_begin(const OperandAddr& oa, bf16x8 (&ka)[8][2]) {
   static_for<0, kKAhead>([&](auto kk_) {
     constexpr int kk = decltype(kk_)::value;
     lds_issue_b128_x2<kKOff>(ka[kk][0], ka[kk][1], oa.k[kk]);
   });
+}
+// S^T = K Q^T for that tile, its first reads requested by qk_tile_begin.  kWithV: also
+// start the V^T reads of fragments 0..kVEarly-1 of the V tile at byte offset kVOff.
+template <int kKOff, int kVOff, bool kWithV>
+__device__ __forceinline__ void qk_tile_begun(const OperandAddr& oa, const bf16x8 (&qf)[8], f32x16 (&s)[2],
+                                              u32x2 (&vf)[16][2], bf16x8 (&ka)[8][2]) {
   static_for<0, 8>([&](auto kk_) {
     constexpr int kk = decltype(kk_)::value;
     lds_wait<issued_at_qk(kk, kWithV) - (2 * kk + 2)>(ka[kk][0], ka[kk][1]);
@@ -252,6 +256,13 @@ __device__ __forceinline__ void qk_tile_sched(const OperandAddr& oa, const bf16x
       issue_v_fragment<kVOff, 2 * (kk + kKAhead - 8) + 1>(oa, vf);
     }
   });
+}
+template <int kKOff, int kVOff, bool kWithV>
+__device__ __forceinline__ void qk_tile_sched(const OperandAddr& oa, const bf16x8 (&qf)[8], f32x16 (&s)[2],
+                                              u32x2 (&vf)[16][2]) {
+  bf16x8 ka[8][2];
+  qk_tile_begin<kKOff>(oa, ka);
+  qk_tile_begun<kKOff, kVOff, kWithV>(oa, qf, s, vf, ka);
 }
 // O^T accumulate step with the accumulator updated in place.  As a builtin the compiler is free
 // to give the result a tuple of its own, and for the loop-carried 64-register accumulator it

@@ -13,11 +13,20 @@
 // needed one step after K tile k, so it is also fetched one step later: step k reads K(k) and
 // V(k-1) while K(k+1) and V(k) arrive.  Two K and two V buffers (64 KB) then suffice, and with
 // 4 wavefronts of under 256 registers two workgroups share a CU.
-// A step is:   read the votes on tile k-1  ->  issue the fetches of K(k+1), V(k) and of the
-// token indices of tile k+2  ->  scores of tile k, PV of tile k-1, softmax of tile k  ->  wait
-// for the wavefront's own fetches  ->  barrier.  The fetches are issued first and waited for
-// last, so they have the whole step to land; nothing between depends on them (the indices
-// loaded in step k are first touched at the top of step k+1).
+// A step is:   read the votes on tile k-1 and the tokens of tile k+1  ->  request the first K
+// fragments  ->  issue the fetches of K(k+1), V(k) and of the token indices of tile k+2  ->  scores of
+// tile k, PV of tile k-1, then the softmax of tile k  ->  wait for the wavefront's own fetches  ->
+// barrier.  The fetches are issued first and waited for last, so they have the whole step to land;
+// nothing between depends on them (the indices loaded in step k are first touched at the top of
+// step k+1).  What bounds a step is the chip's power limit where a walk is long, and before that
+// the two wavefronts of a SIMD taking turns: one's products beside the other's softmax.
+//
+// Walk with votes, us, before / after the softmax was kept behind the PV products, votes and tokens
+// came with one LDS round trip in a loop without inner loops, and K was requested before the fetches
+// (0.97, 0.96 and 0.98 to 1.00 of the time in turn; 32 heads): 8K at 1e-3 309 / 284, 32K at 5e-3 1319 / 1267, at
+// 1e-37 8064 / 7694, 128K at 2e-2 2576 / 2519, at 5e-3 4789 / 4629, at 1e-3 12092 / 11435; 128-row tiles, 128K, half
+// of the heads unstructured 20942 / 19734; one head, 2K 23.3 / 21.7.  Operand reads 4 and 8 instead of 3 and 6
+// fragments ahead: +-0; a higher wavefront priority during the products 1.00, during the softmax 1.03.
 //
 // The wait that ends a step goes through the builtin (wait_fetches): behind a wait it cannot see,
 // the compiler guards the accumulator, loaded from the state in front of the loop, with waits of
@@ -70,7 +79,8 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];   // OperandAddr needs a 256-byte base
   uint16_t* Ks = reinterpret_cast<uint16_t*>(smem);
   uint16_t* Vt = Ks + 2 * kTileElems;
-  int* sflag = reinterpret_cast<int*>(Vt + 2 * kTileElems);   // stop votes: two sets of kWaves
+  uint8_t* vote = reinterpret_cast<uint8_t*>(Vt + 2 * kTileElems);   // stop votes: two sets of one byte per wavefront
+  int* own_tiles = reinterpret_cast<int*>(vote) + kWaves;     // kOwn: own-segment tiles per wavefront
   int32_t* ring = reinterpret_cast<int32_t*>(smem + 4 * kTileBytes + 64);   // map entries: 4 tiles x kWaves x 16
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -119,10 +129,10 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
     for (int d = 16; d > 0; d >>= 1) { lo = min(lo, __shfl_xor(lo, d)); hi = max(hi, __shfl_xor(hi, d)); }
     row_lo = __builtin_amdgcn_readfirstlane(lo);
     myn = active ? __builtin_amdgcn_readfirstlane(hi) / kBN + 1 : 0;
-    if (lane == 0) sflag[2 * kWaves + wave] = myn;
+    if (lane == 0) own_tiles[wave] = myn;
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) nloc = max(nloc, __builtin_amdgcn_readfirstlane(sflag[2 * kWaves + w]));
+    for (int w = 0; w < kWaves; ++w) nloc = max(nloc, __builtin_amdgcn_readfirstlane(own_tiles[w]));
   }
   const int nall = nloc + ntiles;               // tiles of this launch
 
@@ -187,14 +197,17 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   // tokens of tile t, which V(t) needs, are the ones the previous call worked out for K(t):
   // they stay in four registers instead of being read from the ring and clamped again.
   uint32_t tok_cur[4] = {0, 0, 0, 0};
-  auto fetch_step = [&](int t) {
-    uint32_t tn[4];
-    tokens(t + 1, tn);
+  auto fetch_step_of = [&](int t, const uint32_t (&tn)[4]) {      // tn: the tokens of tile t + 1
     if (t + 1 < nall) load_k(t + 1, tn);
     load_v(t, tok_cur);
 #pragma unroll
     for (int gi = 0; gi < 4; ++gi) tok_cur[gi] = tn[gi];
     fetch_index(t + 2);
+  };
+  auto fetch_step = [&](int t) {
+    uint32_t tn[4];
+    tokens(t + 1, tn);
+    fetch_step_of(t, tn);
   };
   if (nall > 0) {
     fetch_index(0);
@@ -244,32 +257,41 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   bf16x8 pb_pend[4];
   float alpha_pend = 1.f, l_save = 0.f, m_save = 0.f;
   bool grow_pend = false;
-  auto vote_flags = [&](int step) { return sflag + kWaves * (step & 1); };
+  auto vote_word = [&](int step) { return vote + kWaves * (step & 1); };
   auto publish = [&](int step) {        // after softmax of tile `step`: vote + speculative stats
     const bool keep = __builtin_amdgcn_ballot_w64(ts.mass >= a.tau * ts.prev) != 0ull;
-    if (lane == 0) vote_flags(step)[wave] = keep ? 1 : 0;
+    vote_word(step)[wave] = keep ? 1 : 0;
     l_save = l_run; m_save = m_ref;
     l_run = ts.prev + ts.mass; m_ref = ts.m_use;
     alpha_pend = ts.alpha; grow_pend = ts.grow;
     pack_p(s, pb_pend);
     ++issued;
   };
-  // the four wavefronts' votes of a step come with one 16-byte read; a query tile's wavefronts
-  // are tile_l, tile_l + tpw, ...
-  struct Votes { int mine, any; };
-  // (The read sits in a loop of one trip whose count the compiler cannot see.  Without an inner
-  // loop in the step, the step loop is the innermost one, the compiler hoists and schedules far
-  // more aggressively, and the walk ends up with 256 registers and spill reloads -- each behind
-  // a wait for all fetches in flight -- inside the step: 158 against 110 ms for the dense walk.)
-  const int one_trip = 1 + (a.BM >> 12);
-  auto read_votes = [&](int step) {
-    Votes v = {0, 0};
-    for (int trip = 0; trip < one_trip; ++trip) {
-      const int4 f = *reinterpret_cast<const int4*>(vote_flags(step) + 4 * trip);
-      v.any |= __builtin_amdgcn_readfirstlane(f.x | f.y | f.z | f.w);
-      v.mine |= tpw == 2 ? __builtin_amdgcn_readfirstlane(tile_l == 0 ? (f.x | f.z) : (f.y | f.w)) : v.any;
+  // The four wavefronts' votes of a step come with one 4-byte read; a query tile's wavefronts are
+  // tile_l, tile_l + tpw, ...
+  struct Votes { uint32_t mine, any; };
+  const uint32_t my_votes = tpw == 1 ? 0xffffffffu : tile_l == 0 ? 0x00ff00ffu : 0xff00ff00u;
+  auto votes_of = [&](uint32_t word) {
+    const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)word);
+    return Votes{w & my_votes, w};
+  };
+  auto read_votes = [&](int step) { return votes_of(*reinterpret_cast<const uint32_t*>(vote_word(step))); };
+  // The same together with the tokens of tile step + 2: one LDS round trip at the top of a step.
+  const uint32_t vote_lds = lds_address(vote), ring_lds = lds_address(ring) + 64 * wave + 16 * (lane >> 4);
+  auto read_votes_and_tokens = [&](int step, uint32_t (&tok)[4]) {
+    uint32_t w;
+    if constexpr (kMapped) {
+      u32x4 e;
+      asm volatile("ds_read_b32 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)"
+                   : "=&v"(w), "=&v"(e)
+                   : "v"(vote_lds + kWaves * (step & 1)), "v"(ring_lds + 64 * kWaves * ((step + 2) & 3)) : "memory");
+#pragma unroll
+      for (int gi = 0; gi < 4; ++gi) tok[gi] = clamp_token((int)e[gi], a.L - 1);
+    } else {
+      asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(w) : "v"(vote_lds + kWaves * (step & 1)) : "memory");
+      tokens(step + 2, tok);
     }
-    return v;
+    return votes_of(w);
   };
   auto end_step = [&] {                 // this wavefront's fetches have landed; everyone's after the barrier
     wait_fetches<0>();
@@ -388,52 +410,43 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
       softmax();
       publish(it);
       end_step();
-      pending = true;                           // a scored tile waits for its vote
-      // Returns false when the query tile stops at this step.
       aim_next(fa, it);
-      auto step = [&](int it_) -> bool {
-        const Votes vf = read_votes(it_ - 1);
-        const int votes = vf.mine;
-        if (votes == 0) {
-          const int any = vf.any;
-          if (a.stop_mode == 0) {
-            l_run = l_save; m_ref = m_save;
-          } else {
-            rescale(o, alpha_pend, grow_pend);
-            pv_tile_only<0>(fa, pb_pend, o);
-            ++committed;
-          }
-          pending = false;
-          wg_done = any == 0;
-          return false;
-        }
-        fetch_step(it_);
+      // One flat loop, the stop's own work behind it: with a return or the last PV product inside, the
+      // compiler hoists what the loop does not have registers for (256, and reloads behind waits for all
+      // fetches in flight; this form takes 220).
+      Votes votes = {1u, 1u};
+      for (++it; it < nall; ++it) {
+        uint32_t tn[4];
+        votes = read_votes_and_tokens(it - 1, tn);
+        if (votes.mine == 0) break;
+        bf16x8 ka[8][2];
+        qk_tile_begin<0>(fa, ka);               // on their way while the fetches are issued
+        fetch_step_of(it, tn);
         u32x2 vfr[16][2];
-        qk_tile_sched<0, 0, true>(fa, qf, s, vfr);
+        qk_tile_begun<0, 0, true>(fa, qf, s, vfr, ka);
         rescale(o, alpha_pend, grow_pend);
         pv_tile_sched<0, true>(fa, pb_pend, o, vfr);
         ++committed;
+        // Left to itself the compiler puts the softmax between the PV products.  The two wavefronts of a
+        // SIMD then get in each other's way; kept behind them, one's products run beside the other's softmax
+        // (a step of both 4150 clocks against 3300 without votes, where a branch keeps them apart).
+        __builtin_amdgcn_sched_barrier(0);
         bool redo;
         ts = softmax_tile_keep_reference<kExactReference>(s, c2, m_ref, l_run, redo);
         if (__builtin_amdgcn_ballot_w64(redo) != 0ull) again(fa);
-        publish(it_);
-        aim_next(fa, it_);
+        publish(it);
+        aim_next(fa, it);
         wait_fetches<0>();
         __syncthreads();
-        return true;
-      };
-      for (++it; it < nall; ++it)
-        if (!step(it)) break;
-      if (pending) {                            // the last tile: its vote is visible now
-        const bool stop = read_votes(nall - 1).mine == 0;
-        if (stop && a.stop_mode == 0) {
-          l_run = l_save; m_ref = m_save;
-        } else {
-          rescale(o, alpha_pend, grow_pend);
-          pv_tile_only<0>(fa, pb_pend, o);      // fa stands at step nall: V(nall-1)
-          ++committed;
-        }
-        wg_done = true;
+      }
+      if (it == nall) votes = read_votes(nall - 1);   // the last tile: its vote is visible now
+      wg_done = it == nall || votes.any == 0;
+      if (votes.mine == 0 && a.stop_mode == 0) {
+        l_run = l_save; m_ref = m_save;
+      } else {
+        rescale(o, alpha_pend, grow_pend);
+        pv_tile_only<0>(fa, pb_pend, o);        // fa stands at step it: V(it-1)
+        ++committed;
       }
     }
     // ---- drain: keep the tile pipeline fed until every query tile of the workgroup has stopped
@@ -441,7 +454,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
       for (; it < nall; ++it) {
         if (it > nloc && read_votes(it - 1).any == 0) break;
         fetch_step(it);
-        if (lane == 0) vote_flags(it)[wave] = 0;
+        vote_word(it)[wave] = 0;
         end_step();
       }
     }
