@@ -52,6 +52,7 @@ constexpr int kScoreWaves = 4;     // wavefronts (row blocks of 32) of a score w
                                    // starves beside the own-segment pass on the second stream (up to 3 ms)
 constexpr int kKStride = 136;      // bf16 elements per K row in LDS (272 B)
 constexpr int kGuideParts = 8;     // workgroups per KV head summing the first key segment
+constexpr int kBesideRows = 256;   // query rows (workgroups) that leave every CU with one at most: 256 CUs
 
 // float -> uint32 whose unsigned order is the float order (-0 canonicalised to +0)
 __device__ inline uint32_t ordered_u32(float f) {
@@ -598,9 +599,12 @@ __device__ __forceinline__ void pool_segment(const PlanArgs& a, const Scratch& s
     for (int j = 0; j < kCols; ++j) a.k_guide[((int64_t)z * a.Hkv + g) * kD + kCols * c + j] = kgv[j];
   }
 
-  // Four rows of a thread per trip, all four loads issued before the first is used (S is a multiple
-  // of 64: no tail).  With 8-byte pieces the next trip's loads are on their way during a trip.
-  constexpr bool kAhead = kLanes == 32;
+  // Four rows of a thread per trip (S is a multiple of 64: no tail).  Where a CU has one workgroup, or its
+  // workgroups are large, memory latency bounds the pass and the next trip's loads are on their way during a
+  // trip (us for the whole ranking without / with: 256 rows of 512 queries 31.1 / 29.6, of 1024 50.8 / 47.0, 128 of
+  // 1024 161 / 156, 128 of 2048 without causality 81.5 / 74.6).  One pass over Q by 256 threads has several
+  // workgroups on a CU from 257 rows on: 512 rows of 1024 90.1 / 91.6, 552 of 320 60.1 / 61.6.
+  const bool ahead = !(kMean && kSort && T == 256) || (Shape::kCap > 512 && gridDim.x <= kBesideRows);
   auto load = [&](Piece (&x)[4], int row0) {
 #pragma unroll
     for (int u = 0; u < 4; ++u)
@@ -608,11 +612,7 @@ __device__ __forceinline__ void pool_segment(const PlanArgs& a, const Scratch& s
   };
   float acc[kCols] = {};
   Piece v4[4];
-  if constexpr (kAhead) load(v4, r);
-  for (int row0 = r; row0 < a.S; row0 += 64) {
-    Piece next[4];
-    if constexpr (kAhead) load(next, min(row0, a.S - 128 + r) + 64);
-    else load(v4, row0);
+  auto trip = [&](int row0) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int row = row0 + 16 * u;
@@ -642,9 +642,21 @@ __device__ __forceinline__ void pool_segment(const PlanArgs& a, const Scratch& s
         if (a.s_q) a.s_q[row_id * a.S + row] = dot;
       }
     }
-    if constexpr (kAhead) {
+  };
+  if (ahead) {
+    load(v4, r);
+    for (int at = 64; at < a.S; at += 64) {
+      Piece next[4];
+      load(next, at + r);
+      trip(at - 64 + r);
 #pragma unroll
       for (int u = 0; u < 4; ++u) v4[u] = next[u];
+    }
+    trip(a.S - 64 + r);
+  } else {
+    for (int at = 0; at < a.S; at += 64) {
+      load(v4, at + r);
+      trip(at + r);
     }
   }
   // ---- q_mean: column sums over the wavefront's four row groups, then over the wavefronts
@@ -1401,7 +1413,7 @@ static void launch_split_sort(const PlanArgs& a, const Scratch& sc, hipStream_t 
 // rows of 256 27.0 / 22.3, 256 rows of 512 34.2 / 31.3, 128 rows of 1024 43.8 / 42.0; on the other
 // side 256 rows of 1024 50.9 / 50.9, 512 rows of 512 53.9 / 59.5, 1024 rows of 256 78.5 / 87.4, 256
 // rows of 2048 87.0 / 89.6.
-constexpr int64_t kBesideRows = 256, kBesideQueries = 1 << 17;
+constexpr int64_t kBesideQueries = 1 << 17;
 using PoolSort512 = SortShape<256, 2>;
 
 hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
