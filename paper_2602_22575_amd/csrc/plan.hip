@@ -723,15 +723,18 @@ __global__ __launch_bounds__(256) void mean_guide_kernel(PlanArgs a, Scratch sc,
 
 // ---------------------------------------------------------------------------------------
 // s_K scoring.  Workgroup = (z, g, group of kScoreWaves row blocks, chunk of sc.chunk tokens);
-// wavefront w owns row block kScoreWaves*group + w (32 rows of the contraction's N side) and keeps
+// a wavefront owns one row block of the group (32 rows of the contraction's N side) and keeps
 // its q_mean split fragments in registers for the whole chunk; the chunk's K rows pass through
-// LDS in tiles of kSub tokens shared by the wavefronts.  Row r of KV head g is (hq = r / N,
-// n = r % N) and needs tokens t < n*S.
+// LDS in tiles of kSub tokens shared by the wavefronts.  Row r of KV head g is a (query head,
+// segment n) and needs tokens t < n*S.
 //   A (32 tokens x 16 dims): K tile rows from LDS, lane (token = l%32, hh = l/32) reads dims
 //                            16*kk + 8*hh .. +8
 //   B (16 dims x 32 rows)  : q_mean split terms, lane (row = l%32, hh) holds the same dims
 //   C (32 tokens x 32 rows): register i of lane l = [token 8*(i/4) + 4*hh + i%4][row l%32],
 //                            so a lane sees one row only and its meta data are scalars
+// What bounds it: the chain of 24 matrix instructions per 32 tokens at two wavefronts per SIMD, and the
+// stores (16 bytes each; 64K tokens, 32 heads, 1024-token segments: 97 us without them, 140 with).  Stored
+// as whole lines after a turn through LDS it was 1 to 3 % faster there and 2 us slower at 8K and 16K.
 __device__ __forceinline__ void score_block(const PlanArgs& a, const Scratch& sc, int block, unsigned char* smem) {
   uint16_t* Kt = reinterpret_cast<uint16_t*>(smem);                          // [kSub][kKStride]
 
@@ -757,15 +760,26 @@ __device__ __forceinline__ void score_block(const PlanArgs& a, const Scratch& sc
   const int g = unit % a.Hkv, z = unit / a.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int m_ = lane & 31, hh = lane >> 5;
-  const int rb = kScoreWaves * rbg + wave;
+  // (shifted by the chunk: the wavefronts with the shorter rows are not always on the same SIMD)
+  const int rb = kScoreWaves * rbg + ((wave + chunk) & (kScoreWaves - 1));
 
-  auto row_limit = [&](int r) { return r < R ? (int)kv_row_len(r % a.N, a.S, a.L, a.non_causal) : 0; };
-  // longest of the rows first .. first + count - 1 (row r has segment r % N: if the run wraps it
-  // contains a last segment, else its own last row is the longest)
+  // Row r: with several groups of row blocks all heads of a segment follow one another, so that a group's
+  // rows are about equally long and the groups of short rows leave most chunks alone (all segments of a head
+  // in a row: every group has long rows, and half of its wavefronts, always on the same two SIMDs, have
+  // nothing to do beyond the middle of the sequence.  This kernel, 256 rows a KV head, 64K tokens 156 -> 140 us,
+  // 128K 294 -> 258).  A single group has every row in any order.
+  const bool by_segment = R > 32 * kScoreWaves;
+  const int inner = by_segment ? G : a.N;
+  auto head_of = [&](int r) { return by_segment ? r % inner : r / inner; };
+  auto segment_of = [&](int r) { return by_segment ? r / inner : r % inner; };
+  auto row_limit = [&](int r) { return r < R ? (int)kv_row_len(segment_of(r), a.S, a.L, a.non_causal) : 0; };
+  // longest of the rows first .. first + count - 1 (the last one's, but if a run by head wraps it
+  // contains a last segment)
   auto run_limit = [&](int first, int count) {
     const int last = min(first + count, R) - 1;
     if (first > last) return 0;
-    return (int)kv_row_len(first / a.N != last / a.N ? a.N - 1 : last % a.N, a.S, a.L, a.non_causal);
+    const int n = !by_segment && first / inner != last / inner ? a.N - 1 : segment_of(last);
+    return (int)kv_row_len(n, a.S, a.L, a.non_causal);
   };
   // token limits: of the workgroup's rows (uniform) and of this wavefront's rows
   const int lim_wg = run_limit(32 * kScoreWaves * rbg, 32 * kScoreWaves);
@@ -778,10 +792,10 @@ __device__ __forceinline__ void score_block(const PlanArgs& a, const Scratch& sc
   const int r = 32 * rb + m_;
   const int lim = row_limit(r);
   const int rr = min(r, R - 1);
-  const int64_t zh = (int64_t)z * a.H + g * G + rr / a.N;
-  const int64_t row_id = zh * a.N + rr % a.N;
+  const int64_t zh = (int64_t)z * a.H + g * G + head_of(rr);
+  const int64_t row_id = zh * a.N + segment_of(rr);
   const int64_t base = zh * kv_rows_total(a.N, a.S, a.L, a.non_causal) +
-                       kv_row_start(rr % a.N, a.S, a.L, a.non_causal);
+                       kv_row_start(segment_of(rr), a.S, a.L, a.non_causal);
   float* skdst = (a.s_k ? a.s_k : sc.sk) + base;
 
   // B fragments: 3 split terms x 8 contraction steps
