@@ -6,7 +6,8 @@
 // wavefront; it needs the key tiles 0 .. (its last row) / 64 of the segment and the causal
 // mask only where a row ends inside a tile.  One workgroup = 4 wavefronts takes two row
 // blocks in turn, one of the upper and one of the lower half of the segment; the second
-// block's first tile and query rows are fetched under the first block's last tile.  Nothing
+// block's first tile and query rows are fetched under the first block's last tile.  (With few
+// workgroups one block each: launch_local.)  Nothing
 // here depends on the query tile size or on the index maps.  With K and V double-buffered a
 // workgroup takes 64 KB of LDS and 4 wavefronts of at most 256 registers, so two workgroups
 // share a CU: their barriers are independent, and one's prologue and epilogue overlap the
@@ -31,6 +32,7 @@ using namespace tile;
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
 constexpr int kRowsPerWg = kWaves * kRowsPerWave;
 constexpr size_t kLocalLds = (size_t)(4 * kTileElems) * 2;   // K x2, V x2
+constexpr int kPairFrom = 1024;    // see launch_local
 constexpr int kStateStores = 16;   // store instructions a wavefront needs at least for its 16 KB of state
 
 // The end-of-step barrier.  Tiles reach LDS by global->LDS loads only, so the barrier needs the
@@ -38,7 +40,7 @@ constexpr int kStateStores = 16;   // store instructions a wavefront needs at le
 // consumed by its MFMAs before the wavefront gets here.
 __device__ __forceinline__ void tile_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
-__global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a) {
+__global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a, const int paired) {
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];   // OperandAddr needs a 256-byte base
   uint16_t* Ks = reinterpret_cast<uint16_t*>(smem);
   uint16_t* Vt = Ks + 2 * kTileElems;
@@ -48,7 +50,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a
   const int m_ = lane & 31, hh = lane >> 5;
   const int G = a.H / a.Hkv;
   const int JG = (a.S + kRowsPerWg - 1) / kRowsPerWg;   // row blocks of 128 per (z,h,n)
-  const int PG = (JG + 1) / 2;                          // workgroups per (z,h,n): a long and a short block each
+  const int PG = paired ? (JG + 1) / 2 : JG;            // workgroups per (z,h,n): a long and a short block each, or one block
 
   // Workgroup -> (z, KV head, segment, query head of the group, pos).  Every (z, KV head, segment)
   // is one unit of G * PG workgroups with consecutive ids on one XCD (block ids are dealt
@@ -82,7 +84,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a
   // row blocks JG-1-pos and JG/2-1-pos, the longest pair first: workgroups of different length
   // drift apart, so that the two on a CU are rarely both at a block's end (state stores, no
   // MFMA work) at once; the middle block of an odd JG stands alone
-  const int jg_of[2] = {JG - 1 - pos, JG / 2 - 1 - pos};
+  const int jg_of[2] = {JG - 1 - pos, paired ? JG / 2 - 1 - pos : -1};
   const int nblk = jg_of[1] < 0 ? 1 : 2;
 
   // ---- loader: every wavefront moves 16 rows of K and 16 rows of V per tile, 4 rows per
@@ -267,9 +269,17 @@ hipError_t launch_local(const AttnArgs& a, hipStream_t stream) {
   });
   if (se != hipSuccess) return se;
   const int JG = (a.S + kRowsPerWg - 1) / kRowsPerWg;
-  const int64_t blocks = (int64_t)a.Z * a.H * a.N * ((JG + 1) / 2);
+  // Two row blocks a workgroup where there are several rounds of workgroups (512 are in flight): what one
+  // prepares for the next then comes for free.  With less than two rounds the longest pair is the kernel's
+  // time, and a block each is shorter.  Paired / one each, us, by the number of pairs: 8 (one head, 2K)
+  // 14.0 / 9.8, 128 37.4 / 26.8, 256 38.9 / 36.7, 512 106.8 / 108.4, 367.6 / 308.6 and 59.7 / 55.3, 640 74.0 / 66.9, 768
+  // 155.9 / 134.4, 1024 102.2 / 101.6 and 172.0 / 166.7; on the other side 1536 164.4 / 165.2, 2048 209.1 / 212.5 and
+  // 138.9 / 143.9.
+  const int64_t segments = (int64_t)a.Z * a.H * a.N;
+  const int paired = segments * ((JG + 1) / 2) > kPairFrom;
+  const int64_t blocks = segments * (paired ? (JG + 1) / 2 : JG);
   if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(s2o_local_kernel, dim3((unsigned)blocks), dim3(kThreads), kLocalLds, stream, a);
+  hipLaunchKernelGGL(s2o_local_kernel, dim3((unsigned)blocks), dim3(kThreads), kLocalLds, stream, a, paired);
   return hipGetLastError();
 }
 
