@@ -298,35 +298,20 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
     __syncthreads();
   };
 
-  // A wavefront's tile whose PV product is due: K(it) sits in K buffer it & 1, V(it-1) in V buffer
-  // (it-1) & 1.  The operand addresses `fa` carry the current buffers and are moved to the other
-  // ones at the end of every step (sixteen additions, outside the sequence of reads and MFMAs), so
-  // one loop body serves both parities -- two bodies with the buffer as a constant get the
-  // accumulator different registers and pay a 32-move shuffle between them on every step.
+  // Step `it` reads K(it) in K buffer it & 1 and V(it-1), whose PV product is due, in V buffer
+  // (it-1) & 1.  The walk's loops come in pairs of steps with the buffers as constants in the reads'
+  // offsets: moving the sixteen operand addresses to the other buffers at the end of every step took
+  // 4 to 6 % of a walk without votes (8K contiguous 998 / 961 us, 32K causal 7472 / 7000, top-k at 16K 525 / 505)
+  // and 1.5 to 2 % of one with votes (32 heads, 128K at 5e-3 4601 / 4495, 32K at 1e-37 7656 / 7497).
   bool acc_loaded = false, pending = false;
   int it = 0;
-  auto aim_next = [&](OperandAddr& fa, int it_) {   // step it_ -> it_ + 1: K moves to the other buffer, V the other way
-    const uint32_t dk = (it_ & 1) ? (uint32_t)(-kTileBytes) : (uint32_t)kTileBytes;
-    fa.shift(dk, 0u - dk);
-  };
-  // The scores of a tile next to the PV product of the one before it; the products of the first
-  // tile stand alone.
-  auto products = [&](const OperandAddr& fa) {
-    if (pending) {
-      u32x2 vfr[16][2];
-      qk_tile_sched<0, 0, true>(fa, qf, s, vfr);
-      rescale(o, alpha_pend, grow_pend);
-      pv_tile_sched<0, true>(fa, pb_pend, o, vfr);
-    } else {
-      qk_tile_only<0>(fa, qf, s);
-    }
-  };
-  auto pv_pending = [&](const OperandAddr& fa) {
-    if (pending) {
-      rescale(o, alpha_pend, grow_pend);
-      pv_tile_only<0>(fa, pb_pend, o);
-      pending = false;
-    }
+  typedef std::integral_constant<int, 0> Even;
+  typedef std::integral_constant<int, 1> Odd;
+  auto k_at = [&](int it_) { return oa.at((uint32_t)((it_ & 1) * kTileBytes), 0u); };
+  auto v_at = [&](int it_) { return oa.at(0u, (uint32_t)(kVBytes0 + (it_ & 1) * kTileBytes)); };
+  auto pv_last = [&] {                          // V(it-1), alone
+    rescale(o, alpha_pend, grow_pend);
+    pv_tile_only<0>(v_at(it - 1), pb_pend, o);
   };
   auto fold = [&] {                             // a tile that is kept without a vote
     pack_p(s, pb_pend);
@@ -340,17 +325,24 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
     m_ref = ts.m_use;
     pending = true;
   };
-  // rare: the tile may move some row's reference
-  auto again = [&](const OperandAddr& fa) {
-    if (kExactReference && __builtin_amdgcn_ballot_w64(confirm_redo(s, ts.mass)) == 0ull) return;
-    qk_tile_only<0>(fa, qf, s);
-    softmax();
+  // The softmax of a step behind the first.  Left to itself the compiler puts it between the PV products.
+  // The two wavefronts of a SIMD then get in each other's way; kept behind them, one's products run beside
+  // the other's softmax (a step of both in 3300 clocks instead of 4150).
+  auto softmax_step = [&](auto par) {
+    __builtin_amdgcn_sched_barrier(0);
+    bool redo;
+    ts = softmax_tile_keep_reference<kExactReference>(s, c2, m_ref, l_run, redo);
+    if (__builtin_amdgcn_ballot_w64(redo) != 0ull &&       // rare: the tile may move some row's reference
+        !(kExactReference && __builtin_amdgcn_ballot_w64(confirm_redo(s, ts.mass)) == 0ull)) {
+      qk_tile_only<decltype(par)::value * kTileBytes>(oa, qf, s);
+      softmax();
+    }
   };
-  OperandAddr fa = oa.at((uint32_t)kKBytes0, (uint32_t)(kVBytes0 + kTileBytes));   // step 0
 
   if constexpr (kOwn) {
     // ---- the segment's own tiles (Pass-1: dense, causal mask where a row ends inside the tile).
     // A wavefront without a query tile (myn = 0) only fetches.
+    OperandAddr fa = oa.at((uint32_t)kKBytes0, (uint32_t)(kVBytes0 + kTileBytes));   // step 0
     zero_acc(o);
     acc_loaded = true;
     wait_fetches<0>();
@@ -358,19 +350,32 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
     for (; it < nloc; ++it) {
       fetch_step(it);
       if (it < myn) {
-        products(fa);
+        if (pending) {
+          u32x2 vfr[16][2];
+          qk_tile_sched<0, 0, true>(fa, qf, s, vfr);
+          rescale(o, alpha_pend, grow_pend);
+          pv_tile_sched<0, true>(fa, pb_pend, o, vfr);
+        } else {
+          qk_tile_only<0>(fa, qf, s);
+        }
         const bool masked = it * kBN + kBN - 1 > row_lo;
         ts = masked ? softmax_tile<true>(s, c2, m_ref, l_run, it * kBN, qoff, hh)
                     : softmax_tile<false>(s, c2, m_ref, l_run, it * kBN, qoff, hh);
         fold();
-      } else {
-        pv_pending(fa);                         // this wavefront's last tile, one step after its scores
+      } else if (pending) {                     // this wavefront's last tile, one step after its scores
+        rescale(o, alpha_pend, grow_pend);
+        pv_tile_only<0>(fa, pb_pend, o);
+        pending = false;
       }
-      aim_next(fa, it);
+      const uint32_t dk = (it & 1) ? (uint32_t)(-kTileBytes) : (uint32_t)kTileBytes;
+      fa.shift(dk, 0u - dk);
       wait_fetches<0>();
       __syncthreads();
     }
-    pv_pending(fa);
+    if (pending) {
+      pv_last();
+      pending = false;
+    }
   }
 
   if (kNoStop && ntiles > 0) {
@@ -380,72 +385,85 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
       wait_fetches<0>();                          // K tile 0 has landed
       __syncthreads();
     }
-    for (; it < nall; ++it) {
+    fetch_step(it);                               // first tile: scores only
+    if (active) {
+      qk_tile_only<0>(k_at(it), qf, s);
+      softmax();
+      fold();
+    }
+    wait_fetches<0>();
+    __syncthreads();
+    ++it;
+    auto step = [&](auto par) {
+      constexpr int kK = decltype(par)::value * kTileBytes, kV = kVBytes0 + kTileBytes - kK;
       fetch_step(it);
       if (active) {
-        products(fa);
-        if (!kExactReference && it == nloc) {
-          softmax();                              // (the walk with votes does so with its first tile)
-        } else {
-          bool redo;
-          ts = softmax_tile_keep_reference<kExactReference>(s, c2, m_ref, l_run, redo);
-          if (__builtin_amdgcn_ballot_w64(redo) != 0ull) again(fa);
-        }
+        u32x2 vfr[16][2];
+        qk_tile_sched<kK, kV, true>(oa, qf, s, vfr);
+        rescale(o, alpha_pend, grow_pend);
+        pv_tile_sched<kV, true>(oa, pb_pend, o, vfr);
+        softmax_step(par);
         fold();
       }
-      aim_next(fa, it);
       wait_fetches<0>();
       __syncthreads();
+      ++it;
+    };
+    if (kOwn && (it & 1) == 0 && it < nall) step(Even{});
+    while (it + 1 < nall) { step(Odd{}); step(Even{}); }
+    if (it < nall) step(Odd{});
+    if (active) {
+      pv_last();
+      committed = issued = ntiles;
     }
-    pv_pending(fa);
-    if (active) committed = issued = ntiles;
   } else if (ntiles > 0) {
     if (!kOwn) end_step();                        // K tile 0 has landed
     bool wg_done = false;
     if (active) {
       // first tile: scores only
       fetch_step(it);
-      qk_tile_only<0>(fa, qf, s);
+      qk_tile_only<0>(k_at(it), qf, s);
       if (!kOwn) { init_acc(); acc_loaded = true; }
       softmax();
       publish(it);
       end_step();
-      aim_next(fa, it);
-      // One flat loop, the stop's own work behind it: with a return or the last PV product inside, the
-      // compiler hoists what the loop does not have registers for (256, and reloads behind waits for all
-      // fetches in flight; this form takes 220).
+      ++it;
+      // One step; false: this query tile stops here.  The stop's own work stands behind the loop: with the
+      // last PV product inside, the compiler hoists what the loop does not have registers for.
       Votes votes = {1u, 1u};
-      for (++it; it < nall; ++it) {
+      auto step = [&](auto par) -> bool {
+        constexpr int kK = decltype(par)::value * kTileBytes, kV = kVBytes0 + kTileBytes - kK;
         uint32_t tn[4];
         votes = read_votes_and_tokens(it - 1, tn);
-        if (votes.mine == 0) break;
+        if (votes.mine == 0) return false;
         bf16x8 ka[8][2];
-        qk_tile_begin<0>(fa, ka);               // on their way while the fetches are issued
+        qk_tile_begin<kK>(oa, ka);              // on their way while the fetches are issued
         fetch_step_of(it, tn);
         u32x2 vfr[16][2];
-        qk_tile_begun<0, 0, true>(fa, qf, s, vfr, ka);
+        qk_tile_begun<kK, kV, true>(oa, qf, s, vfr, ka);
         rescale(o, alpha_pend, grow_pend);
-        pv_tile_sched<0, true>(fa, pb_pend, o, vfr);
+        pv_tile_sched<kV, true>(oa, pb_pend, o, vfr);
         ++committed;
-        // Left to itself the compiler puts the softmax between the PV products.  The two wavefronts of a
-        // SIMD then get in each other's way; kept behind them, one's products run beside the other's softmax
-        // (a step of both 4150 clocks against 3300 without votes, where a branch keeps them apart).
-        __builtin_amdgcn_sched_barrier(0);
-        bool redo;
-        ts = softmax_tile_keep_reference<kExactReference>(s, c2, m_ref, l_run, redo);
-        if (__builtin_amdgcn_ballot_w64(redo) != 0ull) again(fa);
+        softmax_step(par);
         publish(it);
-        aim_next(fa, it);
         wait_fetches<0>();
         __syncthreads();
+        ++it;
+        return true;
+      };
+      for (bool odd = !kOwn || (it & 1) != 0; it < nall; odd = true) {
+        if (odd) {
+          if (!step(Odd{})) break;
+          if (it >= nall) break;
+        }
+        if (!step(Even{})) break;
       }
       if (it == nall) votes = read_votes(nall - 1);   // the last tile: its vote is visible now
       wg_done = it == nall || votes.any == 0;
       if (votes.mine == 0 && a.stop_mode == 0) {
         l_run = l_save; m_ref = m_save;
       } else {
-        rescale(o, alpha_pend, grow_pend);
-        pv_tile_only<0>(fa, pb_pend, o);        // fa stands at step it: V(it-1)
+        pv_last();
         ++committed;
       }
     }
