@@ -25,7 +25,7 @@
 // Measured against the form this replaces, which scattered (key, token) pairs of all rows to
 // buckets in memory, packed the buckets into spans and sorted those (eight launches of its own,
 // Llama head shape, us for the whole ranking): 4K tokens in 512-token segments 77 -> 31, 8K in 1024
-// 110 -> 51, 32K in 2048 277 -> 179, 64K in 1024 1005 -> 752, 128K in 2048 1808 -> 1385, in 4096 1129 ->
+// 110 -> 51, 32K in 2048 277 -> 179, 64K in 1024 1005 -> 731, 128K in 2048 1808 -> 1405, in 4096 1129 ->
 // 886, and 3700 -> 1440 where far-off scores had sent the old spans to their bitonic network.
 //
 // Argsort semantics: descending score, ties by ascending index, -0 == +0.
@@ -339,7 +339,7 @@ __device__ __forceinline__ uint32_t ahead_of(uint64_t p, float s, uint32_t tok) 
 // barrier in front.  bounded: all scores are known to lie in [flo, fhi]; otherwise the range is
 // found first.
 //
-// Linear time: a monotone map of the score to 36 x kThreads fine buckets (two to five per key) by
+// Linear time: a monotone map of the score to 36 x kThreads fine buckets (two to five per key, 18 in the sort of up to 512) by
 // one counting atomic, which also ranks the key inside its bucket, a scan of the counters, and
 // every key is put at its bucket's place.  What is left is the order inside a bucket: keys that
 // share one, a quarter to a half, are listed, and a full set of lanes works on the list: each is
@@ -732,9 +732,10 @@ __global__ __launch_bounds__(256) void mean_guide_kernel(PlanArgs a, Scratch sc,
 //   B (16 dims x 32 rows)  : q_mean split terms, lane (row = l%32, hh) holds the same dims
 //   C (32 tokens x 32 rows): register i of lane l = [token 8*(i/4) + 4*hh + i%4][row l%32],
 //                            so a lane sees one row only and its meta data are scalars
-// What bounds it: the chain of 24 matrix instructions per 32 tokens at two wavefronts per SIMD, and the
-// stores (16 bytes each; 64K tokens, 32 heads, 1024-token segments: 97 us without them, 140 with).  Stored
-// as whole lines after a turn through LDS it was 1 to 3 % faster there and 2 us slower at 8K and 16K.
+// What bounds it: matrix instructions, at two wavefronts per SIMD, and stores of 16 bytes one after the other
+// (64K tokens, 32 heads, 1024-token segments: 140 us; without the stores 97, with a third of the products as
+// well 56).  Two chains of 32 tokens side by side: +-0.  Stored as whole lines after a turn through LDS: 1 to
+// 3 % faster there, 2 us slower at 8K and 16K.
 __device__ __forceinline__ void score_block(const PlanArgs& a, const Scratch& sc, int block, unsigned char* smem) {
   uint16_t* Kt = reinterpret_cast<uint16_t*>(smem);                          // [kSub][kKStride]
 

@@ -26,7 +26,8 @@
 // (0.97, 0.96 and 0.98 to 1.00 of the time in turn; 32 heads): 8K at 1e-3 309 / 284, 32K at 5e-3 1319 / 1267, at
 // 1e-37 8064 / 7694, 128K at 2e-2 2576 / 2519, at 5e-3 4789 / 4629, at 1e-3 12092 / 11435; 128-row tiles, 128K, half
 // of the heads unstructured 20942 / 19734; one head, 2K 23.3 / 21.7.  Operand reads 4 and 8 instead of 3 and 6
-// fragments ahead: +-0; a higher wavefront priority during the products 1.00, during the softmax 1.03.
+// fragments ahead: +-0; a higher wavefront priority during the products 1.00, during the softmax 1.03.  (All
+// before the steps went in pairs, below.)
 //
 // The wait that ends a step goes through the builtin (wait_fetches): behind a wait it cannot see,
 // the compiler guards the accumulator, loaded from the state in front of the loop, with waits of
@@ -41,8 +42,8 @@
 // pipeline first.  It is bound by the matrix products: a query tile in permuted order has rows
 // anywhere in the segment and needs all S/64 own tiles where one in original order stops at its
 // diagonal, which is why a caller with a state buffer gets two launches.  Single launch against two,
-// permuted order, 32 heads (time, two launches = 1): segments of 64 and 256 tokens 0.82 to 0.95, of
-// 512 0.98, of 1024 1.05, of 2048 1.04 to 1.12, of 4096 1.25, of 8192 1.48; original order 0.80 to 1.00.
+// 32 heads, 16K tokens, threshold 5e-3 (time, two launches = 1), permuted order: segments of 64 tokens 0.88, of
+// 256 0.92, of 512 0.98, of 1024 1.07, of 2048 1.25, of 4096 1.39, of 8192 1.50; original order 0.87 to 0.93.
 // Against the 8-wavefront workgroups (one per CU, operand reads placed by the compiler) it replaces:
 // permuted order 0.82 to 0.89 from 512-token segments on, original order 0.74 to 0.86; 16K tokens,
 // 32 heads, original order, threshold 5e-3, with the ranking 1028 -> 697 us.
@@ -56,7 +57,7 @@ namespace {
 using namespace tile;
 
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
-constexpr int kKBytes0 = 0, kVBytes0 = 2 * kTileBytes;             // K x2 at 0, V x2 behind them
+constexpr int kVBytes0 = 2 * kTileBytes;                           // K x2 at 0, V x2 behind them
 constexpr size_t kPrefixLds = (size_t)(4 * kTileBytes) + 64 + 4 * kWaves * 64;   // + vote flags + index ring
 
 // min(max(x, 0), hi) in one instruction (the compiler emits two: it cannot know that hi >= 0)
@@ -302,7 +303,8 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   // (it-1) & 1.  The walk's loops come in pairs of steps with the buffers as constants in the reads'
   // offsets: moving the sixteen operand addresses to the other buffers at the end of every step took
   // 4 to 6 % of a walk without votes (8K contiguous 998 / 961 us, 32K causal 7472 / 7000, top-k at 16K 525 / 505)
-  // and 1.5 to 2 % of one with votes (32 heads, 128K at 5e-3 4601 / 4495, 32K at 1e-37 7656 / 7497).
+  // and 1.5 to 2 % of one with votes (32 heads, 128K at 5e-3 4601 / 4495, 32K at 1e-37 7656 / 7497); the
+  // own-segment tiles of the single launch 1 % (32K 2406 / 2368, 16K in original order 642 / 637).
   bool acc_loaded = false, pending = false;
   int it = 0;
   typedef std::integral_constant<int, 0> Even;
@@ -342,21 +344,21 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   if constexpr (kOwn) {
     // ---- the segment's own tiles (Pass-1: dense, causal mask where a row ends inside the tile).
     // A wavefront without a query tile (myn = 0) only fetches.
-    OperandAddr fa = oa.at((uint32_t)kKBytes0, (uint32_t)(kVBytes0 + kTileBytes));   // step 0
     zero_acc(o);
     acc_loaded = true;
     wait_fetches<0>();
     __syncthreads();                            // K tile 0 has landed
-    for (; it < nloc; ++it) {
+    auto own_step = [&](auto par) {
+      constexpr int kK = decltype(par)::value * kTileBytes, kV = kVBytes0 + kTileBytes - kK;
       fetch_step(it);
       if (it < myn) {
         if (pending) {
           u32x2 vfr[16][2];
-          qk_tile_sched<0, 0, true>(fa, qf, s, vfr);
+          qk_tile_sched<kK, kV, true>(oa, qf, s, vfr);
           rescale(o, alpha_pend, grow_pend);
-          pv_tile_sched<0, true>(fa, pb_pend, o, vfr);
+          pv_tile_sched<kV, true>(oa, pb_pend, o, vfr);
         } else {
-          qk_tile_only<0>(fa, qf, s);
+          qk_tile_only<kK>(oa, qf, s);
         }
         const bool masked = it * kBN + kBN - 1 > row_lo;
         ts = masked ? softmax_tile<true>(s, c2, m_ref, l_run, it * kBN, qoff, hh)
@@ -364,14 +366,15 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
         fold();
       } else if (pending) {                     // this wavefront's last tile, one step after its scores
         rescale(o, alpha_pend, grow_pend);
-        pv_tile_only<0>(fa, pb_pend, o);
+        pv_tile_only<kV>(oa, pb_pend, o);
         pending = false;
       }
-      const uint32_t dk = (it & 1) ? (uint32_t)(-kTileBytes) : (uint32_t)kTileBytes;
-      fa.shift(dk, 0u - dk);
       wait_fetches<0>();
       __syncthreads();
-    }
+      ++it;
+    };
+    while (it + 1 < nloc) { own_step(Even{}); own_step(Odd{}); }
+    if (it < nloc) own_step(Even{});
     if (pending) {
       pv_last();
       pending = false;
@@ -521,7 +524,7 @@ hipError_t launch_prefix(const AttnArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid.blocks), dim3(kThreads), kPrefixLds, stream, a, grid);
   };
   // A threshold of 0 or less never stops, so nothing is lost by leaving the votes out (us with /
-  // without them, 32 heads: 8K 496 / 463, 32K 8018 / 7502, 128K 134462 / 124775).  The reference then
+  // without them, 32 heads: 8K 502 / 466, 32K 7416 / 7043, 128K 127186 / 116604).  The reference then
   // still moves as in the walk with votes, and the results keep its bits.  (The single launch's
   // normaliser is rounded otherwise without votes: there the votes stay.)
   const bool rule = a.stop_mode != 2, no_stop = !rule || a.tau <= 0.f;
