@@ -32,7 +32,8 @@ using namespace tile;
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
 constexpr int kRowsPerWg = kWaves * kRowsPerWave;
 constexpr size_t kLocalLds = (size_t)(4 * kTileElems) * 2;   // K x2, V x2
-constexpr int kPairFrom = 1024;    // see launch_local
+constexpr int kInFlight = 512;     // workgroups in flight: two on each of 256 CUs
+enum { kPairs, kUnitByUnit, kLongestFirst };   // what a workgroup takes, in which order: launch_local
 constexpr int kStateStores = 16;   // store instructions a wavefront needs at least for its 16 KB of state
 
 // The end-of-step barrier.  Tiles reach LDS by global->LDS loads only, so the barrier needs the
@@ -40,7 +41,7 @@ constexpr int kStateStores = 16;   // store instructions a wavefront needs at le
 // consumed by its MFMAs before the wavefront gets here.
 __device__ __forceinline__ void tile_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
-__global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a, const int paired) {
+__global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a, const int form) {
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];   // OperandAddr needs a 256-byte base
   uint16_t* Ks = reinterpret_cast<uint16_t*>(smem);
   uint16_t* Vt = Ks + 2 * kTileElems;
@@ -50,31 +51,49 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a
   const int m_ = lane & 31, hh = lane >> 5;
   const int G = a.H / a.Hkv;
   const int JG = (a.S + kRowsPerWg - 1) / kRowsPerWg;   // row blocks of 128 per (z,h,n)
+  const bool paired = form == kPairs;
   const int PG = paired ? (JG + 1) / 2 : JG;            // workgroups per (z,h,n): a long and a short block each, or one block
 
-  // Workgroup -> (z, KV head, segment, query head of the group, pos).  Every (z, KV head, segment)
-  // is one unit of G * PG workgroups with consecutive ids on one XCD (block ids are dealt
-  // round-robin to the 8 XCDs), the G query heads of the group interleaved: they read the same
-  // 2 * S rows of K and V at about the same time, so the segment is fetched from HBM once per
-  // group instead of once per query head.  All units cost the same here (no early stop), so
-  // nothing needs balancing across XCDs.
+  // Workgroup -> (z, KV head, segment, query head of the group, pos).
+  // Unit by unit: every (z, KV head, segment) is one unit of G * PG workgroups with consecutive ids on
+  // one XCD (block ids are dealt round-robin to the 8 XCDs), the G query heads of the group interleaved:
+  // they read the same 2 * S rows of K and V at about the same time, so the segment is fetched from
+  // HBM once per group instead of once per query head.  All units cost the same here (no early stop),
+  // so nothing needs balancing across XCDs.
+  // Longest first: all units' longest blocks, then their second longest and so on.  A launch of few
+  // rounds takes as long as a long block that starts late, and unit by unit an XCD gets the same few
+  // lengths again and again wherever the number of units is no multiple of 8.  The heads of a group
+  // are 8 ids apart, on one XCD.  One block each, unit by unit / longest first, us: 2 heads over one, 50
+  // segments of 1024 tokens 59.4 / 40.2, 12 over 4, 25 of 512 49.7 / 42.2, 32 over 8, 4 of 1024 50.4 / 48.0 (in
+  // pairs 56.7, 56.3, 54.9).
   int z, g, n, h, pos;
   {
-    const int per_unit = G * PG, U = a.Z * a.Hkv * a.N, b = blockIdx.x;
-    int u, within;
-    if (U % 8 == 0) {
-      const int xcd = b & 7, idx = b >> 3;
-      u = (idx / per_unit) * 8 + xcd;
-      within = idx % per_unit;
+    const int U = a.Z * a.Hkv * a.N, b = blockIdx.x;
+    int u, hq;
+    if (form != kLongestFirst) {
+      const int per_unit = G * PG;
+      int within;
+      if (U % 8 == 0) {
+        const int xcd = b & 7, idx = b >> 3;
+        u = (idx / per_unit) * 8 + xcd;
+        within = idx % per_unit;
+      } else {
+        u = b / per_unit;
+        within = b % per_unit;
+      }
+      pos = within / G;
+      hq = within % G;
     } else {
-      u = b / per_unit;
-      within = b % per_unit;
+      pos = b / (U * G);
+      const int i = b - pos * U * G, first = i / (8 * G) * 8;   // eight units at a time (the last ones: what is left)
+      const int j = i - first * G, m = min(U - first, 8);
+      hq = j / m;
+      u = first + j - hq * m;
     }
-    pos = within / G;
     n = u % a.N;
     g = (u / a.N) % a.Hkv;
     z = u / (a.N * a.Hkv);
-    h = g * G + within % G;
+    h = g * G + hq;
   }
   const uint16_t* Qh = a.Q + z * a.qs[0] + h * a.qs[1];
   const uint16_t* Kh = a.K + z * a.ks[0] + g * a.ks[1];
@@ -282,16 +301,29 @@ hipError_t launch_local(const AttnArgs& a, hipStream_t stream) {
   if (se != hipSuccess) return se;
   const int JG = (a.S + kRowsPerWg - 1) / kRowsPerWg;
   // Two row blocks a workgroup where there are several rounds of workgroups (512 are in flight): what one
-  // prepares for the next then comes for free.  With less than two rounds the longest pair is the kernel's
-  // time, and a block each is shorter.  Paired / one each, us, by the number of pairs: 8 (one head, 2K)
-  // 14.0 / 9.8, 128 37.4 / 26.8, 256 38.9 / 36.7, 512 106.8 / 108.4, 367.6 / 308.6 and 59.7 / 55.3, 640 74.0 / 66.9, 768
-  // 155.9 / 134.4, 1024 102.2 / 101.6 and 172.0 / 166.7; on the other side 1536 164.4 / 165.2, 2048 209.1 / 212.5 and
-  // 138.9 / 143.9.
-  const int64_t segments = (int64_t)a.Z * a.H * a.N;
-  const int paired = segments * ((JG + 1) / 2) > kPairFrom;
-  const int64_t blocks = segments * (paired ? (JG + 1) / 2 : JG);
+  // prepares for the next then comes for free.  With few rounds of pairs the longest pair, or a round that is
+  // hardly begun, is the kernel's time, and a block each is shorter.  With blocks of few tiles a block's own
+  // start counts as well, and a block each pays only as long as it fills places that pairs leave idle.
+  // In pairs / one block each, us, by the number of pairs (and tokens a segment):
+  //   2 blocks (256)           256 17.7 / 15.2, 384 21.5 / 22.4, 512 24.5 / 26.5, 576 34.0 / 31.1, 768 37.3 / 37.5
+  //   3 (320)                  384 21.6 / 18.8, 512 22.2 / 21.7, 768 32.0 / 30.2, 896 32.5 / 33.7, 1280 44.8 / 44.7
+  //   4 (512)                  384 30.6 / 27.1, 512 32.7 / 34.5, 768 53.6 / 49.2, 896 56.9 / 57.9, 1280 91.9 / 91.1
+  //   8 and more (1024; 2048)  512 52.2 / 47.8; 94.5 / 79.3, 1024 98.2 / 93.3; 160 / 151, 1280 135 / 126; 212 / 196,
+  //                            1536 153 / 151; 255 / 241, 2048 199 / 200; 326 / 327, 3072 294 / 296; 474 / 481
+  // One block each goes longest first, unless more than a round of short blocks keeps the XCDs evenly busy as
+  // it is: the rows of a segment are then better read together (unit by unit / longest first, 704 pairs of 320
+  // tokens 26.7 / 29.2, 576 of 512 39.3 / 40.5, 768 of 640 46.7 / 48.5; on the other side 768 of 768 61.2 / 60.3,
+  // 704 of 1024 77.6 / 69.7).
+  const int64_t units = (int64_t)a.Z * a.Hkv * a.N, segments = (int64_t)a.Z * a.H * a.N;
+  const int64_t pairs = segments * ((JG + 1) / 2), idle = (pairs + kInFlight - 1) / kInFlight * kInFlight - pairs;
+  const bool fills = JG > 4 || segments * JG <= kInFlight ||
+                     (JG > 2 ? pairs > kInFlight || 4 * idle >= pairs : 8 * idle >= 5 * pairs);
+  int form = kLongestFirst;
+  if (JG == 1 || !fills || pairs > (JG > 4 ? 3 : 2) * kInFlight) form = kPairs;
+  else if (JG < 6 && units % 8 == 0 && pairs > kInFlight) form = kUnitByUnit;
+  const int64_t blocks = segments * (form == kPairs ? (JG + 1) / 2 : JG);
   if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(s2o_local_kernel, dim3((unsigned)blocks), dim3(kThreads), kLocalLds, stream, a, paired);
+  hipLaunchKernelGGL(s2o_local_kernel, dim3((unsigned)blocks), dim3(kThreads), kLocalLds, stream, a, form);
   return hipGetLastError();
 }
 
