@@ -567,19 +567,29 @@ __device__ __forceinline__ void store_o_rows(uint16_t* head, int64_t row_stride,
 // Otherwise: runs of up to 4 of a segment's workgroups go to the XCDs in turn, shifted by 1
 // every 8 runs.  Dealt out one by one, as before, every XCD fetches every tile for itself: walk with this /
 // with runs, 4 heads, 64K tokens, 1024-token segments 2643 / 2037 us, 128K in 512 721 / 595; 12 heads, 64K in 2048
-// 2118 / 2011, 8K in 256 141 / 133; 4 heads, 128K in 2048 1225 / 1271.  Whole segments share a little more and
+// 2118 / 2011, 8K in 256 141 / 133.  Whole segments share a little more and
 // balance less (4 heads, 64K in 2048: 933 one by one, 938 in runs, 973 whole; 12 heads, 32K in 2048 591, 556, 569).
+// Few and long workgroups are the exception that is left: 4 heads, 128K in 2048 at 1e-3 1203 one by one, 1232 in runs.
+// Shorter runs where all walks are of one length (alike) and an XCD would get so many more workgroups than one
+// by one that some of its 32 CUs have another one: 5248 tokens without causality, 12 heads (492 workgroups, 41 a
+// head) 227 us in runs of 4, which give an XCD 65 for its 64 places, 152 in runs of 3, 149 one by one; 6 heads 107 in
+// runs of 4, 95 of 2, 94 one by one; 36 heads 509 in runs of 4, 441 of 3.
 // (Runs per segment and workgroups per run come from the host: a division takes 0.15 us of a walk that
 // may take 20.)
 struct WalkGrid {
   int per_seg, run, runs;
   int64_t blocks;
 };
-inline WalkGrid walk_grid(int64_t ZH, int64_t N, int per_seg) {
+inline WalkGrid walk_grid(int64_t ZH, int64_t N, int per_seg, bool alike) {
   WalkGrid g;
   g.per_seg = per_seg;
-  g.runs = (per_seg + 3) / 4;
-  g.run = (per_seg + g.runs - 1) / g.runs;
+  const int64_t one = (ZH * N * per_seg + 7) / 8;               // workgroups of an XCD, one by one
+  for (int longest = 4;; --longest) {
+    g.runs = (per_seg + longest - 1) / longest;
+    g.run = (per_seg + g.runs - 1) / g.runs;
+    const int64_t share = (ZH * N * g.runs + 7) / 8 * g.run;    // ... of the fullest XCD, in runs
+    if (longest == 1 || !alike || (share + 31) / 32 == (one + 31) / 32) break;
+  }
   g.blocks = ZH % 8 == 0 ? ZH * N * per_seg : (ZH * N * g.runs + 7) / 8 * 8 * g.run;
   return g;
 }

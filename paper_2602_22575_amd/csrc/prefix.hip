@@ -518,7 +518,7 @@ hipError_t launch_prefix(const AttnArgs& a, hipStream_t stream) {
   const int TJ = a.S / a.BM;
   const int tpw = kWaves / (a.BM / kRowsPerWave);
   const int JG = (TJ + tpw - 1) / tpw;
-  const WalkGrid grid = walk_grid((int64_t)a.Z * a.H, a.N, JG);
+  const WalkGrid grid = walk_grid((int64_t)a.Z * a.H, a.N, JG, a.non_causal || a.N == 1);
   if (grid.blocks <= 0 || grid.blocks > 0x7fffffff) return hipErrorInvalidValue;
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid.blocks), dim3(kThreads), kPrefixLds, stream, a, grid);
