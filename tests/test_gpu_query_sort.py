@@ -32,3 +32,22 @@ def test_long_segments(gpu, S, kind):
     assert np.all(np.abs(pg["q_mean"] - mean) <= room)
     kg = pg["k_guide"][0, 0].astype(np.float64)
     assert np.all(np.abs(pg["s_q"] - Q @ kg) <= (np.abs(Q) @ np.abs(kg)) * (16 * 2.0 ** -24))
+
+
+@pytest.mark.parametrize("S,L", [(64, 128), (576, 1152), (1024, 32768), (2112, 4224), (8192, 16384)])
+def test_scores_come_back_as_they_are(gpu, S, L):
+    """A query that is not a number: its score comes back as one while the sort takes it for the lowest."""
+    w = inputs.workload("llama8k", L=L, S=S, H=3, Hkv=1, seed=S)
+    Qb, Kb, _ = inputs.make_qkv(w)
+    Q = inputs.bf16_bits_to_f32(Qb)
+    bad = (0, S - 1, S // 2 + 3)
+    for i in bad:
+        Q[0, 1, S + i, 5] = np.nan
+    print(f"case: NaN queries S={S} L={L}", flush=True)
+    out = gu.s2o.s2o_plan(gu.to_dev(inputs.f32_to_bf16_bits(Q)), gu.to_dev(Kb), gu.params_for(w), want_scores=True)
+    gu.torch.cuda.synchronize()
+    sq, perm = out.s_q.cpu().numpy(), out.q_perm.cpu().numpy()
+    where = np.zeros(sq.shape, bool)
+    where[0, 1, 1, list(bad)] = True
+    assert np.array_equal(np.isnan(sq), where)
+    assert np.array_equal(perm, np.argsort(-np.where(where, -np.inf, sq), axis=-1, kind="stable"))
