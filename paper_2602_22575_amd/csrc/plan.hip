@@ -736,7 +736,9 @@ __global__ __launch_bounds__(256) void mean_guide_kernel(PlanArgs a, Scratch sc,
 //                            so a lane sees one row only and its meta data are scalars
 // What bounds it: matrix instructions, at two wavefronts per SIMD, and stores of 16 bytes one after the other
 // (64K tokens, 32 heads, 1024-token segments: 140 us; without the stores 97, with a third of the products as
-// well 56).  Two chains of 32 tokens side by side: +-0.  Stored as whole lines after a turn through LDS: 1 to
+// well 56).  And two waits that nothing needs: the compiler guards the q_mean fragments, loaded in front of the
+// loop, with a wait for the next tile's K rows before a tile's first product, and the wait that puts those rows
+// down covers the scores stored since.  Two chains of 32 tokens side by side: +-0.  Stored as whole lines after a turn through LDS: 1 to
 // 3 % faster there, 2 us slower at 8K and 16K.
 __device__ __forceinline__ void score_block(const PlanArgs& a, const Scratch& sc, int block, unsigned char* smem) {
   uint16_t* Kt = reinterpret_cast<uint16_t*>(smem);                          // [kSub][kKStride]
@@ -761,7 +763,7 @@ __device__ __forceinline__ void score_block(const PlanArgs& a, const Scratch& sc
   const int chunk = rest % nchunks;
   const int rbg = rest / nchunks;
   const int g = unit % a.Hkv, z = unit / a.Hkv;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m_ = lane & 31, hh = lane >> 5;
   // (shifted by the chunk: the wavefronts with the shorter rows are not always on the same SIMD)
   const int rb = kScoreWaves * rbg + ((wave + chunk) & (kScoreWaves - 1));
@@ -770,21 +772,22 @@ __device__ __forceinline__ void score_block(const PlanArgs& a, const Scratch& sc
   // rows are about equally long and the groups of short rows leave most chunks alone (all segments of a head
   // in a row: every group has long rows, and half of its wavefronts, always on the same two SIMDs, have
   // nothing to do beyond the middle of the sequence.  This kernel, 256 rows a KV head, 64K tokens 156 -> 140 us,
-  // 128K 294 -> 258).  A single group has every row in any order.
-  const bool by_segment = R > 32 * kScoreWaves;
-  const int inner = by_segment ? G : a.N;
-  auto head_of = [&](int r) { return by_segment ? r % inner : r / inner; };
-  auto segment_of = [&](int r) { return by_segment ? r / inner : r % inner; };
-  auto row_limit = [&](int r) { return r < R ? (int)kv_row_len(segment_of(r), a.S, a.L, a.non_causal) : 0; };
+  // 128K 294 -> 259).  A single group has every row in any order, and without causality all rows are equally
+  // long.  From 256 segments on a head has groups of its own, and by head the rows of a block are neighbours:
+  // whole ranking, by head / by segment, 4 heads over one, 129 segments of 320 144 / 138 us, 200 of 64 85 / 82, but
+  // 3 over one, 256 of 512 522 / 530, 12 over 4, 320 of 64 421 / 429; without causality 16 over one, 128 of 320 0.96.
+  const bool by_segment = R > 32 * kScoreWaves && a.N < 64 * kScoreWaves && !a.non_causal;
+  const int inner = by_segment ? G : a.N;         // row r = (r / inner, r % inner); one division a row
   // longest of the rows first .. first + count - 1 (the last one's, but if a run by head wraps it
   // contains a last segment)
   auto run_limit = [&](int first, int count) {
     const int last = min(first + count, R) - 1;
     if (first > last) return 0;
-    const int n = !by_segment && first / inner != last / inner ? a.N - 1 : segment_of(last);
+    const int u = last / inner, v = last - u * inner;
+    const int n = by_segment ? u : last - first > v ? a.N - 1 : v;
     return (int)kv_row_len(n, a.S, a.L, a.non_causal);
   };
-  // token limits: of the workgroup's rows (uniform) and of this wavefront's rows
+  // token limits: of the workgroup's rows and of this wavefront's rows
   const int lim_wg = run_limit(32 * kScoreWaves * rbg, 32 * kScoreWaves);
   const int lim_wave = run_limit(32 * rb, 32);
   const int t_begin = chunk * sc.chunk;
@@ -792,13 +795,12 @@ __device__ __forceinline__ void score_block(const PlanArgs& a, const Scratch& sc
   const int t_end = min(t_begin + sc.chunk, lim_wg);
 
   // this lane's row
-  const int r = 32 * rb + m_;
-  const int lim = row_limit(r);
-  const int rr = min(r, R - 1);
-  const int64_t zh = (int64_t)z * a.H + g * G + head_of(rr);
-  const int64_t row_id = zh * a.N + segment_of(rr);
-  const int64_t base = zh * kv_rows_total(a.N, a.S, a.L, a.non_causal) +
-                       kv_row_start(segment_of(rr), a.S, a.L, a.non_causal);
+  const int r = 32 * rb + m_, rr = min(r, R - 1);
+  const int u = rr / inner, v = rr - u * inner, n = by_segment ? u : v;
+  const int lim = r < R ? (int)kv_row_len(n, a.S, a.L, a.non_causal) : 0;
+  const int64_t zh = (int64_t)z * a.H + g * G + (by_segment ? v : u);
+  const int64_t row_id = zh * a.N + n;
+  const int64_t base = zh * kv_rows_total(a.N, a.S, a.L, a.non_causal) + kv_row_start(n, a.S, a.L, a.non_causal);
   float* skdst = (a.s_k ? a.s_k : sc.sk) + base;
 
   // B fragments: 3 split terms x 8 contraction steps

@@ -1,5 +1,6 @@
 """Scores and key order where a KV head has several groups of 128 rows: full and partly filled groups and row
-blocks, heads per KV head that divide a block of 32 rows and that do not, one group more and one less."""
+blocks, heads per KV head that divide a block of 32 rows and that do not, one group more and one less;
+rows by segment (up to 255 of them, with causality) and by head."""
 import numpy as np
 import pytest
 
@@ -10,7 +11,7 @@ import gpu_util as gu
 import parity
 
 
-@pytest.mark.parametrize("H,Hkv,N", [(4, 1, 32), (4, 1, 33), (3, 1, 50), (6, 2, 64), (1, 1, 129), (10, 2, 77)])
+@pytest.mark.parametrize("H,Hkv,N", [(4, 1, 32), (4, 1, 33), (3, 1, 50), (6, 2, 64), (1, 1, 129), (10, 2, 77), (3, 1, 255), (3, 1, 256)])
 @pytest.mark.parametrize("non_causal", [0, 1])
 def test_scores_of_several_row_groups(gpu, H, Hkv, N, non_causal):
     S, L = 64, 64 * N
