@@ -223,7 +223,10 @@ __device__ __forceinline__ void issue_v_fragment(const OperandAddr& oa, u32x2 (&
 }
 
 // The K reads of the first kKAhead steps of the K tile at byte offset kKOff from the addresses in `oa`.  A caller
-// may have other work between these and qk_tile_begun, but no LDS read.
+// may have other work between these and qk_tile_begun, but `ka` is in flight there while the compiler takes it as
+// loaded: no instruction may touch it, not even a copy or a spill.  So that work must be short and far from the
+// limit of the registers.  (LDS reads in between do no harm: they complete in order, and the waits are only
+// stricter for them.)  tests/test_asm_reads_in_flight.py looks for such instructions in the built code.
 template <int kKOff>
 __device__ __forceinline__ void qk_tile_begin(const OperandAddr& oa, bf16x8 (&ka)[8][2]) {
   static_for<0, kKAhead>([&](auto kk_) {
