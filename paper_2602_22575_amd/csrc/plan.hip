@@ -24,8 +24,8 @@
 //
 // Measured against the form this replaces, which scattered (key, token) pairs of all rows to
 // buckets in memory, packed the buckets into spans and sorted those (eight launches of its own,
-// Llama head shape, us for the whole ranking): 4K tokens in 512-token segments 77 -> 31, 8K in 1024
-// 110 -> 51, 32K in 2048 277 -> 179, 64K in 1024 1005 -> 731, 128K in 2048 1808 -> 1405, in 4096 1129 ->
+// Llama head shape, us for the whole ranking): 4K tokens in 512-token segments 77 -> 29, 8K in 1024
+// 110 -> 47, 32K in 2048 277 -> 179, 64K in 1024 1005 -> 731, 128K in 2048 1808 -> 1405, in 4096 1129 ->
 // 886, and 3700 -> 1440 where far-off scores had sent the old spans to their bitonic network.
 //
 // Argsort semantics: descending score, ties by ascending index, -0 == +0.
@@ -52,7 +52,7 @@ constexpr int kScoreWaves = 4;     // wavefronts (row blocks of 32) of a score w
                                    // starves beside the own-segment pass on the second stream (up to 3 ms)
 constexpr int kKStride = 136;      // bf16 elements per K row in LDS (272 B)
 constexpr int kGuideParts = 8;     // workgroups per KV head summing the first key segment
-constexpr int kBesideRows = 256;   // query rows (workgroups) that leave every CU with one at most: 256 CUs
+constexpr int kOneEach = 256;      // query rows (workgroups) that leave every CU with one at most: 256 CUs
 
 // float -> uint32 whose unsigned order is the float order (-0 canonicalised to +0)
 __device__ inline uint32_t ordered_u32(float f) {
@@ -604,7 +604,7 @@ __device__ __forceinline__ void pool_segment(const PlanArgs& a, const Scratch& s
   // trip (us for the whole ranking without / with: 256 rows of 512 queries 31.1 / 29.6, of 1024 50.8 / 47.0, 128 of
   // 1024 161 / 156, 128 of 2048 without causality 81.5 / 74.6).  One pass over Q by 256 threads has several
   // workgroups on a CU from 257 rows on: 512 rows of 1024 90.1 / 91.6, 552 of 320 60.1 / 61.6.
-  const bool ahead = !(kMean && kSort && T == 256) || (Shape::kCap > 512 && gridDim.x <= kBesideRows);
+  const bool ahead = !(kMean && kSort && T == 256) || (Shape::kCap > 512 && gridDim.x <= kOneEach);
   auto load = [&](Piece (&x)[4], int row0) {
 #pragma unroll
     for (int u = 0; u < 4; ++u)
@@ -1427,12 +1427,14 @@ static void launch_split_sort(const PlanArgs& a, const Scratch& sc, hipStream_t 
 
 // Small inputs: s_Q and its Argsort run beside the scores, k_guide beside q_mean -- one launch less
 // in the chain, and the query sort out of it, for a second read of Q that the caches serve.  Worth
-// it as long as the chip (256 CUs) is not full with one workgroup per query row and Q is small; us
-// for the whole ranking, sort in front / beside (32 heads over 8): 8 rows of 64 20.1 / 14.7, 256
-// rows of 256 27.0 / 22.3, 256 rows of 512 34.2 / 31.3, 128 rows of 1024 43.8 / 42.0; on the other
-// side 256 rows of 1024 50.9 / 50.9, 512 rows of 512 53.9 / 59.5, 1024 rows of 256 78.5 / 87.4, 256
-// rows of 2048 87.0 / 89.6.
-constexpr int64_t kBesideQueries = 1 << 17;
+// it as long as there is less than a round and a half of query rows on the 256 CUs and Q is small; us
+// for the whole ranking, sort in front / beside (32 heads over 8 unless said; 25 is what the calls take): 64 rows of
+// 512 28.0 / 25.7, 256 of 256 28.7 / 26.8, 256 of 512 34.2 / 29.1, 128 of 1024 40.7 / 38.2, 192 of 768 38.0 / 35.3, 256 of
+// 768 41.7 / 39.4, 320 of 512 39.9 / 34.6, of 768 56.8 / 53.9, 384 of 512 42.0 / 41.5, 256 of 1024 47.5 / 47.5 (8 heads 0.97); on
+// the other side 384 of 1024 73.2 / 74.0, 512 of 256 34.2 / 34.4, of 512 54.4 / 59.8, of 1024 90.1 / 105.8.  With 2048 queries a
+// segment the second read weighs more: 64 rows 57.0 / 56.0, but 96 59.4 / 61.0, 128 63.0 / 64.0.
+constexpr int64_t kBesideRows = 384;
+constexpr int64_t beside_queries(int S) { return S < 2048 ? 1 << 18 : 1 << 17; }
 using PoolSort512 = SortShape<256, 2>;
 
 hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
@@ -1478,7 +1480,7 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
     const int nchunks = (a.L + sc.chunk - 1) / sc.chunk;
     score_blocks = (int64_t)a.Z * a.Hkv * RBG * nchunks;
   }
-  if (a.S <= SmallSort::kCap && rows <= kBesideRows && rows * a.S <= kBesideQueries) {
+  if (a.S <= SmallSort::kCap && rows <= kBesideRows && rows * a.S <= beside_queries(a.S)) {
     hipLaunchKernelGGL(mean_guide_kernel, dim3((unsigned)(rows + guide_blocks)), block, kMeanLds, stream, a, sc, (int)rows);
     const dim3 grid((unsigned)(rows + score_blocks));
     if (a.S <= PoolSort512::kCap)

@@ -9,11 +9,13 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("L,S,H,Hkv,Z", [
-    (64, 64, 1, 1, 257),        # one segment: nothing to score
-    (576, 64, 5, 1, 6),         # an odd number of rows; 45 beside, 270 in front
-    (2560, 512, 4, 2, 13),      # the largest segment of the smaller sort
-    (1152, 576, 4, 4, 33),      # the smallest of the larger sort
-    (4096, 2048, 32, 8, 2),     # 64 rows of 2048: exactly the limit on the queries, then twice that
+    (64, 64, 1, 1, 385),        # one segment: nothing to score
+    (576, 64, 5, 1, 9),         # an odd number of rows; 45 beside, 405 in front
+    (2560, 512, 4, 2, 20),      # the largest segment of the smaller sort; 20 beside, 400 in front
+    (1152, 576, 4, 4, 49),      # the smallest of the larger sort; 8 and 392
+    (3072, 64, 8, 2, 2),        # exactly the limit on the rows, then twice that
+    (8192, 1024, 32, 8, 2),     # 256 rows of 1024: exactly the limit on the queries, then twice that
+    (4096, 2048, 32, 8, 2),     # 64 rows of 2048: the lower limit of the longest segments, then twice that
 ])
 def test_both_places_of_the_query_sort(gpu, L, S, H, Hkv, Z):
     import torch
