@@ -304,7 +304,8 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   // offsets: moving the sixteen operand addresses to the other buffers at the end of every step took
   // 4 to 6 % of a walk without votes (8K contiguous 998 / 961 us, 32K causal 7472 / 7000, top-k at 16K 525 / 505)
   // and 1.5 to 2 % of one with votes (32 heads, 128K at 5e-3 4601 / 4495, 32K at 1e-37 7656 / 7497); the
-  // own-segment tiles of the single launch 1 % (32K 2406 / 2368, 16K in original order 642 / 637).
+  // own-segment tiles of the single launch 1 % (32K 2406 / 2368, 16K in original order 642 / 637; without a stop
+  // rule, both loops, 16K in original order 2122 / 2092, 8 heads 642 / 619, 4K x 4 heads 112 / 106).
   bool acc_loaded = false, pending = false;
   int it = 0;
   typedef std::integral_constant<int, 0> Even;
@@ -329,7 +330,8 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   };
   // The softmax of a step behind the first.  Left to itself the compiler puts it between the PV products.
   // The two wavefronts of a SIMD then get in each other's way; kept behind them, one's products run beside
-  // the other's softmax (a step of both in 3300 clocks instead of 4150).
+  // the other's softmax (a step of the walk with votes took 3810 and 4550 clocks on the two, one without votes,
+  // where a branch kept them apart anyway, 3300; the barrier alone 0.97 of the walk's time).
   auto softmax_step = [&](auto par) {
     __builtin_amdgcn_sched_barrier(0);
     bool redo;
