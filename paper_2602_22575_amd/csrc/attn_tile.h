@@ -576,7 +576,8 @@ __device__ __forceinline__ void store_o_rows(uint16_t* head, int64_t row_stride,
 // Shorter runs where all walks are of one length (alike) and an XCD would get so many more workgroups than one
 // by one that some of its 32 CUs have another one: 5248 tokens without causality, 12 heads (492 workgroups, 41 a
 // head) 227 us in runs of 4, which give an XCD 65 for its 64 places, 152 in runs of 3, 149 one by one; 6 heads 107 in
-// runs of 4, 95 of 2, 94 one by one; 36 heads 509 in runs of 4, 441 of 3.
+// runs of 4, 95 of 2, 94 one by one; 36 heads 509 in runs of 4, 441 of 3; 4 heads, 11 segments of 1280 620 in runs of 4,
+// 396 of 2.
 // (Runs per segment and workgroups per run come from the host: a division takes 0.15 us of a walk that
 // may take 20.)
 struct WalkGrid {
