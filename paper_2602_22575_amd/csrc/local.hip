@@ -64,8 +64,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a
   // rounds takes as long as a long block that starts late, and unit by unit an XCD gets the same few
   // lengths again and again wherever the number of units is no multiple of 8.  The heads of a group
   // are 8 ids apart, on one XCD.  One block each, unit by unit / longest first, us: 2 heads over one, 50
-  // segments of 1024 tokens 59.4 / 40.2, 12 over 4, 25 of 512 49.7 / 42.2, 32 over 8, 4 of 1024 50.4 / 48.0 (in
-  // pairs 56.7, 56.3, 54.9).
+  // segments of 1024 tokens 59.4 / 40.2, 12 over 4, 25 of 512 49.7 / 42.2 (in pairs 56.7, 56.3).
   int z, g, n, h, pos;
   {
     const int U = a.Z * a.Hkv * a.N, b = blockIdx.x;
@@ -302,25 +301,26 @@ hipError_t launch_local(const AttnArgs& a, hipStream_t stream) {
   const int JG = (a.S + kRowsPerWg - 1) / kRowsPerWg;
   // Two row blocks a workgroup where there are several rounds of workgroups (512 are in flight): what one
   // prepares for the next then comes for free.  With few rounds of pairs the longest pair, or a round that is
-  // hardly begun, is the kernel's time, and a block each is shorter.  With blocks of few tiles a block's own
-  // start counts as well, and a block each pays only as long as it fills places that pairs leave idle.
-  // In pairs / one block each, us, by the number of pairs (and tokens a segment):
+  // hardly begun, is the kernel's time, and a block each is shorter.  With two short blocks a segment a block's
+  // own start counts as well, and a block each pays only as long as it fills places that pairs leave idle.
+  // In pairs / one block each, us, by the number of pairs (and tokens a segment), units a multiple of 8:
   //   2 blocks (256)           256 17.7 / 15.2, 384 21.5 / 22.4, 512 24.5 / 26.5, 576 34.0 / 31.1, 768 37.3 / 37.5
   //   3 (320)                  384 21.6 / 18.8, 512 22.2 / 21.7, 768 32.0 / 30.2, 896 32.5 / 33.7, 1280 44.8 / 44.7
   //   4 (512)                  384 30.6 / 27.1, 512 32.7 / 34.5, 768 53.6 / 49.2, 896 56.9 / 57.9, 1280 91.9 / 91.1
-  //   8 and more (1024; 2048)  512 52.2 / 47.8; 94.5 / 79.3, 1024 98.2 / 93.3; 160 / 151, 1280 135 / 126; 212 / 196,
-  //                            1536 153 / 151; 255 / 241, 2048 199 / 200; 326 / 327, 3072 294 / 296; 474 / 481
-  // One block each goes longest first, unless more than a round of short blocks keeps the XCDs evenly busy as
-  // it is: the rows of a segment are then better read together (unit by unit / longest first, 704 pairs of 320
-  // tokens 26.7 / 29.2, 576 of 512 39.3 / 40.5, 768 of 640 46.7 / 48.5; on the other side 768 of 768 61.2 / 60.3,
-  // 704 of 1024 77.6 / 69.7).
+  //   8 and more (1024; 2048)  512 52.2 / 50.5; 94.5 / 78.4, 1024 98.4 / 98.9; 160 / 153, 1536 153 / 156; 255 / 241,
+  //                            2048 199 / 202; 326 / 327, 3072 294 / 296; 474 / 476
+  // and not a multiple (longest first), 1024: 528 76.7 / 51.5, 1008 111.7 / 95.5; 2048: 608 154 / 97, 992 192 / 153; 8192: 1536 0.88.
+  // (512 of 512 tokens are shorter in pairs alone, but not beside the ranking: a layer of 32 heads, 4K 159 / 155 us.)
+  // One block each goes longest first where unit by unit spreads the lengths unevenly over the XCDs, or where all
+  // are in flight at once.  Elsewhere longest first is still shorter alone (512 of 1024 tokens 47.8), but beside the
+  // ranking it lets that wait for its first places: a layer of 8 heads, 16K in 1024 170 / 178 us, in 2048
+  // 189 / 203.
   const int64_t units = (int64_t)a.Z * a.Hkv * a.N, segments = (int64_t)a.Z * a.H * a.N;
   const int64_t pairs = segments * ((JG + 1) / 2), idle = (pairs + kInFlight - 1) / kInFlight * kInFlight - pairs;
-  const bool fills = JG > 4 || segments * JG <= kInFlight ||
-                     (JG > 2 ? pairs > kInFlight || 4 * idle >= pairs : 8 * idle >= 5 * pairs);
-  int form = kLongestFirst;
-  if (JG == 1 || !fills || pairs > (JG > 4 ? 3 : 2) * kInFlight) form = kPairs;
-  else if (JG < 6 && units % 8 == 0 && pairs > kInFlight) form = kUnitByUnit;
+  const bool in_flight = segments * JG <= kInFlight, even = units % 8 == 0;
+  const bool fills = JG > 2 || in_flight || 8 * idle >= 5 * pairs;
+  int form = even && !in_flight ? kUnitByUnit : kLongestFirst;
+  if (JG == 1 || !fills || pairs > (JG > 4 && !even ? 3 : 2) * kInFlight) form = kPairs;
   const int64_t blocks = segments * (form == kPairs ? (JG + 1) / 2 : JG);
   if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
   hipLaunchKernelGGL(s2o_local_kernel, dim3((unsigned)blocks), dim3(kThreads), kLocalLds, stream, a, form);

@@ -1426,15 +1426,15 @@ static void launch_split_sort(const PlanArgs& a, const Scratch& sc, hipStream_t 
 
 
 // Small inputs: s_Q and its Argsort run beside the scores, k_guide beside q_mean -- one launch less
-// in the chain, and the query sort out of it, for a second read of Q that the caches serve.  Worth
-// it as long as there is less than a round and a half of query rows on the 256 CUs and Q is small; us
-// for the whole ranking, sort in front / beside (32 heads over 8 unless said; 25 is what the calls take): 64 rows of
-// 512 28.0 / 25.7, 256 of 256 28.7 / 26.8, 256 of 512 34.2 / 29.1, 128 of 1024 40.7 / 38.2, 192 of 768 38.0 / 35.3, 256 of
-// 768 41.7 / 39.4, 320 of 512 39.9 / 34.6, of 768 56.8 / 53.9, 384 of 512 42.0 / 41.5, 256 of 1024 47.5 / 47.5 (8 heads 0.97); on
-// the other side 384 of 1024 73.2 / 74.0, 512 of 256 34.2 / 34.4, of 512 54.4 / 59.8, of 1024 90.1 / 105.8.  With 2048 queries a
-// segment the second read weighs more: 64 rows 57.0 / 56.0, but 96 59.4 / 61.0, 128 63.0 / 64.0.
+// in the chain, and the query sort out of it, for a second read of Q that the caches serve.  us for the whole
+// ranking, sort in front / beside (32 heads over 8; 25 is what the calls take): 64 rows of 512 28.0 / 25.7, 256 of 256
+// 28.7 / 26.8, 256 of 512 34.2 / 29.1, 128 of 1024 40.7 / 38.2, 320 of 64 31.1 / 26.4.  Alone it also gains a little beyond these
+// lines (192 of 768 38.0 / 35.3, 256 of 768 41.7 / 39.4, 320 of 512 39.9 / 34.6, 256 of 1024 47.5 / 47.5; 512 of 512 54.4 / 59.8), but
+// a layer runs it beside the own-segment pass, where the larger second launch and the second read weigh more.  A
+// layer's time, 32, 16, 8 and 4 heads: 320 rows of 64 0.95, 0.97, 0.97, 0.94, of 128 0.98, 0.94, 0.94, 0.95; on the other side
+// 256 of 768 1.02, 1.02, 1.01, 1.02, 256 of 896 1.02, 1.02, 1.00, 1.00, 384 of 256 0.99, 1.03, 1.03, 1.01, 320 of 512 1.01, 0.98, 1.00, 1.00.
 constexpr int64_t kBesideRows = 384;
-constexpr int64_t beside_queries(int S) { return S < 2048 ? 1 << 18 : 1 << 17; }
+constexpr int64_t beside_queries(int64_t rows) { return rows <= kOneEach ? 1 << 17 : 1 << 16; }
 using PoolSort512 = SortShape<256, 2>;
 
 hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
@@ -1480,7 +1480,7 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
     const int nchunks = (a.L + sc.chunk - 1) / sc.chunk;
     score_blocks = (int64_t)a.Z * a.Hkv * RBG * nchunks;
   }
-  if (a.S <= SmallSort::kCap && rows <= kBesideRows && rows * a.S <= beside_queries(a.S)) {
+  if (a.S <= SmallSort::kCap && rows <= kBesideRows && rows * a.S <= beside_queries(rows)) {
     hipLaunchKernelGGL(mean_guide_kernel, dim3((unsigned)(rows + guide_blocks)), block, kMeanLds, stream, a, sc, (int)rows);
     const dim3 grid((unsigned)(rows + score_blocks));
     if (a.S <= PoolSort512::kCap)

@@ -15,11 +15,14 @@ CASES = [
     (1, 12, 4, 33, 320, 0),          # longest first: 792 pairs, an odd number of blocks, 132 units
     (1, 12, 4, 32, 320, 0),          # unit by unit: 768 pairs, 128 units
     (2, 9, 3, 29, 320, 1),           # pairs: 1044, a batch, strides, 174 units
-    (1, 10, 2, 22, 512, 0),          # pairs: 440 nearly fill a round
+    (1, 10, 2, 22, 512, 0),          # longest first: 440 pairs, 44 units
+    (1, 10, 2, 24, 512, 0),          # unit by unit: 480 pairs, 48 units
     (1, 10, 5, 50, 512, 0),          # longest first: 1000 pairs, 250 units
     (3, 5, 1, 9, 1088, 1),           # longest first: 675 pairs, 9 blocks a segment, 27 units
     (1, 7, 7, 23, 1920, 0),          # longest first: 1288 pairs, 15 blocks
-    (1, 8, 2, 41, 1152, 1),          # pairs: 1640
+    (1, 8, 2, 16, 1024, 0),          # unit by unit: 512 pairs, 32 units
+    (1, 16, 4, 24, 1024, 1),         # pairs: 1536, 96 units
+    (1, 8, 2, 41, 1152, 1),          # pairs: 1640, 82 units
 ]
 
 

@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
     (2560, 512, 4, 2, 20),      # the largest segment of the smaller sort; 20 beside, 400 in front
     (1152, 576, 4, 4, 49),      # the smallest of the larger sort; 8 and 392
     (3072, 64, 8, 2, 2),        # exactly the limit on the rows, then twice that
-    (8192, 1024, 32, 8, 2),     # 256 rows of 1024: exactly the limit on the queries, then twice that
-    (4096, 2048, 32, 8, 2),     # 64 rows of 2048: the lower limit of the longest segments, then twice that
+    (1024, 256, 4, 2, 20),      # 16 rows, then 320: over the lower limit on the queries from 257 rows on
+    (4096, 2048, 32, 8, 2),     # 64 rows of 2048: exactly the limit on the queries, then twice that
 ])
 def test_both_places_of_the_query_sort(gpu, L, S, H, Hkv, Z):
     import torch
