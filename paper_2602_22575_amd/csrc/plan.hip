@@ -692,14 +692,19 @@ __device__ __forceinline__ void pool_segment(const PlanArgs& a, const Scratch& s
 #pragma unroll
   for (int e = 0; e < Shape::kPerThread; ++e) {
     const int i = tid + e * T;
-    const float score = i < a.S ? sq[i] : 0.f;
     tok[e] = (uint32_t)i;
-    f[e] = sort_score(score);
-    // (Not from the row loop: the wait for the next rows at the end of a trip would cover the trip's stores.
-    // Whole ranking, 8 heads, three segments of 6144 queries, stored there / here 154 / 133 us, 32 heads, 8 of 4096
-    // 179 / 152.)
-    if (a.s_q && i < a.S) a.s_q[row_id * a.S + i] = score;
+    f[e] = i < a.S ? sq[i] : 0.f;
   }
+  // (Not from the row loop: the wait for the next rows at the end of a trip would cover the trip's stores.
+  // Whole ranking, 8 heads, three segments of 6144 queries, stored there / here 154 / 133 us, 32 heads, 8 of 4096
+  // 179 / 152.)
+  if (a.s_q) {
+#pragma unroll
+    for (int e = 0; e < Shape::kPerThread; ++e)
+      if (tid + e * T < a.S) a.s_q[row_id * a.S + tid + e * T] = f[e];
+  }
+#pragma unroll
+  for (int e = 0; e < Shape::kPerThread; ++e) f[e] = sort_score(f[e]);
   __syncthreads();                                // the scores and partial sums have been read
   const SortLds<Shape> m(smem);
   block_sort<Shape>(m, a.S, f, tok, false, 0.f, 0.f, a.q_perm + row_id * a.S);
