@@ -2,29 +2,36 @@
 // own-segment pass, paper Alg. 2; prefix.hip: prefix walk, paper Alg. 3, and both in one launch):
 // one wavefront = 32 query rows against one 64-token key tile staged in LDS.
 //
-// MFMA formulation (v_mfma_f32_32x32x16_bf16), transposed so that a query row lives in one
-// lane pair and softmax statistics need a single cross-lane step:
+// MFMA formulation (v_mfma_f32_16x16x32_bf16), transposed so that a query row lives in four
+// lanes and the P operand of the second product comes from the first one's accumulators:
 //   S^T[n, m] = sum_d K[n, d] Q[m, d]        A = K tile rows from LDS, B = Q from registers
 //   O^T[d, m] = sum_n V^T[d, n] P^T[n, m]    A = V^T from LDS,        B = P from the S^T
 //                                            accumulators (no data movement)
-// Lane l = (m = l % 32, hh = l / 32).  A 32x32 accumulator block holds, in register i of lane
-// l, the element [row 8*(i/4) + 4*hh + i%4][column m].  The B operand of the PV product takes
-// registers 8*kk..8*kk+7 of an S^T block as its 8 contraction slots, so slot (hh, jj) is key
-// 16*kk + 8*(jj/4) + 4*hh + jj%4 of the 32-key block.
+// Lane l = (m = l % 16, g = l / 16).  A 16x16 accumulator block holds, in register i of lane
+// l, the element [row 4*g + i][column m]; a wavefront's 32 rows are two column blocks.  The B operand of
+// the PV product takes registers 0..3 of two neighbouring S^T blocks as its 8 contraction slots, so slot (g, jj)
+// is key 16*(jj/4) + 4*g + jj%4 of the 32-key step.
+//
+// Why this shape: a long walk is bound by the chip's power limit, and the 32x32x16 instruction reads and
+// writes twice the accumulators for the same products.  Bare MFMAs on N(0,1) operands at that limit: 16x16x32
+// 2000 to 2090 TFLOP/s, 32x32x16 1800 to 1860 (zero operands: 2475 both).  An operand fragment out of LDS is 1 KB and feeds two
+// instructions where it fed one: the LDS traffic is the same.  The kernels' times with this and the read order
+// below / with 32x32x16, same card: contiguous 8K x 32 heads 848 / 907 us, 32K causal without a stop rule
+// 6470 / 6940, at 5e-3 1151 / 1193, own segments of 1024 tokens at 16K 186 / 217; on zero data, where cycles count,
+// 650 / 632.
 //
 // K and V tiles sit row-major (token rows of 256 bytes) in LDS, written there directly by
 // global_load_lds (no staging registers): a wavefront instruction deposits 4 gathered rows
 // as 1 KB, lane l at byte 16*l, so rows cannot be padded; bank conflicts are avoided by an XOR
 // swizzle instead: the sixteen 16-byte chunks of row r are stored at slot chunk ^ swz(r)
 // (each lane fetches, from global memory, the chunk that belongs at its LDS slot), with
-// swz(r) = 4*(r%4) + 2*((r/4)%2) + (r/8)%2: the 16 rows a 16-byte K read touches land on 16
-// different chunks, and the 4 rows x 64 bytes that half a wavefront touches in a transposing
-// V read land on the four 16-bank groups.
-// Contraction slots (hh, jj) of a 16-key step: keys 4*hh + jj for jj < 4, 8 + 4*hh + jj - 4 behind.
+// swz(r) = 4*(r%4) + 2*((r/4)%2) + (r/8)%2: the 16 rows that 16 lanes of a K read touch land on 16
+// different chunks, and the 8 rows x 32 bytes that half a wavefront touches in a transposing
+// V read on 16 chunks as well.
 // The K operand is a plain 16-byte read of a row; the V^T operand is read with the
 // transposing LDS load ds_read_b64_tr_b16: within each group of 16 lanes, lane i receives
 // element (i % 4) of the four 8-byte rows pointed to by lanes i/4, 4 + i/4, 8 + i/4 and
-// 12 + i/4, so pointing lane r of a group at (key slot r/4, dims 4*(r%4)..+3) hands every
+// 12 + i/4, so pointing lane r of group g at (key 4*g + r/4, dims 4*(r%4)..+3) hands every
 // lane the four keys of its contraction slots at its own head dimension.
 //
 // Online softmax: logits are kept in base-2 units (raw score * softmax_scale * log2 e).
@@ -43,7 +50,6 @@ namespace s2o {
 namespace tile {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -55,6 +61,7 @@ constexpr int kBN = 64;                  // key tile
 constexpr int kRowsPerWave = 32;         // query rows of one wavefront
 constexpr int kRowElems = kD;            // K and V rows sit unpadded in LDS (256 B)
 constexpr int kTileElems = kBN * kRowElems;
+constexpr int kBlockBytes = 16 * kRowElems * 2;   // 16 rows of a tile
 constexpr float kLazy = 8.0f;
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -77,32 +84,13 @@ __device__ __forceinline__ void load_rows_to_lds(const char* lane_src, uint16_t*
   __builtin_amdgcn_global_load_lds((const gvoid*)lane_src, (lvoid*)lds_row0, 16, 0, 0);
 }
 
-// Per-lane element offsets of the MFMA operands inside a tile.
-struct Operands {
-  int koff[8];      // K operand: row 32*nb + m, chunk 2*kk + hh, for the 8 contraction steps
-  int voff[4][2];   // V^T operand: [32-dim block][8-key half of a 16-key step]
-  __device__ __forceinline__ void init(int lane) {
-    const int m_ = lane & 31, hh = lane >> 5;
+// Q fragments of a lane's two rows (16 apart in the wavefront): dims 32*kk + 8*g .. +8 for the 4 contraction steps.
+__device__ __forceinline__ void load_q(const uint16_t* qrow0, const uint16_t* qrow1, int g, bf16x8 (&qf)[4][2]) {
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) koff[kk] = m_ * kRowElems + 8 * ((2 * kk + hh) ^ swz(m_));
-    // lane (group g16 = lane/16, r = lane%16) points at key slot r/4 (+ 4 for the upper lane
-    // half), dims 16*(g16&1) + 4*(r%4); the row's swizzle depends on the lane and on which
-    // 8-key half of the 16-key step is read
-    const int rl = ((lane & 15) >> 2) + 4 * (lane >> 5);
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int a8 = 0; a8 < 2; ++a8) {
-        const int chunk = 4 * db + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-        voff[db][a8] = (rl + 8 * a8) * kRowElems + 8 * (chunk ^ swz(rl + 8 * a8)) + 4 * (lane & 1);
-      }
+  for (int kk = 0; kk < 4; ++kk) {
+    qf[kk][0] = *reinterpret_cast<const bf16x8*>(qrow0 + 32 * kk + 8 * g);
+    qf[kk][1] = *reinterpret_cast<const bf16x8*>(qrow1 + 32 * kk + 8 * g);
   }
-};
-
-// Q fragments of a lane's row: dims 16*kk + 8*hh .. +8 for the 8 contraction steps.
-__device__ __forceinline__ void load_q(const uint16_t* qrow, int hh, bf16x8 (&qf)[8]) {
-#pragma unroll
-  for (int kk = 0; kk < 8; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qrow + 16 * kk + 8 * hh);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -131,9 +119,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 __device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(lvoid*)p; }
 
 template <int kOff>
-__device__ __forceinline__ void lds_issue_b128_x2(bf16x8& d0, bf16x8& d1, uint32_t addr) {   // two reads, 32 rows apart
-  asm volatile("ds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4"
-               : "=&v"(d0), "=&v"(d1) : "v"(addr), "n"(kOff), "n"(kOff + kTileElems) : "memory");
+__device__ __forceinline__ void lds_issue_b128(bf16x8& d, uint32_t addr) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(kOff) : "memory");
 }
 template <int kOff>
 __device__ __forceinline__ void lds_issue_tr64(u32x2& d, uint32_t addr) {
@@ -160,33 +147,52 @@ __device__ __forceinline__ void wait_fetches() {
   asm volatile("" ::: "memory");
 }
 
+// acc += a * b (kFirst: acc = a * b), the first product of a fragment behind its wait.  With the builtin the
+// compiler is free to give the result registers of its own, which costs a copy of the 64-register O^T per key tile,
+// and to move products away from the reads they stand between; in assembly the operand is tied.
+// The compiler then no longer sees an MFMA and inserts no wait states around it.  In front: an
+// MFMA must not read a register in the two issue slots after a VALU instruction wrote it, and
+// the compiler does place moves of the operands right before the statement -- hence the wait and the idle
+// slot (a second product's operands have passed the first one's).  Behind: the next MFMA on the same
+// accumulator needs none; before anything else reads or writes it, mfma_settle() must have run or
+// as much other work lie between.
+template <int kYounger, bool kFirst>
+__device__ __forceinline__ void mfma_wait(f32x4& acc, const bf16x8& a, const bf16x8& b) {
+  if constexpr (kFirst)
+    asm volatile("s_waitcnt lgkmcnt(%3)\n\ts_nop 0\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b), "n"(kYounger));
+  else
+    asm volatile("s_waitcnt lgkmcnt(%3)\n\ts_nop 0\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b), "n"(kYounger));
+}
+template <bool kFirst>
+__device__ __forceinline__ void mfma_next(f32x4& acc, const bf16x8& a, const bf16x8& b) {
+  if constexpr (kFirst) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+
 // Byte addresses of a lane's operand fragments inside a tile that starts at LDS address `base`
 // (a multiple of 256).  The swizzle is an XOR on the 16-byte chunk index, i.e. on address bits
-// 4..7, so the eight K slots and the second V half follow from one address each by an XOR
-// with a constant: K step kk = k[0] ^ (kk << 5); V half 1 = (v[db] ^ 16) + 8 rows.  All sixteen
-// are kept: an XOR at the point of use sits between the read and the MFMA that waits for it
-// (12 XORs fewer per key tile for the V halves alone were worth 2 % of the walk).
+// 4..7, so the slots follow from one address each by an XOR with a constant: K step kk =
+// k[0] ^ (kk << 6), V dims block db = v[0] ^ (db << 5).  All twelve are kept: an XOR at the point of
+// use sits between the read and the MFMA that waits for it.
 struct OperandAddr {
-  uint32_t k[8];      // K operand of contraction step kk, key block 0 (block 1: + 32 rows)
-  uint32_t v[4];      // V^T operand: [32-dim block], keys 0..7 of a 16-key step (next step: + 16 rows)
-  uint32_t vx[4];     // v[db] ^ 16: keys 8..15 of the step sit 8 rows on from there (saves an XOR per read)
+  uint32_t k[4];      // K operand of contraction step kk, keys 0..15 (next 16: + kBlockBytes)
+  uint32_t v[8];      // V^T operand: [16-dim block], keys 0..15 (next 16: + kBlockBytes)
   __device__ __forceinline__ void init(int lane, uint32_t base) {
-    Operands op;
-    op.init(lane);
+    const int m_ = lane & 15, g = lane >> 4;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) k[kk] = (base + 2u * (uint32_t)op.koff[0]) ^ (uint32_t)(kk << 5);
+    for (int kk = 0; kk < 4; ++kk) k[kk] = (base + 2u * (uint32_t)(m_ * kRowElems + 8 * (g ^ swz(m_)))) ^ (uint32_t)(kk << 6);
+    // lane r of group g points at key 4*g + r/4, dims 4*(r%4)..+3
+    const int rl = 4 * g + (m_ >> 2);
 #pragma unroll
-    for (int db = 0; db < 4; ++db) {
-      v[db] = base + 2u * (uint32_t)op.voff[db][0];
-      vx[db] = v[db] ^ 16u;
-    }
+    for (int db = 0; db < 8; ++db)
+      v[db] = (base + 2u * (uint32_t)(rl * kRowElems + 8 * (((m_ & 3) >> 1) ^ swz(rl)) + 4 * (m_ & 1))) ^ (uint32_t)(db << 5);
   }
   // the same fragments in a tile kb / vb bytes further on (multiples of 256; may be "negative")
   __device__ __forceinline__ void shift(uint32_t kb, uint32_t vb) {
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) k[kk] += kb;
+    for (int kk = 0; kk < 4; ++kk) k[kk] += kb;
 #pragma unroll
-    for (int db = 0; db < 4; ++db) { v[db] += vb; vx[db] += vb; }
+    for (int db = 0; db < 8; ++db) v[db] += vb;
   }
   __device__ __forceinline__ OperandAddr at(uint32_t kb, uint32_t vb) const {
     OperandAddr r = *this;
@@ -196,176 +202,214 @@ struct OperandAddr {
 };
 
 constexpr int kTileBytes = kTileElems * 2;          // 16 KB
-constexpr int kVStepBytes = 16 * kRowElems * 2;     // one 16-key contraction step of a V tile
+constexpr int kVStepBytes = 2 * kBlockBytes;        // one 32-key contraction step of a V tile
 
-// The 16 K-fragment reads and 32 V^T-fragment reads of one step form one issue sequence
-// (K read r = 2*kk + nb, then V read 16 + 2*(4*st + db) + half), so that the first V fragments
-// are already on their way while the last score MFMAs run:
-//   the K reads of kk = 0..kKAhead-1 up front; after the MFMAs of step kk the K reads of step
-//   kk + kKAhead, or, once those are exhausted, the reads of two V fragments; the PV product
-//   starts by requesting the rest of the first kVAhead V fragments and then, after the MFMA
-//   of fragment c = 4*st + db, requests fragment c + kVAhead.
-constexpr int kKAhead = 3;     // contraction steps of K fragments in flight (2 fragments each)
-constexpr int kVAhead = 6;     // V fragments in flight (2 transposing reads each)
+// The 16 K-fragment reads and 32 V^T-fragment reads of one step form one issue sequence (K
+// fragments in pairs p = 2*kk + (32-key half), then V fragments c = 8*st + db of two reads each), so that the
+// first V fragments are already on their way while the last score MFMAs run:
+//   the K reads of the pairs 0..kKAhead-1 up front; after the MFMAs of pair p the K reads of pair
+//   p + kKAhead, or, once those are exhausted, the reads of two V fragments; the PV product
+//   starts by requesting the rest of the first kVAhead V fragments and then, after the MFMAs
+//   of fragment c, requests fragment c + kVAhead.
+// A fragment feeds two MFMAs of 16 clocks, and a wavefront waits with its second until the first has gone into
+// the pipe: a read stands behind each of them, not two behind both (contiguous 8K x 32 heads 0.98 of the time, on
+// zero data 0.95).  3 and 6 or 4 and 8 ahead: 1.00 to 1.02 of the time.
+// While its products run, a wavefront has priority over the other one of its SIMD, which is in its softmax or
+// at a barrier then: walk at 1e-3, 32K, 0.98 of the time, own-segment pass 0.97; without a stop rule 1.00.  (The other way round
+// 0.98, 0.99, 1.01.)
+constexpr int kKAhead = 2;     // pairs of K fragments in flight
+constexpr int kVAhead = 4;     // V fragments in flight (2 transposing reads each)
 constexpr int kVEarly = 2 * kKAhead;   // V fragments requested during the score MFMAs
+constexpr int kProductPriority = 1;
 
-// LDS reads issued before the score MFMAs of step kk wait for their fragments
-constexpr int issued_at_qk(int kk, bool with_v) {
-  const int k_reads = 2 * (kk + kKAhead < 8 ? kk + kKAhead : 8);
-  const int v_frags = with_v && kk + kKAhead > 8 ? 2 * (kk + kKAhead - 8) : 0;
+// LDS reads issued before the score MFMAs of pair p wait for their fragments
+constexpr int issued_at_qk(int p, bool with_v) {
+  const int k_reads = 2 * (p + kKAhead < 8 ? p + kKAhead : 8);
+  const int v_frags = with_v && p + kKAhead > 8 ? 2 * (p + kKAhead - 8) : 0;
   return k_reads + 2 * v_frags;
 }
 
+template <int kKOff, int p, int e>
+__device__ __forceinline__ void issue_k_fragment(const OperandAddr& oa, bf16x8 (&ka)[8][2]) {
+  lds_issue_b128<kKOff + (2 * (p & 1) + e) * kBlockBytes>(ka[p][e], oa.k[p >> 1]);
+}
+template <int kKOff, int p>
+__device__ __forceinline__ void issue_k_pair(const OperandAddr& oa, bf16x8 (&ka)[8][2]) {
+  issue_k_fragment<kKOff, p, 0>(oa, ka);
+  issue_k_fragment<kKOff, p, 1>(oa, ka);
+}
+template <int kVOff, int c, int e>
+__device__ __forceinline__ void issue_v_half(const OperandAddr& oa, u32x2 (&vf)[16][2]) {
+  lds_issue_tr64<kVOff + (c >> 3) * kVStepBytes + e * kBlockBytes>(vf[c][e], oa.v[c & 7]);
+}
 template <int kVOff, int c>
 __device__ __forceinline__ void issue_v_fragment(const OperandAddr& oa, u32x2 (&vf)[16][2]) {
-  lds_issue_tr64<kVOff + (c / 4) * kVStepBytes>(vf[c][0], oa.v[c % 4]);
-  lds_issue_tr64<kVOff + (c / 4) * kVStepBytes + 8 * kRowElems * 2>(vf[c][1], oa.vx[c % 4]);
+  issue_v_half<kVOff, c, 0>(oa, vf);
+  issue_v_half<kVOff, c, 1>(oa, vf);
 }
 
-// The K reads of the first kKAhead steps of the K tile at byte offset kKOff from the addresses in `oa`.  A caller
+// The K reads of the first kKAhead pairs of the K tile at byte offset kKOff from the addresses in `oa`.  A caller
 // may have other work between these and qk_tile_begun, but `ka` is in flight there while the compiler takes it as
 // loaded: no instruction may touch it, not even a copy or a spill.  So that work must be short and far from the
 // limit of the registers.  (LDS reads in between do no harm: they complete in order, and the waits are only
 // stricter for them.)  tests/test_asm_reads_in_flight.py looks for such instructions in the built code.
 template <int kKOff>
 __device__ __forceinline__ void qk_tile_begin(const OperandAddr& oa, bf16x8 (&ka)[8][2]) {
-  static_for<0, kKAhead>([&](auto kk_) {
-    constexpr int kk = decltype(kk_)::value;
-    lds_issue_b128_x2<kKOff>(ka[kk][0], ka[kk][1], oa.k[kk]);
-  });
+  static_for<0, kKAhead>([&](auto p_) { issue_k_pair<kKOff, decltype(p_)::value>(oa, ka); });
 }
 // S^T = K Q^T for that tile, its first reads requested by qk_tile_begin.  kWithV: also
 // start the V^T reads of fragments 0..kVEarly-1 of the V tile at byte offset kVOff.
 template <int kKOff, int kVOff, bool kWithV>
-__device__ __forceinline__ void qk_tile_begun(const OperandAddr& oa, const bf16x8 (&qf)[8], f32x16 (&s)[2],
+__device__ __forceinline__ void qk_tile_begun(const OperandAddr& oa, const bf16x8 (&qf)[4][2], f32x4 (&s)[4][2],
                                               u32x2 (&vf)[16][2], bf16x8 (&ka)[8][2]) {
-  static_for<0, 8>([&](auto kk_) {
-    constexpr int kk = decltype(kk_)::value;
-    lds_wait<issued_at_qk(kk, kWithV) - (2 * kk + 2)>(ka[kk][0], ka[kk][1]);
-    if constexpr (kk == 0) {
-      f32x16 z;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) z[i] = 0.f;
-      s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk][0], qf[kk], z, 0, 0, 0);
-      s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk][1], qf[kk], z, 0, 0, 0);
-    } else {
-      s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk][0], qf[kk], s[0], 0, 0, 0);
-      s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk][1], qf[kk], s[1], 0, 0, 0);
-    }
-    if constexpr (kk + kKAhead < 8) {
-      lds_issue_b128_x2<kKOff>(ka[kk + kKAhead][0], ka[kk + kKAhead][1], oa.k[kk + kKAhead]);
-    } else if constexpr (kWithV) {
-      issue_v_fragment<kVOff, 2 * (kk + kKAhead - 8)>(oa, vf);
-      issue_v_fragment<kVOff, 2 * (kk + kKAhead - 8) + 1>(oa, vf);
-    }
+  __builtin_amdgcn_s_setprio(kProductPriority);
+  static_for<0, 8>([&](auto p_) {
+    constexpr int p = decltype(p_)::value, kk = p >> 1, kb = 2 * (p & 1);
+    constexpr int kYounger = issued_at_qk(p, kWithV) - (2 * p + 2);
+    // (one read, or two of a V fragment, behind the first and behind the third product)
+    auto issue = [&](auto e_) {
+      constexpr int e = decltype(e_)::value;
+      if constexpr (p + kKAhead < 8) issue_k_fragment<kKOff, p + kKAhead, e>(oa, ka);
+      else if constexpr (kWithV) issue_v_fragment<kVOff, 2 * (p + kKAhead - 8) + e>(oa, vf);
+    };
+    mfma_wait<kYounger, kk == 0>(s[kb][0], ka[p][0], qf[kk][0]);
+    issue(std::integral_constant<int, 0>{});
+    mfma_next<kk == 0>(s[kb][1], ka[p][0], qf[kk][1]);
+    mfma_next<kk == 0>(s[kb + 1][0], ka[p][1], qf[kk][0]);
+    issue(std::integral_constant<int, 1>{});
+    mfma_next<kk == 0>(s[kb + 1][1], ka[p][1], qf[kk][1]);
   });
+  if constexpr (!kWithV) {
+    __builtin_amdgcn_s_setprio(0);
+    asm volatile("s_nop 15\n\ts_nop 3"
+                 : "+v"(s[0][0]), "+v"(s[0][1]), "+v"(s[1][0]), "+v"(s[1][1]), "+v"(s[2][0]), "+v"(s[2][1]), "+v"(s[3][0]), "+v"(s[3][1]));
+  }
 }
 template <int kKOff, int kVOff, bool kWithV>
-__device__ __forceinline__ void qk_tile_sched(const OperandAddr& oa, const bf16x8 (&qf)[8], f32x16 (&s)[2],
+__device__ __forceinline__ void qk_tile_sched(const OperandAddr& oa, const bf16x8 (&qf)[4][2], f32x4 (&s)[4][2],
                                               u32x2 (&vf)[16][2]) {
   bf16x8 ka[8][2];
   qk_tile_begin<kKOff>(oa, ka);
   qk_tile_begun<kKOff, kVOff, kWithV>(oa, qf, s, vf, ka);
 }
-// O^T accumulate step with the accumulator updated in place.  As a builtin the compiler is free
-// to give the result a tuple of its own, and for the loop-carried 64-register accumulator it
-// does: a copy of O^T (32 two-register moves) per key tile.  In assembly the operand is tied.
-// The compiler then no longer sees an MFMA and inserts no wait states around it.  In front: an
-// MFMA must not read a register in the two issue slots after a VALU instruction wrote it, and
-// the compiler does place moves of the operands right before the statement -- hence the two
-// idle slots.  Behind: the next MFMA on the same accumulator needs none; before anything else
-// reads or writes the accumulator, mfma_settle() must have run.
-__device__ __forceinline__ void mfma_acc(f32x16& acc, const bf16x8& a, const bf16x8& b) {
-  asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void mfma_settle(f32x16 (&o)[4]) {
-  asm volatile("s_nop 15\n\ts_nop 3" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]));
+// The results of all products are in their registers.
+__device__ __forceinline__ void mfma_settle(f32x4 (&o)[2][8]) {
+  asm volatile("s_nop 15\n\ts_nop 3"
+               : "+v"(o[0][0]), "+v"(o[0][1]), "+v"(o[0][2]), "+v"(o[0][3]), "+v"(o[0][4]), "+v"(o[0][5]), "+v"(o[0][6]),
+                 "+v"(o[0][7]), "+v"(o[1][0]), "+v"(o[1][1]), "+v"(o[1][2]), "+v"(o[1][3]), "+v"(o[1][4]), "+v"(o[1][5]),
+                 "+v"(o[1][6]), "+v"(o[1][7]));
 }
 
-// O^T += V^T P^T.  kEarly: fragments 0..kVEarly-1 were requested by qk_tile_sched.
+// O^T += V^T P^T.  kEarly: fragments 0..kVEarly-1 were requested by qk_tile_sched; the softmax of the step then
+// stands between these products and whatever touches O^T next.
 template <int kVOff, bool kEarly>
-__device__ __forceinline__ void pv_tile_sched(const OperandAddr& oa, const bf16x8 (&pb)[4], f32x16 (&o)[4],
+__device__ __forceinline__ void pv_tile_sched(const OperandAddr& oa, const bf16x8 (&pb)[2][2], f32x4 (&o)[2][8],
                                               u32x2 (&vf)[16][2]) {
+  if constexpr (!kEarly) __builtin_amdgcn_s_setprio(kProductPriority);
   static_for<(kEarly ? kVEarly : 0), kVAhead>([&](auto c_) { issue_v_fragment<kVOff, decltype(c_)::value>(oa, vf); });
   static_for<0, 16>([&](auto c_) {
-    constexpr int c = decltype(c_)::value, st = c / 4, db = c % 4;
+    constexpr int c = decltype(c_)::value, st = c >> 3, db = c & 7;
     // V reads issued so far: fragments 0..kVAhead-1 and fragment c' + kVAhead after every earlier c'
     constexpr int frags = (c + kVAhead < 16 ? c + kVAhead : 16);
-    lds_wait<2 * frags - (2 * c + 2)>(vf[c][0], vf[c][1]);
     const u32x4 w = {vf[c][0].x, vf[c][0].y, vf[c][1].x, vf[c][1].y};
-    mfma_acc(o[db], __builtin_bit_cast(bf16x8, w), pb[st]);
-    if constexpr (c + kVAhead < 16) issue_v_fragment<kVOff, c + kVAhead>(oa, vf);
+    const bf16x8 vfrag = __builtin_bit_cast(bf16x8, w);
+    mfma_wait<2 * frags - (2 * c + 2), false>(o[0][db], vfrag, pb[st][0]);
+    if constexpr (c + kVAhead < 16) issue_v_half<kVOff, c + kVAhead, 0>(oa, vf);
+    mfma_next<false>(o[1][db], vfrag, pb[st][1]);
+    if constexpr (c + kVAhead < 16) issue_v_half<kVOff, c + kVAhead, 1>(oa, vf);
   });
-  mfma_settle(o);
+  __builtin_amdgcn_s_setprio(0);
+  if constexpr (!kEarly) mfma_settle(o);
 }
 
 // The same two products alone, for a step with one of them.
 template <int kKOff>
-__device__ __forceinline__ void qk_tile_only(const OperandAddr& oa, const bf16x8 (&qf)[8], f32x16 (&s)[2]) {
+__device__ __forceinline__ void qk_tile_only(const OperandAddr& oa, const bf16x8 (&qf)[4][2], f32x4 (&s)[4][2]) {
   u32x2 none[16][2];
   qk_tile_sched<kKOff, 0, false>(oa, qf, s, none);
 }
 template <int kVOff>
-__device__ __forceinline__ void pv_tile_only(const OperandAddr& oa, const bf16x8 (&pb)[4], f32x16 (&o)[4]) {
+__device__ __forceinline__ void pv_tile_only(const OperandAddr& oa, const bf16x8 (&pb)[2][2], f32x4 (&o)[2][8]) {
   u32x2 vf[16][2];
   pv_tile_sched<kVOff, false>(oa, pb, o, vf);
 }
 
-// Value of the lane 32 away, combined with the lane's own (the two halves of a query row's
-// statistics): v_permlane32_swap exchanges the upper half of one register with the lower half
-// of another, so two copies of x come back as (x of lanes 0..31, x of lanes 32..63) in every
-// lane -- no LDS round trip as with a bpermute.
-__device__ __forceinline__ float xhalf_max(float x) {
-  const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+// A query row lives in the four lanes l % 16 + 16*{0..3}, which hold its values in pairs of rows 16
+// apart.  Row statistics are kept by *home* lanes instead: lane l has those of the wavefront's row
+// l % 16 + 16 * (l / 32) (two lanes each).  v_permlane32_swap exchanges the upper half of one register with
+// the lower half of another: of (x0, x1), the values of the two rows, it makes the two that a home
+// lane has to combine first; of (x, x) the home values of both rows in every lane.
+// v_permlane16_swap does the same to the odd and even groups of 16 lanes.
+__device__ __forceinline__ int home_row(int lane) { return (lane & 15) + 16 * (lane >> 5); }
+__device__ __forceinline__ float row_max(float x0, float x1) {
+  const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
+  const float x = fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+  const u32x2 q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(q.x), __uint_as_float(q.y));
 }
-__device__ __forceinline__ float xhalf_sum(float x) {
-  const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r.x) + __uint_as_float(r.y);
+__device__ __forceinline__ float row_sum(float x0, float x1) {
+  const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
+  const float x = __uint_as_float(r.x) + __uint_as_float(r.y);
+  const u32x2 q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(q.x) + __uint_as_float(q.y);
+}
+__device__ __forceinline__ void both_rows(int x, int (&r)[2]) {
+  const u32x2 p = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+  r[0] = (int)p.x; r[1] = (int)p.y;
+}
+__device__ __forceinline__ void both_rows(float x, float (&r)[2]) {
+  const u32x2 p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  r[0] = __uint_as_float(p.x); r[1] = __uint_as_float(p.y);
 }
 
-// What a tile's score step hands to its PV step and to the row statistics.
+// What a tile's score step hands to its PV step and to the row statistics.  All of the lane's home row, but
+// the reference, which every lane needs for both of its rows.
 struct TileStats {
-  float alpha;   // factor that moves the old terms to the reference used for this tile (1 if unchanged)
-  float mass;    // the tile's softmax mass for this lane's row, in that reference
-  float prev;    // the row's mass so far, in that reference
-  float m_use;   // the reference maximum used for this tile
-  bool grow;     // the reference moved: the accumulator needs alpha
+  float alpha;     // factor that moves the old terms to the reference used for this tile (1 if unchanged)
+  float mass;      // the tile's softmax mass, in that reference
+  float prev;      // the row's mass so far, in that reference
+  float m_use[2];  // the reference maximum used for this tile
+  bool grow;       // the reference moved: the accumulator needs alpha
 };
 
 // Softmax numerators of a tile (left in s) and the row statistics.  kMask: apply the causal
-// mask, the tile starting at key position key0 of the segment and the lane's row being qoff.
+// mask, the tile starting at key position key0 of the segment and the lane's home row being qoff.
 template <bool kMask>
-__device__ __forceinline__ TileStats softmax_tile(f32x16 (&s)[2], float c2, float m_ref, float l_run, int key0,
-                                                  int qoff, int hh) {
-  float mx = -INFINITY;
+__device__ __forceinline__ TileStats softmax_tile(f32x4 (&s)[4][2], float c2, const float (&m_ref)[2], float l_run, int key0,
+                                                  int qoff, int lane) {
+  int q[2] = {0, 0};
+  if (kMask) both_rows(qoff, q);
+  float mx[2] = {-INFINITY, -INFINITY};
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
+  for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      if (kMask) {
-        const int kpos = key0 + 32 * nb + 8 * (i >> 2) + 4 * hh + (i & 3);
-        if (kpos > qoff) s[nb][i] = -INFINITY;     // CausalMask
+    for (int i = 0; i < 4; ++i) {
+      const int kpos = key0 + 16 * kb + 4 * (lane >> 4) + i;
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) {
+        if (kMask && kpos > q[cb]) s[kb][cb][i] = -INFINITY;     // CausalMask
+        mx[cb] = fmaxf(mx[cb], s[kb][cb][i]);
       }
-      mx = fmaxf(mx, s[nb][i]);
     }
-  mx = xhalf_max(mx) * c2;
+  const float top = row_max(mx[0], mx[1]) * c2;
+  const float m_old = lane < 32 ? m_ref[0] : m_ref[1];
   TileStats t;
-  t.grow = mx > m_ref + kLazy;
-  t.m_use = t.grow ? mx : m_ref;
-  float sum = 0.f;
-  const float neg = -t.m_use;
+  t.grow = top > m_old + kLazy;
+  const float m_new = t.grow ? top : m_old;
+  both_rows(m_new, t.m_use);
+  float sum[2] = {0.f, 0.f};
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
+  for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float pe = __builtin_amdgcn_exp2f(fmaf(s[nb][i], c2, neg));
-      s[nb][i] = pe;
-      sum += pe;
-    }
-  sum = xhalf_sum(sum);
-  t.mass = sum;
-  t.alpha = t.grow ? __builtin_amdgcn_exp2f(m_ref - t.m_use) : 1.0f;
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float pe = __builtin_amdgcn_exp2f(fmaf(s[kb][cb][i], c2, -t.m_use[cb]));
+        s[kb][cb][i] = pe;
+        sum[cb] += pe;
+      }
+  t.mass = row_sum(sum[0], sum[1]);
+  t.alpha = t.grow ? __builtin_amdgcn_exp2f(m_old - m_new) : 1.0f;
   t.prev = l_run * t.alpha;
   return t;
 }
@@ -389,108 +433,118 @@ __device__ __forceinline__ TileStats softmax_tile(f32x16 (&s)[2], float c2, floa
 constexpr float kMassLimit = 65536.0f, kSameMass = 128.0f;
 constexpr float kSameMax = 240.0f;       // 2^kLazy less the rounding of logits up to 2^16
 static_assert(kLazy == 8.0f && 64.0f * kSameMax < kMassLimit, "kSameMax lies just below 2^kLazy");
-__device__ __forceinline__ bool confirm_redo(const f32x16 (&s)[2], float mass) {
+__device__ __forceinline__ bool confirm_redo(const f32x4 (&s)[4][2], float mass) {
   float mx = 0.f;
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
+  for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[nb][i]);
-  return !(xhalf_max(mx) <= kSameMax && mass <= kMassLimit);    // (NaN: confirmed)
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[kb][cb][i]);
+  return !(mx <= kSameMax && mass <= kMassLimit);    // of any lane that holds a part of the row (NaN: confirmed)
 }
 template <bool kExactReference>
-__device__ __forceinline__ TileStats softmax_tile_keep_reference(f32x16 (&s)[2], float c2, float m_ref, float l_run,
-                                                                 bool& redo) {
+__device__ __forceinline__ TileStats softmax_tile_keep_reference(f32x4 (&s)[4][2], float c2, const float (&m_ref)[2],
+                                                                 float l_run, bool& redo) {
   TileStats t;
   t.grow = false;
-  t.m_use = m_ref;
+  t.m_use[0] = m_ref[0]; t.m_use[1] = m_ref[1];
   t.alpha = 1.0f;
   t.prev = l_run;
-  const float neg = -m_ref;
-  float sum = 0.f;
+  float sum[2] = {0.f, 0.f};
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
+  for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float pe = __builtin_amdgcn_exp2f(fmaf(s[nb][i], c2, neg));
-      s[nb][i] = pe;
-      sum += pe;
-    }
-  t.mass = xhalf_sum(sum);
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float pe = __builtin_amdgcn_exp2f(fmaf(s[kb][cb][i], c2, -m_ref[cb]));
+        s[kb][cb][i] = pe;
+        sum[cb] += pe;
+      }
+  t.mass = row_sum(sum[0], sum[1]);
   redo = !(t.mass <= (kExactReference ? kSameMass : kMassLimit));
   return t;
 }
 
-// P^T fragments (bf16) for the four 16-key contraction steps
-__device__ __forceinline__ void pack_p(const f32x16 (&s)[2], bf16x8 (&pb)[4]) {
+// P^T fragments (bf16) of both rows for the two 32-key contraction steps
+__device__ __forceinline__ void pack_p(const f32x4 (&s)[4][2], bf16x8 (&pb)[2][2]) {
 #pragma unroll
-  for (int st = 0; st < 4; ++st) {
-    const int nb = st >> 1, k2 = st & 1;
-    u32x4 w;
+  for (int st = 0; st < 2; ++st)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) w[q] = pack_bf16x2(s[nb][8 * k2 + 2 * q], s[nb][8 * k2 + 2 * q + 1]);
-    pb[st] = __builtin_bit_cast(bf16x8, w);
-  }
+    for (int cb = 0; cb < 2; ++cb) {
+      u32x4 w;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) w[q] = pack_bf16x2(s[2 * st + (q >> 1)][cb][2 * (q & 1)], s[2 * st + (q >> 1)][cb][2 * (q & 1) + 1]);
+      pb[st][cb] = __builtin_bit_cast(bf16x8, w);
+    }
 }
 
 // rare: move the accumulator to a new reference maximum (O^T *= alpha)
-__device__ __forceinline__ void rescale(f32x16 (&o)[4], float al, bool gr) {
+__device__ __forceinline__ void rescale(f32x4 (&o)[2][8], float al, bool gr) {
   if (__builtin_amdgcn_ballot_w64(gr) != 0ull) {
+    mfma_settle(o);
+    float alpha[2];
+    both_rows(al, alpha);
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        // in place: as plain C++ the products get registers of their own and the common path
-        // (no rescale) pays for the merge with a copy of the whole accumulator per key tile
-        float x = o[db][i];
-        asm volatile("v_mul_f32 %0, %1, %0" : "+v"(x) : "v"(al));
-        o[db][i] = x;
-      }
+      for (int db = 0; db < 8; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          // in place: as plain C++ the products get registers of their own and the common path
+          // (no rescale) pays for the merge with a copy of the whole accumulator per key tile
+          float x = o[cb][db][i];
+          asm volatile("v_mul_f32 %0, %1, %0" : "+v"(x) : "v"(alpha[cb]));
+          o[cb][db][i] = x;
+        }
   }
 }
 
-__device__ __forceinline__ void zero_acc(f32x16 (&o)[4]) {
+__device__ __forceinline__ void zero_acc(f32x4 (&o)[2][8]) {
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+  for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
+    for (int db = 0; db < 8; ++db)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[cb][db][i] = 0.f;
 }
 
-// State buffers: a row's accumulator is kept as 128 fp32 = four 128-byte lines, one per 32-dim
-// block db: the 16 values of the lane with hh = 0 in register order, then those of hh = 1
-// (`sp` in load_acc = row base + 16*hh).
+// State buffers: a row's accumulator is kept as 128 fp32 in the order of the head's dims = four 128-byte lines.
 //
 // lines_from_acc regroups the accumulators of a wavefront's 32 consecutive rows through two
-// wavefront-private 4 KB LDS areas: afterwards lane L holds in o[db][4k .. 4k+3] the 16-byte
-// piece L % 8 of line db of row 8k + L / 8, and a store instruction of store_acc_lines writes 8
-// whole lines.  Stored straight from the accumulator layout an instruction would put 16 bytes
-// into each of 64 lines: the same bytes in 16 times as many write requests, which is what the
+// wavefront-private 4 KB LDS areas: afterwards lane L holds in acc_line(q, k) the 16-byte
+// piece L % 8 of line q of row 8k + L / 8, and a store instruction of store_acc_lines writes 8
+// whole lines.  Stored straight from the accumulator layout an instruction would put 64 bytes
+// into each of 16 lines: the same bytes in twice as many write requests, which is what the
 // own-segment pass then waits for.  (LDS serves a wavefront's accesses in order: the reads
 // behind the writes need no wait of their own.)
-__device__ __forceinline__ void lines_from_acc(f32x16 (&o)[4], uint32_t area0, uint32_t area1, int lane) {
+__device__ __forceinline__ f32x4& acc_line(f32x4 (&o)[2][8], int q, int k) { return o[k >> 1][2 * q + (k & 1)]; }
+__device__ __forceinline__ const f32x4& acc_line(const f32x4 (&o)[2][8], int q, int k) { return o[k >> 1][2 * q + (k & 1)]; }
+__device__ __forceinline__ void lines_from_acc(f32x4 (&o)[2][8], uint32_t area0, uint32_t area1, int lane) {
   // LDS accesses in assembly, like the fragment reads: the compiler would put a wait for every
   // outstanding global load in front of them (it cannot tell them from a global->LDS load's target)
-  const int m_ = lane & 31, hh = lane >> 5, grp = lane >> 3, piece = lane & 7;
-  const uint32_t wr = (uint32_t)(m_ * 128), rd = (uint32_t)(grp * 128 + ((piece ^ grp) << 4));
-  uint32_t wq[4];                              // pieces rotated per row: no bank conflicts
-#pragma unroll
-  for (int q = 0; q < 4; ++q) wq[q] = wr + (uint32_t)(((hh * 4 + q) ^ (m_ & 7)) << 4);
+  const int m_ = lane & 15, g = lane >> 4, grp = lane >> 3, piece = lane & 7;
+  // row r sits at line r ^ (r / 8 % 2), its pieces rotated by r: the 16 rows of a write land on 16 bank groups
+  const uint32_t wr = (uint32_t)((m_ ^ (m_ >> 3)) * 128 + ((g ^ (m_ & 7)) << 4));
+  const uint32_t rd = (uint32_t)(grp * 128 + ((piece ^ grp) << 4));
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      const int db = 2 * pass + half;
+      const int q = 2 * pass + half;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f32x4 v = {o[db][4 * q], o[db][4 * q + 1], o[db][4 * q + 2], o[db][4 * q + 3]};
-        asm volatile("ds_write_b128 %0, %1" :: "v"((half ? area1 : area0) + wq[q]), "v"(v) : "memory");
-      }
+      for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+          asm volatile("ds_write_b128 %0, %1" :: "v"((half ? area1 : area0) + 2048u * cb + (wr ^ (uint32_t)(e << 6))), "v"(o[cb][2 * q + e]) : "memory");
     }
     f32x4 r[2][4];
 #pragma unroll
     for (int half = 0; half < 2; ++half)
 #pragma unroll
       for (int k = 0; k < 4; ++k)
-        asm volatile("ds_read_b128 %0, %1" : "=v"(r[half][k]) : "v"((half ? area1 : area0) + rd + 1024u * k) : "memory");
+        asm volatile("ds_read_b128 %0, %1" : "=v"(r[half][k]) : "v"((half ? area1 : area0) + (rd ^ (uint32_t)((k & 1) << 7)) + 1024u * k) : "memory");
     asm volatile("s_waitcnt lgkmcnt(0)"
                  : "+v"(r[0][0]), "+v"(r[0][1]), "+v"(r[0][2]), "+v"(r[0][3]), "+v"(r[1][0]), "+v"(r[1][1]),
                    "+v"(r[1][2]), "+v"(r[1][3])
@@ -498,57 +552,52 @@ __device__ __forceinline__ void lines_from_acc(f32x16 (&o)[4], uint32_t area0, u
 #pragma unroll
     for (int half = 0; half < 2; ++half)
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[2 * pass + half][4 * k + e] = r[half][k][e];
+      for (int k = 0; k < 4; ++k) acc_line(o, 2 * pass + half, k) = r[half][k];
   }
 }
 // `wave_rows` = the accumulator state of the wavefront's first row; o as left by lines_from_acc.
-__device__ __forceinline__ void store_acc_lines(float* wave_rows, const f32x16 (&o)[4], int lane) {
+__device__ __forceinline__ void store_acc_lines(float* wave_rows, const f32x4 (&o)[2][8], int lane) {
   float* p = wave_rows + (lane >> 3) * kD + (lane & 7) * 4;
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+  for (int q = 0; q < 4; ++q)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const f32x4 v = {o[db][4 * k], o[db][4 * k + 1], o[db][4 * k + 2], o[db][4 * k + 3]};
-      *reinterpret_cast<f32x4*>(p + 8 * k * kD + 32 * db) = v;
-    }
+    for (int k = 0; k < 4; ++k) *reinterpret_cast<f32x4*>(p + 8 * k * kD + 32 * q) = acc_line(o, q, k);
 }
-__device__ __forceinline__ void load_acc(const float* sp, f32x16 (&o)[4]) {
+// sp0, sp1 = accumulator states of the lane's two rows + 4 * (lane / 16)
+__device__ __forceinline__ void load_acc(const float* sp0, const float* sp1, f32x4 (&o)[2][8]) {
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(sp + 32 * db + 4 * i4);
-      o[db][4 * i4] = v[0]; o[db][4 * i4 + 1] = v[1]; o[db][4 * i4 + 2] = v[2]; o[db][4 * i4 + 3] = v[3];
-    }
+  for (int db = 0; db < 8; ++db) {
+    o[0][db] = *reinterpret_cast<const f32x4*>(sp0 + 16 * db);
+    o[1][db] = *reinterpret_cast<const f32x4*>(sp1 + 16 * db);
+  }
 }
 
 // Normalise a wavefront's 32 output rows and store them as whole rows: the rows are regrouped
 // through a wavefront-private 8 KB LDS area (32 rows x 256 bytes, the 16-byte chunks of a row
 // rotated by the row number against bank conflicts), so that a store instruction writes 4
-// complete rows (8 lines) where the accumulator layout would give 16 bytes to each of 32
-// lines.  `tok` = the lane's destination row (a token index, the same in both lanes of a
-// row); `head` + tok * row_stride is its address.
+// complete rows (8 lines) where the accumulator layout would give 32 bytes to each of 16
+// lines.  `tok` = the home row's destination (a token index), `inv` its factor; `head` +
+// tok * row_stride is the row's address.
 __device__ __forceinline__ void store_o_rows(uint16_t* head, int64_t row_stride, int tok, unsigned char* area,
-                                             int lane, const f32x16 (&o)[4], float inv) {
-  const int n = lane & 31, hh = lane >> 5;
-  unsigned char* wr = area + n * 256 + 8 * hh;
+                                             int lane, const f32x4 (&o)[2][8], float inv) {
+  const int m_ = lane & 15, g = lane >> 4;
+  float factor[2];
+  both_rows(inv, factor);
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+  for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {            // dims 32*db + 8*i4 + 4*hh + (0..3)
+    for (int db = 0; db < 8; ++db) {            // dims 16*db + 4*g + (0..3) of row 16*cb + m_
       u32x2 w;
-      w.x = pack_bf16x2(o[db][4 * i4] * inv, o[db][4 * i4 + 1] * inv);
-      w.y = pack_bf16x2(o[db][4 * i4 + 2] * inv, o[db][4 * i4 + 3] * inv);
-      *reinterpret_cast<u32x2*>(wr + (((4 * db + i4) ^ (n & 15)) << 4)) = w;
+      w.x = pack_bf16x2(o[cb][db][0] * factor[cb], o[cb][db][1] * factor[cb]);
+      w.y = pack_bf16x2(o[cb][db][2] * factor[cb], o[cb][db][3] * factor[cb]);
+      *reinterpret_cast<u32x2*>(area + (16 * cb + m_) * 256 + (((2 * db + (g >> 1)) ^ m_) << 4) + 8 * (g & 1)) = w;
     }
   const int sub = lane >> 4, chunk = lane & 15;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     const int row = 4 * k + sub;
     const u32x4 v = *reinterpret_cast<const u32x4*>(area + row * 256 + ((chunk ^ (row & 15)) << 4));
-    const int t = __builtin_amdgcn_ds_bpermute(4 * row, tok);
+    const int t = __builtin_amdgcn_ds_bpermute(4 * ((row & 15) + 32 * (k >> 2)), tok);
     *reinterpret_cast<u32x4*>(head + (int64_t)t * row_stride + 8 * chunk) = v;
   }
 }

@@ -48,7 +48,6 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: branches on it are scalar
-  const int m_ = lane & 31, hh = lane >> 5;
   const int G = a.H / a.Hkv;
   const int JG = (a.S + kRowsPerWg - 1) / kRowsPerWg;   // row blocks of 128 per (z,h,n)
   const bool paired = form == kPairs;
@@ -140,10 +139,15 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a
   // rows of this wavefront in block jg: r0 .. r0 + 31 (original order), all inside the
   // segment or none (S is a multiple of 64, r0 of 32)
   auto row0 = [&](int jg) { return jg * kRowsPerWg + kRowsPerWave * wave; };
-  auto row_of = [&](int jg) { return min(row0(jg) + m_, a.S - 1); };
+  auto row_of = [&](int jg) { return min(row0(jg) + home_row(lane), a.S - 1); };        // the lane's home row
   auto tiles_of = [&](int jg) { return (min(jg * kRowsPerWg + kRowsPerWg, a.S) - 1) / kBN + 1; };
-  bf16x8 qf[8];
-  load_q(Qh + (int64_t)(nS + row_of(jg_of[0])) * a.qs[2], hh, qf);
+  bf16x8 qf[4][2];
+  auto load_rows = [&](int jg) {
+    const uint16_t* q0 = Qh + (int64_t)(nS + min(row0(jg) + (lane & 15), a.S - 1)) * a.qs[2];
+    const uint16_t* q1 = Qh + (int64_t)(nS + min(row0(jg) + (lane & 15) + 16, a.S - 1)) * a.qs[2];
+    load_q(q0, q1, lane >> 4, qf);
+  };
+  load_rows(jg_of[0]);
   OperandAddr oa;
   oa.init(lane, lds_address(smem));
   // operand addresses for step g: K(g) in K buffer g & 1, V(g-1) in V buffer (g-1) & 1 (K x2 at
@@ -153,8 +157,8 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a
   };
 
   const float c2 = a.scale_log2e;
-  f32x16 o[4];
-  f32x16 s[2];
+  f32x4 o[2][8];
+  f32x4 s[4][2];
   int gstep = 0;                                // tiles the workgroup has walked so far
   // The accumulator state of a block leaves during step 0 of the next block (`carry`: o then
   // holds it regrouped into lines; the PV products of the new block only start with step 1).
@@ -177,9 +181,9 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a
     const int nloc = tiles_of(jg);              // key tiles this block needs
     const int myn = active ? wave_pmax / kBN + 1 : 0;   // ... and this wavefront
     const bool more = bi + 1 < nblk;
-    float m_ref = -INFINITY, l_run = 0.f;
+    float m_ref[2] = {-INFINITY, -INFINITY}, l_run = 0.f;
     if (!carry) zero_acc(o);
-    bf16x8 pb_pend[4];
+    bf16x8 pb_pend[2][2];
     float alpha_pend = 1.f;
     bool grow_pend = false, pending = false;
 
@@ -187,12 +191,12 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a
     auto softmax_step = [&](int it) {
       // CausalMask only if some row of the wavefront ends inside this tile
       const bool masked = it * kBN + kBN - 1 > r0;
-      const TileStats t = masked ? softmax_tile<true>(s, c2, m_ref, l_run, it * kBN, qoff, hh)
-                                 : softmax_tile<false>(s, c2, m_ref, l_run, it * kBN, qoff, hh);
+      const TileStats t = masked ? softmax_tile<true>(s, c2, m_ref, l_run, it * kBN, qoff, lane)
+                                 : softmax_tile<false>(s, c2, m_ref, l_run, it * kBN, qoff, lane);
       pack_p(s, pb_pend);
       alpha_pend = t.alpha; grow_pend = t.grow;
       l_run = t.prev + t.mass;
-      m_ref = t.m_use;
+      m_ref[0] = t.m_use[0]; m_ref[1] = t.m_use[1];
       pending = true;
     };
     // K of the block's next tile, else tile 0: of the next block (same segment), or unused.
@@ -258,13 +262,13 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a
     }
 
     // ---- leave the un-normalised state for the prefix walk
-    if (active && hh == 0) {
+    if (active && (lane & 16) == 0) {
       const int64_t st_row = zh * a.L + nS + qoff;
       a.st_l[st_row] = l_run;
-      a.st_m[st_row] = m_ref;
+      a.st_m[st_row] = lane < 32 ? m_ref[0] : m_ref[1];
     }
     // the next block's query rows, under the last PV product and the state's way out
-    if (more) load_q(Qh + (int64_t)(nS + row_of(jg_of[bi + 1])) * a.qs[2], hh, qf);
+    if (more) load_rows(jg_of[bi + 1]);
     if (pending) {                              // the block's last tile: its V arrived during the last step
       const OperandAddr fa = aim(gstep);
       rescale(o, alpha_pend, grow_pend);

@@ -86,7 +86,6 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m_ = lane & 31, hh = lane >> 5;
   const int BM = a.BM;                                   // query tile rows: 64 or 128
   const int tpw = BM == 64 ? 2 : 1;                      // query tiles per workgroup
   const int TJ = a.S >> (BM == 64 ? 6 : 7);              // query tiles per segment
@@ -115,10 +114,10 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   const int j = jg * tpw + tile_l;              // this wavefront's permuted query tile
   const bool active = j < TJ;
 
-  // ---- the query row of this lane
+  // ---- the home row of this lane
   int qoff;
   {
-    const int r = min(j, TJ - 1) * BM + kRowsPerWave * part + m_;
+    const int r = min(j, TJ - 1) * BM + kRowsPerWave * part + home_row(lane);
     qoff = a.use_q_perm ? a.q_perm[(zh * a.N + n) * a.S + r] : r;
     qoff = min(max(qoff, 0), a.S - 1);
   }
@@ -127,7 +126,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   if constexpr (kOwn) {
     int lo = qoff, hi = qoff;
 #pragma unroll
-    for (int d = 16; d > 0; d >>= 1) { lo = min(lo, __shfl_xor(lo, d)); hi = max(hi, __shfl_xor(hi, d)); }
+    for (int d : {1, 2, 4, 8, 32}) { lo = min(lo, __shfl_xor(lo, d)); hi = max(hi, __shfl_xor(hi, d)); }
     row_lo = __builtin_amdgcn_readfirstlane(lo);
     myn = active ? __builtin_amdgcn_readfirstlane(hi) / kBN + 1 : 0;
     if (lane == 0) own_tiles[wave] = myn;
@@ -219,8 +218,10 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   }
 
   // ---- the Q fragments of the row
-  bf16x8 qf[8];
-  load_q(Qh + (int64_t)(nS + qoff) * a.qs[2], hh, qf);
+  int rows[2];                                  // the lane's two rows
+  both_rows(qoff, rows);
+  bf16x8 qf[4][2];
+  load_q(Qh + (int64_t)(nS + rows[0]) * a.qs[2], Qh + (int64_t)(nS + rows[1]) * a.qs[2], lane >> 4, qf);
   OperandAddr oa;
   oa.init(lane, lds_address(smem));
 
@@ -232,20 +233,21 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   // Without causality there is no own-segment pass: every row starts from the empty state.
   // Neither is there a state to resume in the single-launch form.
   const int64_t st_row = zh * a.L + nS + qoff;
-  float m_ref = -INFINITY, l_run = 0.f;
+  float m_ref[2] = {-INFINITY, -INFINITY}, l_run = 0.f;
   const bool no_state = kOwn || a.non_causal;
-  if (!no_state) { m_ref = a.st_m[st_row]; l_run = a.st_l[st_row]; }
-  f32x16 o[4];
-  const float* st_acc_row = a.st_acc + st_row * kD + 16 * hh;
+  if (!no_state) { both_rows(a.st_m[st_row], m_ref); l_run = a.st_l[st_row]; }
+  f32x4 o[2][8];
+  const float* st_acc_rows[2];
+  for (int cb = 0; cb < 2; ++cb) st_acc_rows[cb] = a.st_acc + (zh * a.L + nS + rows[cb]) * kD + 4 * (lane >> 4);
   auto init_acc = [&] {
     if (no_state) zero_acc(o);
-    else load_acc(st_acc_row, o);
+    else load_acc(st_acc_rows[0], st_acc_rows[1], o);
   };
   int committed = 0, issued = 0;
 
-  f32x16 s[2];
+  f32x4 s[4][2];
   TileStats ts;
-  auto softmax = [&] { ts = softmax_tile<false>(s, c2, m_ref, l_run, 0, 0, hh); };
+  auto softmax = [&] { ts = softmax_tile<false>(s, c2, m_ref, l_run, 0, 0, lane); };
 
   // ---- prefix tiles in KV_perm order with the early-stop rule: the query tile continues iff
   // some row's tile mass reaches tau * (mass so far).  The wavefronts of a tile vote through
@@ -255,15 +257,15 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   // drop; the accumulator is only ever touched by a tile that is kept.  Every wavefront runs
   // one barrier per step; one whose query tile has stopped (or that has none) drops into a
   // drain loop that only keeps fetching tiles for the others.
-  bf16x8 pb_pend[4];
-  float alpha_pend = 1.f, l_save = 0.f, m_save = 0.f;
+  bf16x8 pb_pend[2][2];
+  float alpha_pend = 1.f, l_save = 0.f;
   bool grow_pend = false;
   auto vote_word = [&](int step) { return vote + kWaves * (step & 1); };
   auto publish = [&](int step) {        // after softmax of tile `step`: vote + speculative stats
     const bool keep = __builtin_amdgcn_ballot_w64(ts.mass >= a.tau * ts.prev) != 0ull;
     vote_word(step)[wave] = keep ? 1 : 0;
-    l_save = l_run; m_save = m_ref;
-    l_run = ts.prev + ts.mass; m_ref = ts.m_use;
+    l_save = l_run;
+    l_run = ts.prev + ts.mass; m_ref[0] = ts.m_use[0]; m_ref[1] = ts.m_use[1];
     alpha_pend = ts.alpha; grow_pend = ts.grow;
     pack_p(s, pb_pend);
     ++issued;
@@ -325,7 +327,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
 #pragma clang fp contract(off)
       l_run = ts.prev + ts.mass;                // (two roundings, as in the walk with votes)
     }
-    m_ref = ts.m_use;
+    m_ref[0] = ts.m_use[0]; m_ref[1] = ts.m_use[1];
     pending = true;
   };
   // The softmax of a step behind the first.  Left to itself the compiler puts it between the PV products.
@@ -363,8 +365,8 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
           qk_tile_only<kK>(oa, qf, s);
         }
         const bool masked = it * kBN + kBN - 1 > row_lo;
-        ts = masked ? softmax_tile<true>(s, c2, m_ref, l_run, it * kBN, qoff, hh)
-                    : softmax_tile<false>(s, c2, m_ref, l_run, it * kBN, qoff, hh);
+        ts = masked ? softmax_tile<true>(s, c2, m_ref, l_run, it * kBN, qoff, lane)
+                    : softmax_tile<false>(s, c2, m_ref, l_run, it * kBN, qoff, lane);
         fold();
       } else if (pending) {                     // this wavefront's last tile, one step after its scores
         rescale(o, alpha_pend, grow_pend);
@@ -466,7 +468,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
       if (it == nall) votes = read_votes(nall - 1);   // the last tile: its vote is visible now
       wg_done = it == nall || votes.any == 0;
       if (votes.mine == 0 && a.stop_mode == 0) {
-        l_run = l_save; m_ref = m_save;
+        l_run = l_save;
       } else {
         pv_last();
         ++committed;
