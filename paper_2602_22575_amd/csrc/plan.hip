@@ -41,6 +41,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kD = 128;
 constexpr int kSampleStride = 32;  // one sampled score per this many tokens
@@ -273,6 +274,14 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 -> rows 1, 3
   x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 -> rows 2, 3
   return x;
+}
+
+// The value of another lane of a row of 16: rotated by up to 15 lanes, or neighbours swapped (data-parallel-primitive
+// moves, which the compiler folds into the instruction that uses them).
+constexpr int kRotated = 0x120, kSwapped = 0xb1;
+template <int kControl>
+__device__ __forceinline__ float lane_move(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), kControl, 0xf, 0xf, true));
 }
 
 // A value that is the same in every lane, as the scalar it is.
@@ -631,12 +640,20 @@ __device__ __forceinline__ void pool_segment(const PlanArgs& a, const Scratch& s
         return t;
       };
       float dot = chain(0.f);
+      // Moves between lanes inside the additions: as shuffles, through LDS, they bounded the pass.  Whole ranking, us,
+      // shuffles / moves: 32 heads, 4K in 512 29.3 / 27.0, 8K in 1024 47.1 / 42.4, 16K in 4096 104 / 75; 8 heads, 16K in 8192 167 /
+      // 109; 12 over 4, 5K in 1024 without causality 37 / 30; 128K in 2048 1413 / 1410 (bound by Q from memory).
       if constexpr (kLanes == 32) {
-        const float even = __shfl_xor(dot, 1);
+        const float even = lane_move<kSwapped>(dot);
         dot = chain((c & 1) ? even : 0.f);        // complete in the odd lanes
+        const u32x2 p = __builtin_amdgcn_permlane16_swap(__float_as_uint(dot), __float_as_uint(dot), false, false);
+        dot = __uint_as_float(p.x) + __uint_as_float(p.y);
       }
-#pragma unroll
-      for (int d = kLanes / 2; d >= kLanes / 16; d >>= 1) dot += __shfl_xor(dot, d);
+      // plus that of lane c ^ 8, then ^ 4, ^ 2 (and ^ 1): the sums repeat with that period, so a rotation is enough
+      dot += lane_move<kRotated + 8>(dot);
+      dot += lane_move<kRotated + 4>(dot);
+      dot += lane_move<kRotated + 2>(dot);
+      if constexpr (kLanes == 16) dot += lane_move<kRotated + 1>(dot);
       if (c == kLanes / 16 - 1) sq[row] = dot;
     }
   };
