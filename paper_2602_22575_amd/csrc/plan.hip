@@ -86,6 +86,9 @@ struct SortShape {
 using SmallSort = SortShape<256, 8>;     // 2048 keys, 29 KB: five workgroups per CU
 using MidSort = SortShape<512, 13>;      // 6656 keys, 77 KB: two per CU
 using LargeSort = SortShape<1024, 13>;   // 13312 keys, 153 KB: one per CU
+using Sort4K = SortShape<1024, 4>;       // rows that fit one sort, besides the ones above: launch_plan
+using Sort7K = SortShape<1024, 7>;
+using Sort10K = SortShape<1024, 10>;
 using QuerySort = SortShape<512, 16>;    // 8192 keys, 89 KB: one per CU
 
 // Rows longer than the sort's capacity are cut into ranges of this many keys on average.  The
@@ -1199,7 +1202,10 @@ __global__ __launch_bounds__(Shape::kThreads, 4) void split_sort_kernel(PlanArgs
 // scores s with thr[r] <= s < thr[r-1] (the first range has no upper end, the last one takes
 // all the rest, NaN included).
 //
-// kWhole     every row fits one sort.
+// kWhole     every row fits one sort.  Nothing but the row itself is read, so the rows go to the workgroups in order of
+//            their length, longest first, there and back.  (As pairs of a long and a short one on one XCD, as a scan's
+//            pieces go, some workgroups had four rows where others had two: whole ranking, us, pairs / there and back,
+//            32 heads, 7360 tokens in 320 63.7 / 56.6, 8K in 256 80 / 74, 12K in 512 83.6 / 77.2, 12 heads 54.4 / 45.0.)
 // kScan      a range's keys are collected by scanning the row (two comparisons per score); the
 //            number of keys above the range, counted on the way, is its first rank.
 // kLeftOver  the same for the ranges that split_sort_kernel has listed: normally none.
@@ -1217,12 +1223,16 @@ __global__ __launch_bounds__(Shape::kThreads, 4) void row_sort_kernel(PlanArgs a
   const SortLds<Shape> m(smem);
   const float* const scores = a.s_k ? a.s_k : sc.sk;
   const int xcd = (int)blockIdx.x & 7;
-  // items of this XCD's workgroups, or of all (kLeftOver)
-  const int nitems = kMode == kLeftOver ? (int)uniform(sc.ticket[1]) : (a.Z * a.H * pairs + 7) / 8 * slots;
-  const int stride = kMode == kLeftOver ? (int)gridDim.x : (int)gridDim.x >> 3;
+  // items of all workgroups, or of this XCD's (kScan)
+  const int ZH = a.Z * a.H, nrows = a.non_causal ? ZH * a.N : ZH * (a.N - 1);
+  const int nitems = kMode == kLeftOver ? (int)uniform(sc.ticket[1]) : kMode == kWhole ? nrows : (ZH * pairs + 7) / 8 * slots;
+  const int stride = kMode == kScan ? (int)gridDim.x >> 3 : (int)gridDim.x;
   uint32_t* const cursor = m.misc + 50;          // keys collected
   uint32_t* const nabove = m.misc + 51;          // keys above the range
-  for (int idx = kMode == kLeftOver ? (int)blockIdx.x : (int)blockIdx.x >> 3; idx < nitems; idx += stride) {
+  for (int first_idx = 0; first_idx < nitems; first_idx += stride) {
+    int idx = first_idx + (kMode == kScan ? (int)blockIdx.x >> 3 : (int)blockIdx.x);
+    if (kMode == kWhole && (first_idx / stride & 1) != 0) idx = first_idx + stride - 1 - (int)blockIdx.x;
+    if (idx >= nitems) continue;
     RowItem cur;
     int end = 0;                                 // rank behind the range, as the splitter counted it
     if (kMode == kLeftOver) {
@@ -1235,6 +1245,13 @@ __global__ __launch_bounds__(Shape::kThreads, 4) void row_sort_kernel(PlanArgs a
       cur.len = (int)kv_row_len(n, a.S, a.L, a.non_causal);
       cur.nr = row_ranges(cur.len, kCap);
       cur.base = row_base(a, cur.row_id / a.N, n);
+      cur.valid = true;
+    } else if (kMode == kWhole) {
+      const int n = a.N - 1 - idx / ZH, zh = idx % ZH;
+      cur.len = (int)kv_row_len(n, a.S, a.L, a.non_causal);
+      cur.r = 0; cur.nr = 1;
+      cur.base = row_base(a, zh, n);
+      cur.row_id = (int64_t)zh * a.N + n;
       cur.valid = true;
     } else {
       cur = row_item(a, sc, slots, pairs, xcd, idx);
@@ -1417,24 +1434,35 @@ __global__ __launch_bounds__(Shape::kThreads, 4) void row_sort_kernel(PlanArgs a
 }
 
 // ---------------------------------------------------------------------------------------
-template <class Shape, RowMode kMode>
-static void launch_row_sort(const PlanArgs& a, const Scratch& sc, int cus, hipStream_t stream) {
+template <class Shape>
+static int64_t sorts_per_cu() {
+  const int64_t by_lds = 163840 / (int64_t)Shape::kLds, by_threads = 2048 / Shape::kThreads;
+  return by_lds < by_threads ? by_lds : by_threads;
+}
+
+template <class Shape>
+static void launch_whole_rows(const PlanArgs& a, const Scratch& sc, int cus, hipStream_t stream) {
+  const int64_t rows = (int64_t)a.Z * a.H * (a.non_causal ? a.N : a.N - 1), fit = cus * sorts_per_cu<Shape>();
+  hipLaunchKernelGGL((row_sort_kernel<Shape, kWhole>), dim3((unsigned)(rows < fit || fit < 1 ? rows : fit)),
+                     dim3(Shape::kThreads), Shape::kLds, stream, a, sc, 1, 1);
+}
+
+static void launch_scan(const PlanArgs& a, const Scratch& sc, int cus, hipStream_t stream) {
   int slots = 1, pairs = a.N;
   if (a.non_causal) {
-    slots = row_ranges(a.L, Shape::kCap);
+    slots = row_ranges(a.L, MidSort::kCap);
   } else {
     pairs = a.N / 2;                             // rows 1 .. N-1: (N-1, 1), (N-2, 2), ..., the middle one alone
     for (int p = 0; p < pairs; ++p) {
       const int hi = a.N - 1 - p, lo = 1 + p;
-      const int k = row_ranges((int64_t)hi * a.S, Shape::kCap) + (lo < hi ? row_ranges((int64_t)lo * a.S, Shape::kCap) : 0);
+      const int k = row_ranges((int64_t)hi * a.S, MidSort::kCap) + (lo < hi ? row_ranges((int64_t)lo * a.S, MidSort::kCap) : 0);
       slots = k > slots ? k : slots;
     }
   }
   const int64_t per_xcd = ((int64_t)a.Z * a.H * pairs + 7) / 8 * slots;
-  const int64_t by_lds = 163840 / (int64_t)Shape::kLds, by_threads = 2048 / Shape::kThreads;
-  const int64_t fit = cus / 8 * (by_lds < by_threads ? by_lds : by_threads);
+  const int64_t fit = cus / 8 * sorts_per_cu<MidSort>();
   const int64_t groups = per_xcd < fit || fit < 1 ? per_xcd : fit;
-  hipLaunchKernelGGL((row_sort_kernel<Shape, kMode>), dim3((unsigned)(8 * groups)), dim3(Shape::kThreads), Shape::kLds,
+  hipLaunchKernelGGL((row_sort_kernel<MidSort, kScan>), dim3((unsigned)(8 * groups)), dim3(MidSort::kThreads), MidSort::kLds,
                      stream, a, sc, slots, pairs);
 }
 
@@ -1478,6 +1506,9 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
           {reinterpret_cast<const void*>(&row_sort_kernel<MidSort, kScan>), MidSort::kLds},
           {reinterpret_cast<const void*>(&row_sort_kernel<MidSort, kLeftOver>), MidSort::kLds},
           {reinterpret_cast<const void*>(&split_sort_kernel<MidSort>), MidSort::kLds + kSplitLds},
+          {reinterpret_cast<const void*>(&row_sort_kernel<Sort10K, kWhole>), Sort10K::kLds},
+          {reinterpret_cast<const void*>(&row_sort_kernel<Sort4K, kWhole>), Sort4K::kLds},
+          {reinterpret_cast<const void*>(&row_sort_kernel<Sort7K, kWhole>), Sort7K::kLds},
           {reinterpret_cast<const void*>(&row_sort_kernel<LargeSort, kWhole>), LargeSort::kLds}};
       static_assert(2 * (MidSort::kLds + kSplitLds) <= 163840, "two workgroups per CU");
       for (const auto& b : big) {
@@ -1529,10 +1560,21 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
   if (score_blocks > 0) {
     if (sc.max_ranges > 1)
       hipLaunchKernelGGL(threshold_kernel, dim3((unsigned)rows), dim3(256), 0, stream, a, sc);
-    if (sc.cap == SmallSort::kCap) launch_row_sort<SmallSort, kWhole>(a, sc, cus, stream);
-    else if (sc.cap == LargeSort::kCap) launch_row_sort<LargeSort, kWhole>(a, sc, cus, stream);
-    else if (sc.max_ranges == 1) launch_row_sort<MidSort, kWhole>(a, sc, cus, stream);
-    else if (!sc.split) launch_row_sort<MidSort, kScan>(a, sc, cus, stream);
+    if (sc.max_ranges == 1) {
+      const int64_t longest = a.non_causal ? a.L : (int64_t)a.L - a.S;
+      // With at most a row a CU, 1024 threads sort it; with more, two smaller workgroups share a CU where rows fit them.  Above
+      // 6656 keys one sort has the CU whatever its shape, and the smallest that holds the rows has the fewest empty
+      // turns.  Whole ranking, us, 32 heads unless said, in shapes of 2048, 6656 and 13312 keys only / with 4096, 7168
+      // and 10240 as well: rows of 3584, a row a CU 27.0 / 26.6 (more rows 38.0 / 42.3: not taken), 6400 (16 rows, no causality) 27.8 / 25.8,
+      // 7040 57.1 / 52.6, 7936 73.5 / 70.6, 8704 66.9 / 64.8, 9216 55.6 / 54.1.
+      const int64_t krows = (int64_t)a.Z * a.H * (a.non_causal ? a.N : a.N - 1);
+      if (longest <= SmallSort::kCap) launch_whole_rows<SmallSort>(a, sc, cus, stream);
+      else if (krows <= kOneEach && longest <= Sort4K::kCap) launch_whole_rows<Sort4K>(a, sc, cus, stream);
+      else if (krows > kOneEach && longest <= MidSort::kCap) launch_whole_rows<MidSort>(a, sc, cus, stream);
+      else if (longest <= Sort7K::kCap) launch_whole_rows<Sort7K>(a, sc, cus, stream);
+      else if (longest <= Sort10K::kCap) launch_whole_rows<Sort10K>(a, sc, cus, stream);
+      else launch_whole_rows<LargeSort>(a, sc, cus, stream);
+    } else if (!sc.split) launch_scan(a, sc, cus, stream);
     else launch_split_sort(a, sc, stream);
   }
   return hipGetLastError();
