@@ -126,21 +126,25 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+_STRIDE_OF = {"Q": "q_stride", "K": "k_stride", "V": "v_stride", "O": "o_stride"}
+
+
 def _check_qkv(params: S2OParams, **tensors):
     """The library sees only pointers: refuse tensors it would silently misread (wrong dtype,
     another device, or a memory layout that params' strides do not describe)."""
     import torch
-    dev = None
+    bf16, dev = torch.bfloat16, None
     for name, t in tensors.items():
         if t is None:
             continue
-        if t.dtype != torch.bfloat16 or not t.is_cuda:
+        if t.dtype != bf16 or not t.is_cuda:
             raise ValueError(f"{name}: expected a CUDA bfloat16 tensor, got {t.dtype} on {t.device}")
-        dev = t.device if dev is None else dev
-        if t.device != dev:
+        if dev is None:
+            dev = t.device
+        elif t.device != dev:
             raise ValueError(f"{name}: on {t.device}, the other tensors on {dev}")
-        stride = tuple(getattr(params, {"Q": "q_stride", "K": "k_stride", "V": "v_stride", "O": "o_stride"}[name]))
-        if stride == (0, 0, 0):
+        stride = getattr(params, _STRIDE_OF[name])
+        if stride[0] == 0 and stride[1] == 0 and stride[2] == 0:
             if not t.is_contiguous():
                 raise ValueError(f"{name}: params describe a packed [Z,heads,L,D] tensor but this one is not "
                                  "contiguous (pass its strides in params or call .contiguous())")
@@ -159,9 +163,11 @@ def _keep_alive_on(stream, *tensors):
 
 
 def _stream_handle(stream) -> Optional[int]:
+    if stream is not None:
+        return stream.cuda_stream or None
+    # torch.cuda.current_stream() without the Stream object around the handle: 0.3 instead of 2.9 us a call
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream or None
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
 
 
 @dataclass
@@ -185,7 +191,8 @@ def s2o_plan(Q, K, params: S2OParams, want_scores: bool = True, scratch=None, st
     import torch
     lib = load_library()
     _check_qkv(params, Q=Q, K=K)
-    sz = s2o_plan_sizes(params)
+    scratch_bytes = C.c_size_t(0)
+    _check(lib.s2o_plan_sizes(C.byref(params), None, None, None, None, None, None, C.byref(scratch_bytes)))
     dev = Q.device
     Z, H, Hkv, L, D, S = (params.batch, params.q_heads, params.kv_heads, params.seq_len,
                           params.head_dim, params.seg_len)
@@ -206,7 +213,7 @@ def s2o_plan(Q, K, params: S2OParams, want_scores: bool = True, scratch=None, st
         out.k_guide = torch.empty((Z, Hkv, D), dtype=torch.float32, device=dev)
     own_scratch = scratch is None and not static_scratch
     if own_scratch:
-        scratch = torch.empty(sz["scratch"], dtype=torch.uint8, device=dev)
+        scratch = torch.empty(scratch_bytes.value, dtype=torch.uint8, device=dev)
     out.status = torch.empty(1, dtype=torch.int32, device=dev)
     _keep_alive_on(stream, scratch if own_scratch else None, out.status, out.s_q, out.s_k, out.q_mean, out.k_guide,
                    None if maps is not None else out.q_perm, None if maps is not None else out.kv_perm)
@@ -217,11 +224,7 @@ def s2o_plan(Q, K, params: S2OParams, want_scores: bool = True, scratch=None, st
     else:
         _check(lib.s2o_plan(Q.data_ptr(), K.data_ptr(), C.byref(params), C.byref(po),
                             scratch.data_ptr(), scratch.numel(), _stream_handle(stream)))
-    if P == 0:
-        out.kv_perm = out.kv_perm[:, :, :0]
-        if out.s_k is not None:
-            out.s_k = out.s_k[:, :, :0]
-    else:
+    if P < 4 or maps is not None:                # (the buffers hold at least four entries)
         out.kv_perm = out.kv_perm[:, :, :P]
         if out.s_k is not None:
             out.s_k = out.s_k[:, :, :P]
