@@ -24,9 +24,9 @@
 //
 // Measured against the form this replaces, which scattered (key, token) pairs of all rows to
 // buckets in memory, packed the buckets into spans and sorted those (eight launches of its own,
-// Llama head shape, us for the whole ranking): 4K tokens in 512-token segments 77 -> 29, 8K in 1024
-// 110 -> 47, 32K in 2048 277 -> 179, 64K in 1024 1005 -> 731, 128K in 2048 1808 -> 1405, in 4096 1129 ->
-// 886, and 3700 -> 1440 where far-off scores had sent the old spans to their bitonic network.
+// Llama head shape, us for the whole ranking): 4K tokens in 512-token segments 77 -> 26, 8K in 1024
+// 110 -> 40, 32K in 2048 277 -> 174, 64K in 1024 1005 -> 725, 128K in 2048 1808 -> 1401, and 3700 -> 1440 where
+// far-off scores had sent the old spans to their bitonic network.
 //
 // Argsort semantics: descending score, ties by ascending index, -0 == +0.
 #include <float.h>
@@ -1498,12 +1498,12 @@ static void launch_split_sort(const PlanArgs& a, const Scratch& sc, hipStream_t 
 
 // Small inputs: s_Q and its Argsort run beside the scores, k_guide beside q_mean -- one launch less
 // in the chain, and the query sort out of it, for a second read of Q that the caches serve.  us for the whole
-// ranking, sort in front / beside (32 heads over 8; 25 is what the calls take): 64 rows of 512 28.0 / 25.7, 256 of 256
-// 28.7 / 26.8, 256 of 512 34.2 / 29.1, 128 of 1024 40.7 / 38.2, 320 of 64 31.1 / 26.4.  Alone it also gains a little beyond these
-// lines (192 of 768 38.0 / 35.3, 256 of 768 41.7 / 39.4, 320 of 512 39.9 / 34.6, 256 of 1024 47.5 / 47.5; 512 of 512 54.4 / 59.8), but
+// ranking, sort in front / beside, 32 heads over 8 (20 is what the calls take): 64 rows of 512 23.8 / 19.2, 256 of 256
+// 25.9 / 20.8, 256 of 512 29.8 / 26.2, 128 of 1024 31.9 / 31.6, 320 of 64 22.8 / 20.1, 384 of 128 24.3 / 20.3.  Alone it also gains
+// a little beyond these lines (192 of 768 31.3 / 30.6, 256 of 768 36.3 / 35.3, 320 of 512 34.8 / 32.0; 256 of 1024 40.0 / 41.9), but
 // a layer runs it beside the own-segment pass, where the larger second launch and the second read weigh more.  A
-// layer's time, 32, 16, 8 and 4 heads: 320 rows of 64 0.95, 0.97, 0.97, 0.94, of 128 0.98, 0.94, 0.94, 0.95; on the other side
-// 256 of 768 1.02, 1.02, 1.01, 1.02, 256 of 896 1.02, 1.02, 1.00, 1.00, 384 of 256 0.99, 1.03, 1.03, 1.01, 320 of 512 1.01, 0.98, 1.00, 1.00.
+// layer up to its walk, 32, 8 and 4 heads: 320 rows of 64 0.95, 0.94, 0.96, of 128 0.97, 0.96, 0.94; on the other side
+// 256 of 768 0.98, 1.01, 1.00, 512 of 256 0.98, 1.05, 1.00, 320 of 512 1.00, 0.98, 1.00.
 constexpr int64_t kBesideRows = 384;
 constexpr int64_t beside_queries(int64_t rows) { return rows <= kOneEach ? 1 << 17 : 1 << 16; }
 using PoolSort512 = SortShape<256, 2>;

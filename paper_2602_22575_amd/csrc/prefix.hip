@@ -25,9 +25,14 @@
 // came with one LDS round trip in a loop without inner loops, and K was requested before the fetches
 // (0.97, 0.96 and 0.98 to 1.00 of the time in turn; 32 heads): 8K at 1e-3 309 / 284, 32K at 5e-3 1319 / 1267, at
 // 1e-37 8064 / 7694, 128K at 2e-2 2576 / 2519, at 5e-3 4789 / 4629, at 1e-3 12092 / 11435; 128-row tiles, 128K, half
-// of the heads unstructured 20942 / 19734; one head, 2K 23.3 / 21.7.  Operand reads 4 and 8 instead of 3 and 6
-// fragments ahead: +-0; a higher wavefront priority during the products 1.00, during the softmax 1.03.  (All
-// before the steps went in pairs, below.)
+// of the heads unstructured 20942 / 19734; one head, 2K 23.3 / 21.7.  (All before the steps went in pairs, below, and
+// with 32x32x16 products; prefetch depth and wavefront priority of the present ones: attn_tile.h.)
+//
+// Other splits of the work, with the present products, 32 heads, time / this kernel's.  64 rows a wavefront, one
+// wavefront a SIMD, softmax by hand between its products (half the LDS reads and fetches): 1.00 at contiguous 8K,
+// 1.19 on zero data, 1.03 to 1.6 where walks are short: one wavefront issues too slowly.  256 rows a
+// workgroup of 8 wavefronts (half the fetches), with a barrier a step 1.03 (zero data 1.22), with arrival counters in LDS and four
+// buffers each 1.06 (1.28): two independent workgroups are what keeps one's products beside the other's softmax.
 //
 // The wait that ends a step goes through the builtin (wait_fetches): behind a wait it cannot see,
 // the compiler guards the accumulator, loaded from the state in front of the loop, with waits of
