@@ -163,11 +163,15 @@ def _keep_alive_on(stream, *tensors):
 
 
 def _stream_handle(stream) -> Optional[int]:
-    if stream is not None:
-        return stream.cuda_stream or None
-    # torch.cuda.current_stream() without the Stream object around the handle: 0.3 instead of 2.9 us a call
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
+    if stream is None:
+        # torch's own entry leaves out the Stream object around the handle (0.3 instead of 2.9 us a call); it is not
+        # a public one and need not be there
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(torch.cuda.current_device()) or None
+        stream = torch.cuda.current_stream()
+    return stream.cuda_stream or None
 
 
 @dataclass
