@@ -22,7 +22,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak (published, at 2.4 GHz)
 PEAK_HBM_GBS = 8000.0
-BF16_FLOP_PER_CLK = 256 * 4 * 1024   # 256 CUs x 4 SIMDs x 1024 FLOP per clock (a 32x32x16 MFMA takes 32 clocks)
+BF16_FLOP_PER_CLK = 256 * 4 * 1024   # 256 CUs x 4 SIMDs x 1024 FLOP per clock (a 16x16x32 MFMA takes 16 clocks)
 
 
 def kernel_source_id():

@@ -17,8 +17,10 @@
 // 2000 to 2090 TFLOP/s, 32x32x16 1800 to 1860 (zero operands: 2475 both).  An operand fragment out of LDS is 1 KB and feeds two
 // instructions where it fed one: the LDS traffic is the same.  The kernels' times with this and the read order
 // below / with 32x32x16, same card: contiguous 8K x 32 heads 848 / 907 us, 32K causal without a stop rule
-// 6470 / 6940, at 5e-3 1151 / 1193, own segments of 1024 tokens at 16K 186 / 217; on zero data, where cycles count,
-// 650 / 632.
+// 6470 / 6940, at 5e-3 1151 / 1193, own segments of 1024 tokens at 16K 186 / 217.  In cycles it costs: twice the
+// products to issue, and less vector work beside them.  On zero data, which draws little power, 8K contiguous 650 / 632,
+// causal walks at 1e-37 8K 374 / 361, 32K 5665 / 5429, 128K 101.2 / 90.0 ms (without votes 96.2 / 89.5), single launch
+// 32K 6563 / 6193, own segments 128K 1896 / 1844.
 //
 // K and V tiles sit row-major (token rows of 256 bytes) in LDS, written there directly by
 // global_load_lds (no staging registers): a wavefront instruction deposits 4 gathered rows
@@ -127,15 +129,6 @@ template <int kOff>
 __device__ __forceinline__ void lds_issue_tr64(u32x2& d, uint32_t addr) {
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(kOff) : "memory");
 }
-// The named values are valid once at most kYounger LDS reads issued after them are outstanding.
-template <int kYounger>
-__device__ __forceinline__ void lds_wait(bf16x8& a, bf16x8& b) {
-  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(kYounger));
-}
-template <int kYounger>
-__device__ __forceinline__ void lds_wait(u32x2& a, u32x2& b) {
-  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(kYounger));
-}
 // All global->LDS tile loads (and every other global load) of this wavefront have landed.
 __device__ __forceinline__ void wait_tile_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // The same wait, for all but the kYoungest most recent vector-memory instructions of the
@@ -148,7 +141,8 @@ __device__ __forceinline__ void wait_fetches() {
   asm volatile("" ::: "memory");
 }
 
-// acc += a * b (kFirst: acc = a * b), the first product of a fragment behind its wait.  With the builtin the
+// acc += a * b (kFirst: acc = a * b), the first product of a fragment behind its wait: the fragment is there once at
+// most kYounger LDS reads issued after it are outstanding.  With the builtin the
 // compiler is free to give the result registers of its own, which costs a copy of the 64-register O^T per key tile,
 // and to move products away from the reads they stand between; in assembly the operand is tied.
 // The compiler then no longer sees an MFMA and inserts no wait states around it.  In front: an

@@ -228,8 +228,8 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a
       wait_fetches<0>();                        // (a wait on every path into the loop: see wait_fetches)
     }
     // One step; `par`: the parity of gstep, so that the tile buffers are constants in the reads' offsets
-    // (sixteen address additions a step less: the pass 1 to 2 % shorter, 128K 2488 -> 2445 us, 8K x 4 heads
-    // 26.4 -> 25.9).  Numerators formed against the running reference, as in the walk, are slower here: in
+    // (the address additions of a step less, sixteen then, with 32x32x16 products: the pass 1 to 2 % shorter, 128K
+    // 2488 -> 2445 us, 8K x 4 heads 26.4 -> 25.9).  Numerators formed against the running reference, as in the walk, are slower here: in
     // original order the maximum keeps rising and tiles are scored again (128K 2664 us).
     auto step = [&](auto par) {
       constexpr int kK = decltype(par)::value * kTileBytes, kV = 3 * kTileBytes - kK;

@@ -70,8 +70,8 @@ __device__ inline float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0
 
 // ---------------------------------------------------------------------------------------
 constexpr int kMapBins = 256;      // linear pieces of the map
-// Shapes of the LDS sort: threads and keys per thread; 36 fine buckets per thread, that is 4.5, 2.8, 2.8
-// and 2.3 per key for a full set of the shapes below.
+// Shapes of the LDS sort: threads and keys per thread; 36 fine buckets per thread, that is 36 / kPer per key for a
+// full set: 4.5, 2.8, 2.8, 9, 5.1, 3.6 and 2.3 for the shapes below.
 template <int kT, int kPer>
 struct SortShape {
   static constexpr int kThreads = kT, kPerThread = kPer, kCap = kT * kPer;
@@ -1587,7 +1587,11 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t stream) {
       // 6656 keys one sort has the CU whatever its shape, and the smallest that holds the rows has the fewest empty
       // turns.  Whole ranking, us, 32 heads unless said, in shapes of 2048, 6656 and 13312 keys only / with 4096, 7168
       // and 10240 as well: rows of 3584, a row a CU 27.0 / 26.6 (more rows 38.0 / 42.3: not taken), 6400 (16 rows, no causality) 27.8 / 25.8,
-      // 7040 57.1 / 52.6, 7936 73.5 / 70.6, 8704 66.9 / 64.8, 9216 55.6 / 54.1.
+      // 7040 57.1 / 52.6, 7936 73.5 / 70.6, 8704 66.9 / 64.8, 9216 55.6 / 54.1.  Up to 6656 keys a workgroup of 1024
+      // threads does not fit beside one of the own-segment pass, one of 512 does; a layer that runs the two at once shows nothing of
+      // it.  22 layers with at most a row a CU, rows of 2560 to 6400 keys, captured in a graph, time in 1024 / in 512 threads: whole layer
+      // 0.983 to 1.003 (8 heads, 6656 in 512 122.0 / 123.1 us, 32 heads, 4K in 512 153.6 / 155.3), up to its walk 0.983 to
+      // 1.010, the ranking alone 0.960 to 0.997.
       const int64_t krows = (int64_t)a.Z * a.H * (a.non_causal ? a.N : a.N - 1);
       if (longest <= SmallSort::kCap) launch_whole_rows<SmallSort>(a, sc, cus, stream);
       else if (krows <= kOneEach && longest <= Sort4K::kCap) launch_whole_rows<Sort4K>(a, sc, cus, stream);

@@ -258,8 +258,9 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
   // some row's tile mass reaches tau * (mass so far).  The wavefronts of a tile vote through
   // LDS; the vote on tile k is written before the barrier that ends step k and read at the
   // start of step k+1, where the PV product of tile k is then run, dropped, or folded in as
-  // the last one.  The statistics (l, m) are advanced speculatively and rolled back on a
-  // drop; the accumulator is only ever touched by a tile that is kept.  Every wavefront runs
+  // the last one.  The statistics (l, m) are advanced speculatively, and on a drop the mass l is
+  // rolled back: nothing reads m_ref after a stop, and the accumulator is only ever touched (rescaled
+  // included) by a tile that is kept.  Every wavefront runs
   // one barrier per step; one whose query tile has stopped (or that has none) drops into a
   // drain loop that only keeps fetching tiles for the others.
   bf16x8 pb_pend[2][2];
@@ -308,7 +309,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_prefix_kernel(const AttnArgs 
 
   // Step `it` reads K(it) in K buffer it & 1 and V(it-1), whose PV product is due, in V buffer
   // (it-1) & 1.  The walk's loops come in pairs of steps with the buffers as constants in the reads'
-  // offsets: moving the sixteen operand addresses to the other buffers at the end of every step took
+  // offsets: moving the operand addresses (sixteen then, with 32x32x16 products) to the other buffers at the end of every step took
   // 4 to 6 % of a walk without votes (8K contiguous 998 / 961 us, 32K causal 7472 / 7000, top-k at 16K 525 / 505)
   // and 1.5 to 2 % of one with votes (32 heads, 128K at 5e-3 4601 / 4495, 32K at 1e-37 7656 / 7497); the
   // own-segment tiles of the single launch 1 % (32K 2406 / 2368, 16K in original order 642 / 637; without a stop
