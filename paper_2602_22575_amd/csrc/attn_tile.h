@@ -612,16 +612,16 @@ __device__ __forceinline__ void store_o_rows(uint16_t* head, int64_t row_stride,
 // the longest share 1.18 -> 1.03 of the mean, walk 324 -> 295 us; 32K with two of 8 groups walking
 // four times as far 1.07 -> 1.02, 3290 -> 3090 us.)
 // Otherwise: runs of up to 4 of a segment's workgroups go to the XCDs in turn, shifted by 1
-// every 8 runs.  Dealt out one by one, as before, every XCD fetches every tile for itself: walk with this /
-// with runs, 4 heads, 64K tokens, 1024-token segments 2643 / 2037 us, 128K in 512 721 / 595; 12 heads, 64K in 2048
-// 2118 / 2011, 8K in 256 141 / 133.  Whole segments share a little more and
-// balance less (4 heads, 64K in 2048: 933 one by one, 938 in runs, 973 whole; 12 heads, 32K in 2048 591, 556, 569).
-// Few and long workgroups are the exception that is left: 4 heads, 128K in 2048 at 1e-3 1203 one by one, 1232 in runs.
+// every 8 runs.  Dealt out one by one every XCD fetches every tile for itself: walk at 1e-3 with this /
+// with runs, 4 heads, 64K tokens, 1024-token segments 1187 / 889 us, 128K in 512 1593 / 1212; 12 heads, 64K in 2048
+// 1976 / 1877, 8K in 256 175 / 171.  Whole segments share a little more and
+// balance less (4 heads, 64K in 2048: 881 one by one, 864 in runs, 905 whole; 12 heads, 32K in 2048 1341, 1238, 1265).
+// Few workgroups are the exception that is left: 20 heads, 8K in 1024 166 one by one, 169 in runs.
 // Shorter runs where all walks are of one length (alike) and an XCD would get so many more workgroups than one
 // by one that some of its 32 CUs have another one: 5248 tokens without causality, 12 heads (492 workgroups, 41 a
-// head) 227 us in runs of 4, which give an XCD 65 for its 64 places, 152 in runs of 3, 149 one by one; 6 heads 107 in
-// runs of 4, 95 of 2, 94 one by one; 36 heads 509 in runs of 4, 441 of 3; 4 heads, 11 segments of 1280 620 in runs of 4,
-// 396 of 2.
+// head) 224 us in runs of 4, which give an XCD 65 for its 64 places, 146 in runs of 3, 151 one by one; 6 heads 113 in
+// runs of 4, 106 of 2, 107 one by one; 36 heads 506 in runs of 4, 465 of 3; 4 heads, 11 segments of 1280 574 in runs of 4,
+// 369 of 2.
 // (Runs per segment and workgroups per run come from the host: a division takes 0.15 us of a walk that
 // may take 20.)
 struct WalkGrid {

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kThreads, 2) void s2o_local_kernel(const AttnArgs a
   // rounds takes as long as a long block that starts late, and unit by unit an XCD gets the same few
   // lengths again and again wherever the number of units is no multiple of 8.  The heads of a group
   // are 8 ids apart, on one XCD.  One block each, unit by unit / longest first, us: 2 heads over one, 50
-  // segments of 1024 tokens 59.4 / 40.2, 12 over 4, 25 of 512 49.7 / 42.2 (in pairs 56.7, 56.3).
+  // segments of 1024 tokens 60.4 / 39.9, 12 over 4, 25 of 512 50.1 / 43.7 (in pairs 56.2, 56.8).
   int z, g, n, h, pos;
   {
     const int U = a.Z * a.Hkv * a.N, b = blockIdx.x;
@@ -308,17 +308,17 @@ hipError_t launch_local(const AttnArgs& a, hipStream_t stream) {
   // hardly begun, is the kernel's time, and a block each is shorter.  With two short blocks a segment a block's
   // own start counts as well, and a block each pays only as long as it fills places that pairs leave idle.
   // In pairs / one block each, us, by the number of pairs (and tokens a segment), units a multiple of 8:
-  //   2 blocks (256)           256 17.7 / 15.2, 384 21.5 / 22.4, 512 24.5 / 26.5, 576 34.0 / 31.1, 768 37.3 / 37.5
-  //   3 (320)                  384 21.6 / 18.8, 512 22.2 / 21.7, 768 32.0 / 30.2, 896 32.5 / 33.7, 1280 44.8 / 44.7
-  //   4 (512)                  384 30.6 / 27.1, 512 32.7 / 34.5, 768 53.6 / 49.2, 896 56.9 / 57.9, 1280 91.9 / 91.1
-  //   8 and more (1024; 2048)  512 52.2 / 50.5; 94.5 / 78.4, 1024 98.4 / 98.9; 160 / 153, 1536 153 / 156; 255 / 241,
-  //                            2048 199 / 202; 326 / 327, 3072 294 / 296; 474 / 476
-  // and not a multiple (longest first), 1024: 528 76.7 / 51.5, 1008 111.7 / 95.5; 2048: 608 154 / 97, 992 192 / 153; 8192: 1536 0.88.
-  // (512 of 512 tokens are shorter in pairs alone, but not beside the ranking: a layer of 32 heads, 4K 159 / 155 us.)
+  //   2 blocks (256)           256 18.1 / 15.3, 384 22.0 / 24.4, 512 24.9 / 28.0, 576 34.4 / 31.4, 768 38.1 / 38.3
+  //   3 (320)                  384 20.8 / 19.9, 512 21.3 / 22.6, 768 32.5 / 30.1, 896 33.0 / 33.8, 1280 44.8 / 44.3
+  //   4 (512)                  384 30.5 / 29.4, 512 32.7 / 35.1, 768 52.8 / 48.8, 896 55.1 / 55.1, 1280 86.7 / 86.5
+  //   8 and more (1024; 2048)  512 51.8 / 51.7; 93.0 / 76.8, 1024 91.8 / 91.0; 158 / 148, 1536 145 / 149; 238 / 234,
+  //                            2048 190 / 194; 310 / 311, 3072 277 / 287; 461 / 463
+  // and not a multiple (longest first), 1024: 528 77.9 / 51.2, 1008 109.1 / 93.1; 2048: 608 148 / 93, 992 171 / 142; 8192: 1536 0.87.
+  // (512 of 512 tokens are shorter in pairs alone, but not beside the ranking: a layer of 32 heads, 4K 158 / 156 us.)
   // One block each goes longest first where unit by unit spreads the lengths unevenly over the XCDs, or where all
-  // are in flight at once.  Elsewhere longest first is still shorter alone (512 of 1024 tokens 47.8), but beside the
-  // ranking it lets that wait for its first places: a layer of 8 heads, 16K in 1024 170 / 178 us, in 2048
-  // 189 / 203.
+  // are in flight at once.  Elsewhere longest first can still be shorter alone (512 of 1024 tokens 46.5), but beside the
+  // ranking it lets that wait for its first places: a layer of 8 heads, 16K in 1024 237 / 247 us, in 2048
+  // 268 / 273.
   const int64_t units = (int64_t)a.Z * a.Hkv * a.N, segments = (int64_t)a.Z * a.H * a.N;
   const int64_t pairs = segments * ((JG + 1) / 2), idle = (pairs + kInFlight - 1) / kInFlight * kInFlight - pairs;
   const bool in_flight = segments * JG <= kInFlight, even = units % 8 == 0;

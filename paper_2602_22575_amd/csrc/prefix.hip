@@ -47,8 +47,8 @@
 // pipeline first.  It is bound by the matrix products: a query tile in permuted order has rows
 // anywhere in the segment and needs all S/64 own tiles where one in original order stops at its
 // diagonal, which is why a caller with a state buffer gets two launches.  Single launch against two,
-// 32 heads, 16K tokens, threshold 5e-3 (time, two launches = 1), permuted order: segments of 64 tokens 0.88, of
-// 256 0.92, of 512 0.98, of 1024 1.07, of 2048 1.25, of 4096 1.39, of 8192 1.50; original order 0.87 to 0.93.
+// 32 heads, 16K tokens, threshold 5e-3 (time, two launches = 1), permuted order: segments of 64 tokens 0.89, of
+// 256 0.92, of 512 0.96, of 1024 1.08, of 2048 1.20, of 4096 1.39, of 8192 1.53; original order 0.86 to 0.93.
 // Against the 8-wavefront workgroups (one per CU, operand reads placed by the compiler) it replaces:
 // permuted order 0.82 to 0.89 from 512-token segments on, original order 0.74 to 0.86; 16K tokens,
 // 32 heads, original order, threshold 5e-3, with the ranking 1028 -> 697 us.
@@ -534,7 +534,7 @@ hipError_t launch_prefix(const AttnArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid.blocks), dim3(kThreads), kPrefixLds, stream, a, grid);
   };
   // A threshold of 0 or less never stops, so nothing is lost by leaving the votes out (us with /
-  // without them, 32 heads: 8K 502 / 466, 32K 7416 / 7043, 128K 127186 / 116604).  The reference then
+  // without them, 32 heads: 8K 448 / 418, 32K 7296 / 6587, 128K 125166 / 110741).  The reference then
   // still moves as in the walk with votes, and the results keep its bits.  (The single launch's
   // normaliser is rounded otherwise without votes: there the votes stay.)
   const bool rule = a.stop_mode != 2, no_stop = !rule || a.tau <= 0.f;
