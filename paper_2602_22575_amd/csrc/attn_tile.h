@@ -20,7 +20,9 @@
 // 6470 / 6940, at 5e-3 1151 / 1193, own segments of 1024 tokens at 16K 186 / 217.  In cycles it costs: twice the
 // products to issue, and less vector work beside them.  On zero data, which draws little power, 8K contiguous 650 / 632,
 // causal walks at 1e-37 8K 374 / 361, 32K 5665 / 5429, 128K 101.2 / 90.0 ms (without votes 96.2 / 89.5), single launch
-// 32K 6563 / 6193, own segments 128K 1896 / 1844.
+// 32K 6563 / 6193, own segments 128K 1896 / 1844; on Gaussian data where a CU has a workgroup or two of short runs: own
+// segments alone, one head, 4K in 1024 25.5 / 24.6, 4 heads, 8K in 1024 27.3 / 26.3, 32 heads, 8K in 64 47.5 / 45.9 (in 256
+// 47.2 / 48.4, in 1024 94.8 / 98.5).
 //
 // K and V tiles sit row-major (token rows of 256 bytes) in LDS, written there directly by
 // global_load_lds (no staging registers): a wavefront instruction deposits 4 gathered rows
