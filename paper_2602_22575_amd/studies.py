@@ -30,8 +30,8 @@
   python -m paper_2602_22575_amd.studies power        is the prefix walk limited by its instruction
       schedule or by the chip's power budget?  The same dense walk (tau = 1e-37: every tile
       folded in after its vote, identical instruction stream) on the workload's Gaussian data, with V zeroed, and with
-      Q, K and V all zero, with the shader clock the driver reports sampled meanwhile: equal
-      time x clock products with very different clocks mean the cycle count is fixed and the
+      Q, K and V all zero, with the shader clock the driver reports sampled meanwhile: time x
+      clock products that differ much less than the clocks mean that the cycle count hardly changes and the
       clock is what the data's switching activity leaves of the power budget.  Followed by the
       own-segment pass on the workload's data and on zeros.
 
